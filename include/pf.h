@@ -194,8 +194,10 @@ int pf_plan_segments(const pf_pool *pool, int T, int q_tokens, int32_t *seg_tile
 
 /* Process-wide tuning switches, for tests and A/B measurements.  Each argument: -1 = leave unchanged.
  *   attn_variant  attention kernel for head_dim 128: 0 = 4 waves x 32 query rows, staged through registers;
- *                 1 = 8 waves x 32 rows in two alternating groups (the default);
- *                 2 = 4 waves x 64 rows, one wave per SIMD (measured slower than 1; kept selectable)
+ *                 1 = 8 waves x 32 rows in two alternating groups;
+ *                 2 = 4 waves x 64 rows, one wave per SIMD (measured slower than 1; kept selectable);
+ *                 -2 = chosen per launch (the default): 1, or for launches too small to fill the chip with its 256-row
+ *                 work items, items of 32 query rows whose keys are split over a workgroup's eight waves
  *   attn_queue    1 = resident workgroups fed from per-die work queues (default), 0 = one work item per workgroup
  *   seg_tiles     key tiles per work item for every head, 0 = planned per launch (default)
  *   plan_uniform  1 = the planner stops after choosing one segment length for all heads

@@ -125,7 +125,7 @@ def make_policy(p):
 
 
 def pf_set_tuning(attn_variant=-1, attn_queue=-1, seg_tiles=-1, plan_uniform=-1):
-    """Process-wide tuning switches; -1 leaves a switch unchanged."""
+    """Process-wide tuning switches; -1 leaves a switch unchanged, attn_variant=-2 gives the choice back to the library."""
     _check(lib().pf_set_tuning(int(attn_variant), int(attn_queue), int(seg_tiles), int(plan_uniform)), "pf_set_tuning")
 
 

@@ -18,7 +18,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", os.path.jo
          "-mllvm", "-amdgpu-spill-vgpr-to-agpr=0"]
 
 
-W64_KERNEL = "_Z17pf_attn_pp_kernelILi128ELi4EEv10AttnParams"
+W64_KERNEL = "_Z17pf_attn_pp_kernelILi128ELi4ELb0EEv10AttnParams"
 W64_FIRST_HIDDEN = 32     # the kernel's asm statements own a64..a255; the compiler's own code must stay below a32
 
 

@@ -43,10 +43,23 @@ constexpr int ATT_WAVES = 4;
 // weights without loss of relative precision).
 constexpr float ATT_LAZY_LOG2 = 8.0f;
 
+struct TagT { static constexpr bool value = true; };
+struct TagF { static constexpr bool value = false; };
+template <int N>
+struct IntC { static constexpr int value = N; };
+template <int B, class F, int... I>
+__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>) {
+  (f(IntC<B + I>()), ...);
+}
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  static_for_impl<B>(f, std::make_integer_sequence<int, E - B>());
+}
+
 struct AttnParams {
   const __bf16 *q, *k_cur, *v_cur, *k_pool, *v_pool;
   __bf16 *out;
-  const int32_t *sel_count, *sel_slots;
+  const int32_t *sel_slots;
   const PfWorkItem *items;
   int32_t *counters;
   int32_t *tickets;     // work-queue mode: next entry of each die's queue [PF_NUM_XCD], then the count of workgroups done; null = one item per workgroup
@@ -374,63 +387,19 @@ __device__ __forceinline__ void st_dev4(float *p, f32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
 }
 
-template <int D, int NQB, int NWAVES = ATT_WAVES>
-__device__ __forceinline__ void attn_epilogue(const AttnParams &P, const PfWorkItem &it, f32x16 (&o)[NQB][D / 32],
-                                              float (&m_run)[NQB], float (&l_run)[NQB], float *sStage, int32_t *sFlagp,
-                                              int tid) {
-  constexpr int BQ = NWAVES * 32 * NQB;
-  constexpr int NT = NWAVES * 64;
-  constexpr int NDB = D / 32;
-  constexpr int LD = D + 4;                        // row stride of the staged tile: 16-byte writes of 16 rows hit all banks
-  const int lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, g = lane >> 5;
-  const int h = it.head;
+// A partial result of item `it`: O [BQ][D], m [BQ], l [BQ] of its segment `seg`.
+template <int D, int BQ>
+__device__ __forceinline__ float *attn_partial(const AttnParams &P, const PfWorkItem &it, int seg) {
+  return P.workspace + (size_t)(it.part0 + seg * P.n_qt) * ((size_t)BQ * (D + 2));
+}
+
+// The workgroup has parked its partial result of a split head's item `it`; the last segment of the (head, query tile) to
+// arrive merges all of them.  sM, sInvL: BQ floats of LDS each, not in use.
+template <int D, int BQ, int NT>
+__device__ __forceinline__ void attn_arrive_and_merge(const AttnParams &P, const PfWorkItem &it, float *sM, float *sInvL,
+                                                      int32_t *sFlagp, int tid) {
   const float c = P.scale_log2;
-  float *sO = sStage;                              // [BQ][LD]
-  float *sM = sStage + BQ * LD, *sL = sM + BQ;     // [BQ] each
-
-  // ---- accumulators -> LDS rows ----
-#pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    const int lrow_q = (wave * NQB + qb) * 32 + l32;
-    const float lsum = partner_sum(l_run[qb]);
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4)
-        *(float4 *)(sO + lrow_q * LD + db * 32 + 8 * i4 + 4 * g) =
-            make_float4(o[qb][db][i4 * 4], o[qb][db][i4 * 4 + 1], o[qb][db][i4 * 4 + 2], o[qb][db][i4 * 4 + 3]);
-    if (g == 0) { sM[lrow_q] = m_run[qb]; sL[lrow_q] = lsum; }
-  }
-  __syncthreads();
-
-  __bf16 *oh = P.out + (size_t)h * P.head_stride;
-  if (it.nseg == 1) {
-    for (int e = tid; e < BQ * (D / 8); e += NT) {
-      const int r = e / (D / 8), d0 = (e % (D / 8)) * 8;
-      const int row = it.q0 + r;
-      if (row >= P.q_tokens) continue;
-      const float inv = 1.0f / sL[r];
-      const float4 a = *(const float4 *)(sO + r * LD + d0), b = *(const float4 *)(sO + r * LD + d0 + 4);
-      bf16x8 w;
-      w[0] = (__bf16)(a.x * inv); w[1] = (__bf16)(a.y * inv); w[2] = (__bf16)(a.z * inv); w[3] = (__bf16)(a.w * inv);
-      w[4] = (__bf16)(b.x * inv); w[5] = (__bf16)(b.y * inv); w[6] = (__bf16)(b.z * inv); w[7] = (__bf16)(b.w * inv);
-      *(bf16x8 *)(oh + (size_t)row * P.tok_stride + d0) = w;
-    }
-    return;
-  }
-
-  // ---- split head: park the unnormalised partial (O, m, l), the last segment to arrive merges ----
-  const size_t part_floats = (size_t)BQ * (D + 2);
-  {
-    float *po = P.workspace + (size_t)(it.part0 + it.seg * P.n_qt) * part_floats;
-    float *pm = po + (size_t)BQ * D;                // m[BQ] then l[BQ]
-    for (int e = tid; e < BQ * (D / 4); e += NT) {
-      const int r = e / (D / 4), d0 = (e % (D / 4)) * 4;
-      st_dev4(po + (size_t)r * D + d0, *(const f32x4 *)(sO + r * LD + d0));
-    }
-    for (int e = tid; e < 2 * BQ; e += NT) st_dev1(pm + e, sM[e]);      // sM and sL are adjacent
-  }
+  __bf16 *oh = P.out + (size_t)pf_item_head(it) * P.head_stride;
   __builtin_amdgcn_s_waitcnt(0);             // this wave's partial stores have completed
 #if PF_STRICT_FENCES
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // the memory model's own publication: release before the arrival
@@ -455,9 +424,8 @@ __device__ __forceinline__ void attn_epilogue(const AttnParams &P, const PfWorkI
   // Phase A: per query row, the maximum M over the segments' reference maxima and the total denominator
   // L = sum_s 2^((m_s-M)c) l_s.  Phase B: out = sum_s 2^((m_s-M)c) O_s / L. ----
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  float *sInvL = sL;
-  const float *base = P.workspace + (size_t)it.part0 * part_floats;
-  const size_t seg_stride = (size_t)P.n_qt * part_floats;
+  const float *base = attn_partial<D, BQ>(P, it, 0);
+  const size_t seg_stride = (size_t)P.n_qt * ((size_t)BQ * (D + 2));
   const int nseg = it.nseg;
   for (int r = tid; r < BQ; r += NT) {
     const float *pm = base + (size_t)BQ * D + r;
@@ -471,9 +439,10 @@ __device__ __forceinline__ void attn_epilogue(const AttnParams &P, const PfWorkI
     sInvL[r] = 1.0f / lsum;
   }
   __syncthreads();
-  constexpr int EG = 4;                                        // 8-channel output groups per thread in flight
-  static_assert((BQ * (D / 8)) % (NT * EG) == 0, "merge tiling");
-  for (int e0 = tid; e0 < BQ * (D / 8); e0 += NT * EG) {
+  // 8-channel output groups per thread in flight
+  constexpr int EG = BQ * (D / 8) >= 4 * NT ? 4 : 1, NE = BQ * (D / 8);
+  static_assert(NE % (NT * EG) == 0 || NE < NT, "merge tiling");
+  for (int e0 = tid; e0 < NE; e0 += NT * EG) {
     int r[EG], d0[EG];
     float mrow[EG];
     float4 acc[EG][2];
@@ -512,14 +481,72 @@ __device__ __forceinline__ void attn_epilogue(const AttnParams &P, const PfWorkI
   }
 }
 
+template <int D, int NQB, int NWAVES = ATT_WAVES>
+__device__ __forceinline__ void attn_epilogue(const AttnParams &P, const PfWorkItem &it, f32x16 (&o)[NQB][D / 32],
+                                              float (&m_run)[NQB], float (&l_run)[NQB], float *sStage, int32_t *sFlagp,
+                                              int tid) {
+  constexpr int BQ = NWAVES * 32 * NQB;
+  constexpr int NT = NWAVES * 64;
+  constexpr int NDB = D / 32;
+  constexpr int LD = D + 4;                        // row stride of the staged tile: 16-byte writes of 16 rows hit all banks
+  const int lane = tid & 63, wave = tid >> 6;
+  const int l32 = lane & 31, g = lane >> 5;
+  const int h = pf_item_head(it);
+  float *sO = sStage;                              // [BQ][LD]
+  float *sM = sStage + BQ * LD, *sL = sM + BQ;     // [BQ] each
+
+  // ---- accumulators -> LDS rows ----
+#pragma unroll
+  for (int qb = 0; qb < NQB; ++qb) {
+    const int lrow_q = (wave * NQB + qb) * 32 + l32;
+    const float lsum = partner_sum(l_run[qb]);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4)
+        *(float4 *)(sO + lrow_q * LD + db * 32 + 8 * i4 + 4 * g) =
+            make_float4(o[qb][db][i4 * 4], o[qb][db][i4 * 4 + 1], o[qb][db][i4 * 4 + 2], o[qb][db][i4 * 4 + 3]);
+    if (g == 0) { sM[lrow_q] = m_run[qb]; sL[lrow_q] = lsum; }
+  }
+  __syncthreads();
+
+  __bf16 *oh = P.out + (size_t)h * P.head_stride;
+  if (it.nseg == 1) {
+    for (int e = tid; e < BQ * (D / 8); e += NT) {
+      const int r = e / (D / 8), d0 = (e % (D / 8)) * 8;
+      const int row = it.q0 + r;
+      if (row >= P.q_tokens) continue;
+      const float inv = 1.0f / sL[r];
+      const float4 a = *(const float4 *)(sO + r * LD + d0), b = *(const float4 *)(sO + r * LD + d0 + 4);
+      bf16x8 w;
+      w[0] = (__bf16)(a.x * inv); w[1] = (__bf16)(a.y * inv); w[2] = (__bf16)(a.z * inv); w[3] = (__bf16)(a.w * inv);
+      w[4] = (__bf16)(b.x * inv); w[5] = (__bf16)(b.y * inv); w[6] = (__bf16)(b.z * inv); w[7] = (__bf16)(b.w * inv);
+      *(bf16x8 *)(oh + (size_t)row * P.tok_stride + d0) = w;
+    }
+    return;
+  }
+
+  // ---- split head: park the unnormalised partial (O, m, l), the last segment to arrive merges ----
+  {
+    float *po = attn_partial<D, BQ>(P, it, it.seg);
+    float *pm = po + (size_t)BQ * D;                // m[BQ] then l[BQ]
+    for (int e = tid; e < BQ * (D / 4); e += NT) {
+      const int r = e / (D / 4), d0 = (e % (D / 4)) * 4;
+      st_dev4(po + (size_t)r * D + d0, *(const f32x4 *)(sO + r * LD + d0));
+    }
+    for (int e = tid; e < 2 * BQ; e += NT) st_dev1(pm + e, sM[e]);      // sM and sL are adjacent
+  }
+  attn_arrive_and_merge<D, BQ, NT>(P, it, sM, sL, sFlagp, tid);
+}
+
 // ---------------------------------------------------------------------------------------------------
 // Common set-up of a workgroup: its work item, the head's key layout, its Q^T fragments.
 // ---------------------------------------------------------------------------------------------------
 template <int D>
 __device__ __forceinline__ void attn_setup_head(const AttnParams &P, const PfWorkItem &it, HeadKV &H, int tid) {
   constexpr int CPR = D / 8;
-  const int h = it.head;
-  H.n_sel = P.sel_count[h];
+  const int h = pf_item_head(it);
+  H.n_sel = pf_item_n_sel(it);
   H.tpf = P.tpf;
   H.hist_tokens = H.n_sel * P.tpf;
   H.lkv = H.hist_tokens + P.q_tokens;
@@ -538,7 +565,7 @@ template <int D, int NQB>
 __device__ __forceinline__ void attn_load_q(const AttnParams &P, const PfWorkItem &it, bf16x8 (&qf)[NQB][D / 16], int tid) {
   const int lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, g = lane >> 5;
-  const __bf16 *qh = P.q + (size_t)it.head * P.head_stride;
+  const __bf16 *qh = P.q + (size_t)pf_item_head(it) * P.head_stride;
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
     const int row = pf_min(it.q0 + (wave * NQB + qb) * 32 + l32, P.q_tokens - 1);
@@ -564,6 +591,8 @@ __device__ __forceinline__ void attn_zero(f32x16 (&o)[NQB][D / 32], float (&m_ru
       for (int i = 0; i < 16; ++i) o[qb][db][i] = 0.0f;
   }
 }
+
+#include "pf_attn_thin.h"
 
 // ---------------------------------------------------------------------------------------------------
 // Kernel 0: 32 query rows per wave, two workgroups per CU.
@@ -591,8 +620,18 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void pf_attn_kernel(AttnParams P) {
   __shared__ __attribute__((aligned(16))) char smem[K_BYTES + V_BYTES > STAGE_BYTES ? K_BYTES + V_BYTES : STAGE_BYTES];
   __shared__ int32_t sFlag;
   const PfWorkItem it = P.items[blockIdx.x];
-  if (it.head < 0) return;
+  if (it.head_sel < 0) return;
   attn_item_classic<D, 1>(P, it, (__bf16 (*)[PF_BK * (D + 8)])smem, (__bf16 (*)[PF_BK * (D + 32)])(smem + K_BYTES), &sFlag);
+}
+
+// Thin items only, one per workgroup (head_dim 64).
+template <int D>
+__global__ __launch_bounds__(THIN_WAVES * 64, 2) void pf_attn_thin_kernel(AttnParams P) {
+  __shared__ __attribute__((aligned(1024))) char smem[Thin<D>::SMEM_BYTES];
+  __shared__ int32_t sFlag;
+  const PfWorkItem it = P.items[blockIdx.x];
+  if (it.head_sel < 0) return;
+  thin_item<D>(P, it, smem, &sFlag, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -623,18 +662,6 @@ constexpr int PP_WAVES = 8;
 constexpr int PP_KSTAGES = 4;                                   // K of tile u is read in phase M(u)
 constexpr int PP_VSTAGES = 5;                                   // V of tile u is read one phase later, in M(u+1)
 constexpr int PP_TILE_BYTES = PF_BK * 128 * 2;                  // one tensor's tile, head_dim 128, unpadded
-struct TagT { static constexpr bool value = true; };
-struct TagF { static constexpr bool value = false; };
-template <int N>
-struct IntC { static constexpr int value = N; };
-template <int B, class F, int... I>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>) {
-  (f(IntC<B + I>()), ...);
-}
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-  static_for_impl<B>(f, std::make_integer_sequence<int, E - B>());
-}
 constexpr int PP_RING = 4;                                      // fragments requested ahead of their MFMA
 // LDS reads that fragments i+1 .. last of a matrix phase take (see the kernel: V^T fragments two, K one)
 constexpr int pp_reads_between(int i, int last) {
@@ -857,7 +884,7 @@ __device__ __forceinline__ void pp_wait_lgkm() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int D, int NW>
+template <int D, int NW, bool THIN = false>
 __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(AttnParams) {
   static_assert(D == 128, "tile layouts are written for 256-byte rows");
   static_assert(NW == 8 || NW == 4, "8 waves x 32 query rows, or 4 waves x 64");
@@ -871,6 +898,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
 
   // K ring, then V ring; the epilogue reuses the same memory to stage the output rows
   static_assert((PP_KSTAGES + PP_VSTAGES) * PP_TILE_BYTES >= attn_stage_floats(256, D) * 4, "output staging fits");
+  static_assert((PP_KSTAGES + PP_VSTAGES) * PP_TILE_BYTES >= Thin<D>::SMEM_BYTES, "thin items fit");
   __shared__ __attribute__((aligned(1024))) char smem[(PP_KSTAGES + PP_VSTAGES) * PP_TILE_BYTES];
   __shared__ int32_t sFlag;
   __shared__ int32_t sNext;
@@ -901,7 +929,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     AttnParams R = __builtin_bit_cast(AttnParams, pw);
     // pointers rebuilt from raw words: say again that they point to global memory
     R.q = as_global(R.q), R.k_cur = as_global(R.k_cur), R.v_cur = as_global(R.v_cur), R.k_pool = as_global(R.k_pool);
-    R.v_pool = as_global(R.v_pool), R.out = as_global(R.out), R.sel_count = as_global(R.sel_count);
+    R.v_pool = as_global(R.v_pool), R.out = as_global(R.out);
     R.sel_slots = as_global(R.sel_slots), R.items = as_global(R.items), R.counters = as_global(R.counters);
     R.tickets = as_global(R.tickets), R.workspace = as_global(R.workspace);
     return R;
@@ -934,7 +962,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
   hop_v = hop;
   if (item_idx < 0) break;
   const PfWorkItem it = P.items[item_idx];
-  if (it.head < 0) continue;
+  if (it.head_sel < 0) continue;
   if (__builtin_expect(P.block_trace != nullptr, 0) && tid0 == 0) {
     const long long now = wall_clock64();
     if (sTrace[3] == 0) sTrace[1] = now;
@@ -943,6 +971,9 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
   }
   int tid = tid0;
   asm volatile("" : "+v"(tid));               // per-lane constants are worked out anew for each item, not kept across the loop
+  if constexpr (THIN) {
+    thin_item<D>(P, it, smem, &sFlag, tid);
+  } else {
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave >> 2;
@@ -1484,7 +1515,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
   }
   const AttnParams Pe = load_params();                         // read again: nothing of it is held through the loop above
   attn_epilogue<D, NQB, NW>(Pe, it, o, m_run, l_run, (float *)&sK[0][0], &sFlag, tid);
-  if (__builtin_expect(Pe.block_trace != nullptr, 0) && tid0 == 0) {
+  }
+  if (__builtin_expect(load_params().block_trace != nullptr, 0) && tid0 == 0) {
     const long long now = wall_clock64();
     sTrace[0] += now - sTrace[2];
     sTrace[2] = now;                                           // doubles as "last end"
@@ -1532,7 +1564,10 @@ extern "C" int pf_set_block_trace(void *dev_buffer, size_t bytes) {
 }
 
 static int launch_attn(const AttnParams &P, int head_dim, int variant, int n_blocks, hipStream_t stream) {
-  if (head_dim == 128 && variant == 1)
+  if (head_dim == 128 && variant == PF_THIN_VARIANT)
+    hipLaunchKernelGGL((pf_attn_pp_kernel<128, 8, true>), dim3(P.tickets ? pf_min(n_blocks, pp_resident_workgroups()) : n_blocks),
+                       dim3(8 * 64), 0, stream, P);
+  else if (head_dim == 128 && variant == 1)
     hipLaunchKernelGGL((pf_attn_pp_kernel<128, 8>), dim3(P.tickets ? pf_min(n_blocks, pp_resident_workgroups()) : n_blocks),
                        dim3(8 * 64), 0, stream, P);
   else if (head_dim == 128 && variant == 2)
@@ -1540,6 +1575,8 @@ static int launch_attn(const AttnParams &P, int head_dim, int variant, int n_blo
                        dim3(4 * 64), 0, stream, P);
   else if (head_dim == 128 && variant == 0)
     hipLaunchKernelGGL((pf_attn_kernel<128>), dim3(n_blocks), dim3(ATT_THREADS), 0, stream, P);
+  else if (head_dim == 64 && variant == PF_THIN_VARIANT)
+    hipLaunchKernelGGL((pf_attn_thin_kernel<64>), dim3(n_blocks), dim3(THIN_WAVES * 64), 0, stream, P);
   else if (head_dim == 64 && variant == 0)
     hipLaunchKernelGGL((pf_attn_kernel<64>), dim3(n_blocks), dim3(ATT_THREADS), 0, stream, P);
   else
@@ -1568,7 +1605,7 @@ static int attn_fwd_impl(const pf_pool *pool, const pf_index *index, const void 
     return PF_ERR_INVALID_ARG;
   if (!index->sel_count || !index->sel_slots || !index->work) return PF_ERR_INVALID_ARG;
   if (index->q_tokens != q_tokens || index->T_built != pool->T_host) return PF_ERR_INVALID_ARG;  // stale index
-  if (index->variant < 0 || index->variant >= PF_NUM_VARIANTS || index->n_blocks < 1) return PF_ERR_INVALID_ARG;
+  if (index->variant < 0 || index->variant >= PF_NUM_KERNELS || index->n_blocks < 1) return PF_ERR_INVALID_ARG;
   if (!(softmax_scale >= 0.0f) || softmax_scale > 1.0e6f) return PF_ERR_INVALID_ARG;
   const int bq = pf_variant_bq(index->variant);
   const size_t need = (size_t)index->n_partials * pf_partial_bytes(bq, pool->head_dim);
@@ -1584,7 +1621,6 @@ static int attn_fwd_impl(const pf_pool *pool, const pf_index *index, const void 
   P.k_pool = (const __bf16 *)pool->k_pool;
   P.v_pool = (const __bf16 *)pool->v_pool;
   P.out = (__bf16 *)out;
-  P.sel_count = index->sel_count;
   P.sel_slots = index->sel_slots;
   P.items = (const PfWorkItem *)(w + L.items_off);
   P.counters = (int32_t *)(w + L.counters_off);
@@ -1637,7 +1673,7 @@ static int static_scratch_ptr(void **out) {
 extern "C" int pf_ragged_attn_fwd_static(const pf_pool *pool, const pf_index *index, const void *q, const void *k_cur,
                                          const void *v_cur, void *out, int q_tokens, float softmax_scale, void *stream) {
   if (!pool || !index) return PF_ERR_INVALID_ARG;
-  if (index->variant < 0 || index->variant >= PF_NUM_VARIANTS || index->n_partials < 0) return PF_ERR_INVALID_ARG;
+  if (index->variant < 0 || index->variant >= PF_NUM_KERNELS || index->n_partials < 0) return PF_ERR_INVALID_ARG;
   if (pool->head_dim != 64 && pool->head_dim != 128) return PF_ERR_UNSUPPORTED;
   const size_t need = (size_t)index->n_partials * pf_partial_bytes(pf_variant_bq(index->variant), pool->head_dim);
   if (need > PF_STATIC_SCRATCH_BYTES) return PF_ERR_CAPACITY;

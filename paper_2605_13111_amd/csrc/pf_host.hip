@@ -55,7 +55,7 @@ int env_int(const char *name, int dflt) {
   return e ? atoi(e) : dflt;
 }
 Tuning &tuning() {
-  static Tuning t = {env_int("PF_ATTN_VARIANT", PF_DEFAULT_VARIANT), env_int("PF_ATTN_QUEUE", 1),
+  static Tuning t = {env_int("PF_ATTN_VARIANT", -1), env_int("PF_ATTN_QUEUE", 1),
                      env_int("PF_SEG_TILES", 0), getenv("PF_PLAN_UNIFORM") ? 1 : 0};
   return t;
 }
@@ -65,6 +65,7 @@ extern "C" int pf_set_tuning(int attn_variant, int attn_queue, int seg_tiles, in
   if (attn_variant >= PF_NUM_VARIANTS || seg_tiles > (1 << 20)) return PF_ERR_INVALID_ARG;
   Tuning &t = tuning();
   if (attn_variant >= 0) t.attn_variant = attn_variant;
+  if (attn_variant == -2) t.attn_variant = -1;       // the library's own choice again
   if (attn_queue >= 0) t.attn_queue = attn_queue != 0;
   if (seg_tiles >= 0) t.seg_tiles = seg_tiles;
   if (plan_uniform >= 0) t.plan_uniform = plan_uniform != 0;
@@ -104,16 +105,35 @@ struct PlanCosts {
 };
 static const PlanCosts kCostsDirect = {8.0, 2.0, 2.0};
 static const PlanCosts kCostsQueue = {4.0, 2.0, 3.0};
+// A thin block (32 query rows, pf_attn_thin.h): its share of a full block's time per key tile, and its fixed cost.  A full
+// block's time shared by its eight groups of 32 rows would be 0.125: launches of thin blocks alone reach 600 - 675 TFLOP/s
+// where full ones reach 1020 - 1110 (one to eight layers at model shape), and are twice as fast where full ones leave most
+// of the chip idle (5 heads x 666 queries x up to 3663 keys: 32 us against 63 us).
+static const double kThinTile = 0.19, kThinBlock = 4.0;
 constexpr int PF_PLAN_ROUNDS = 3;
 constexpr int PF_PLAN_MAX_NSEG = 16;                // segment counts tried per head in step 2
 constexpr double PF_PLAN_MIN_GAIN = 0.01;           // step 2 must beat step 1 by this much to be used
 constexpr size_t PF_PLAN_CACHE = 16384;            // remembered plans (about 300 bytes each)
 
+// Blocks of a launch: n_qt query tiles per (head, segment).
+struct LaunchShape {
+  int n_qt, slots_per_die;
+  bool thin, queue;
+};
+static LaunchShape launch_shape(int variant, int q_tokens, bool queue) {
+  LaunchShape S;
+  const int bq = pf_variant_bq(variant);
+  S.n_qt = pf_ceil_div(q_tokens, bq);
+  S.slots_per_die = 32 * (variant == 0 ? 2 : 1);                  // workgroups resident per die
+  S.thin = variant == PF_THIN_VARIANT;
+  S.queue = queue;
+  return S;
+}
+
 // Finish time of the launch in which head h has key tiles n_kvt[h] cut into segments of at most seg[h] tiles.
-static double model_finish(const std::vector<int> &n_kvt, const std::vector<int> &seg, int n_qt, int slots_per_die,
-                           bool queue) {
+static double model_finish(const std::vector<int> &n_kvt, const std::vector<int> &seg, const LaunchShape &S) {
   typedef std::priority_queue<double, std::vector<double>, std::greater<double> > MinHeap;
-  const PlanCosts &C = queue ? kCostsQueue : kCostsDirect;
+  const PlanCosts &C = S.queue ? kCostsQueue : kCostsDirect;
   const int H = (int)n_kvt.size();
   // heads by descending segment length (ties: head id), as the index kernel ranks them
   std::vector<int> order(H), nsegs(H), len(H);
@@ -131,38 +151,38 @@ static double model_finish(const std::vector<int> &n_kvt, const std::vector<int>
     for (int sgi = 0; sgi < nseg; ++sgi, ++k) {
       const int row = k / PF_NUM_XCD, col = k % PF_NUM_XCD;
       const int xcd = (row & 1) ? PF_NUM_XCD - 1 - col : col;
+      const int tiles = pf_seg_begin(nk, nseg, sgi + 1) - pf_seg_begin(nk, nseg, sgi);
       // the merge falls to whichever segment arrives last; the replay charges it to the last one launched
-      teams[xcd].push_back(pf_seg_begin(nk, nseg, sgi + 1) - pf_seg_begin(nk, nseg, sgi) + C.block +
-                           (nseg > 1 ? C.split : 0.0) + (nseg > 1 && sgi == nseg - 1 ? C.merge * nseg : 0.0));
+      const double park = (nseg > 1 ? C.split : 0.0) + (nseg > 1 && sgi == nseg - 1 ? C.merge * nseg : 0.0);
+      teams[xcd].push_back(S.thin ? kThinTile * tiles + kThinBlock + park / 8 : tiles + C.block + park);
     }
   }
   double finish = 0.0;
-  if (!queue) {
+  if (!S.queue) {
     for (int x = 0; x < PF_NUM_XCD; ++x) {
       MinHeap cu;
-      for (int c = 0; c < slots_per_die; ++c) cu.push(0.0);
-      for (size_t t = 0; t < teams[x].size(); ++t)
-        for (int q = 0; q < n_qt; ++q) {
-          const double e = cu.top() + teams[x][t];
-          cu.pop();
-          cu.push(e);
-          finish = e > finish ? e : finish;
-        }
+      for (int c = 0; c < S.slots_per_die; ++c) cu.push(0.0);
+      for (size_t i = 0; i < teams[x].size() * (size_t)S.n_qt; ++i) {
+        const double e = cu.top() + teams[x][i / S.n_qt];
+        cu.pop();
+        cu.push(e);
+        finish = e > finish ? e : finish;
+      }
     }
     return finish;
   }
   // work queue: the worker that frees up first takes the next block of its die's list, else of the next die's
   typedef std::pair<double, int> Worker;             // (time it is free, home die)
   std::priority_queue<Worker, std::vector<Worker>, std::greater<Worker> > workers;
-  for (int w = 0; w < PF_NUM_XCD * slots_per_die; ++w) workers.push(Worker(0.0, w % PF_NUM_XCD));
+  for (int w = 0; w < PF_NUM_XCD * S.slots_per_die; ++w) workers.push(Worker(0.0, w % PF_NUM_XCD));
   size_t next[PF_NUM_XCD] = {};
   while (!workers.empty()) {
     const Worker w = workers.top();
     workers.pop();
     for (int hop = 0; hop < PF_NUM_XCD; ++hop) {
       const int x = (w.second + hop) % PF_NUM_XCD;
-      if (next[x] < teams[x].size() * (size_t)n_qt) {
-        const double e = w.first + teams[x][next[x] / n_qt];
+      if (next[x] < teams[x].size() * (size_t)S.n_qt) {
+        const double e = w.first + teams[x][next[x] / S.n_qt];
         ++next[x];
         finish = e > finish ? e : finish;
         workers.push(Worker(e, w.second));
@@ -184,36 +204,15 @@ struct KeyHash {
   }
 };
 std::mutex g_plan_mutex;
-std::unordered_map<std::vector<int>, PfSegPlan, KeyHash> g_plan_cache;
-}  // namespace
+struct Remembered {
+  PfSegPlan plan;
+  int variant;
+};
+std::unordered_map<std::vector<int>, Remembered, KeyHash> g_plan_cache;
 
-void pf_auto_plan(const pf_pool *pool, int T, int q_tokens, int variant, bool queue, PfSegPlan *plan) {
-  const int H = pool->n_heads;
-  const int n_qt = pf_ceil_div(q_tokens, pf_variant_bq(variant));
-  const int slots_per_die = 32 * (variant == 0 ? 2 : 1);          // workgroups resident per die
-  memset(plan, 0, sizeof(*plan));
-  plan->uniform = PF_DEFAULT_SEG_TILES;
-  std::vector<int> key(H + 2);
-  long long total = 0;
-  for (int h = 0; h < H; ++h) {
-    const int nsel = pf_sel_count_impl(pool->policy_host[h], T);
-    key[h] = pf_ceil_div(nsel * pool->tokens_per_frame + q_tokens, PF_BK);
-    total += pf_ceil_div(key[h], PF_AUTO_MIN_SEG);
-  }
-  if (total * n_qt > 50000) return;                               // keep the replay cheap on huge launches
-  const bool uniform_only = H > PF_PLAN_HEADS || tuning().plan_uniform != 0;
-  key[H] = n_qt;
-  key[H + 1] = variant * 4 + (queue ? 2 : 0) + (uniform_only ? 1 : 0);
-  {
-    std::lock_guard<std::mutex> lock(g_plan_mutex);
-    auto hit = g_plan_cache.find(key);
-    if (hit != g_plan_cache.end()) {
-      *plan = hit->second;
-      return;
-    }
-  }
-  const std::vector<int> n_kvt(key.begin(), key.begin() + H);
-
+// Segment lengths for one kernel; returns the replayed finish time.
+double plan_segments(const std::vector<int> &n_kvt, const LaunchShape &S, bool uniform_only, PfSegPlan *plan) {
+  const int H = (int)n_kvt.size();
   // Many candidate lengths cut the heads into the same segment counts: the replay runs once per distinct cut.
   std::unordered_map<std::vector<int>, double, KeyHash> seen;
   std::vector<int> cut(H);
@@ -221,7 +220,7 @@ void pf_auto_plan(const pf_pool *pool, int T, int q_tokens, int variant, bool qu
     for (int h = 0; h < H; ++h) cut[h] = pf_max(1, pf_ceil_div(n_kvt[h], seg[h]));
     auto f = seen.find(cut);
     if (f != seen.end()) return f->second;
-    const double t = model_finish(n_kvt, seg, n_qt, slots_per_die, queue);
+    const double t = model_finish(n_kvt, seg, S);
     seen.emplace(cut, t);
     return t;
   };
@@ -239,54 +238,104 @@ void pf_auto_plan(const pf_pool *pool, int T, int q_tokens, int variant, bool qu
   }
   std::fill(seg.begin(), seg.end(), plan->uniform);
   const double uniform_t = finish_of(seg);
+  if (uniform_only) return uniform_t;
 
   // step 2: per key count, the segment count of its own
-  if (!uniform_only) {
-    std::vector<int> distinct(n_kvt);
-    std::sort(distinct.begin(), distinct.end());
-    distinct.erase(std::unique(distinct.begin(), distinct.end()), distinct.end());
-    double cur_t = uniform_t;
-    for (int round = 0; round < PF_PLAN_ROUNDS; ++round) {
-      bool changed = false;
-      for (size_t d = 0; d < distinct.size(); ++d) {
-        const int nk = distinct[d];
-        int cur_seg = 0;
+  std::vector<int> distinct(n_kvt);
+  std::sort(distinct.begin(), distinct.end());
+  distinct.erase(std::unique(distinct.begin(), distinct.end()), distinct.end());
+  double cur_t = uniform_t;
+  for (int round = 0; round < PF_PLAN_ROUNDS; ++round) {
+    bool changed = false;
+    for (size_t d = 0; d < distinct.size(); ++d) {
+      const int nk = distinct[d];
+      int cur_seg = 0;
+      for (int h = 0; h < H; ++h)
+        if (n_kvt[h] == nk) cur_seg = seg[h];
+      int best_seg = cur_seg;
+      for (int n = 1; n <= PF_PLAN_MAX_NSEG; ++n) {
+        const int cand = pf_ceil_div(nk, n);
+        if (cand < PF_AUTO_MIN_SEG && n > 1) break;
+        if (cand == cur_seg) continue;
         for (int h = 0; h < H; ++h)
-          if (n_kvt[h] == nk) cur_seg = seg[h];
-        int best_seg = cur_seg;
-        for (int n = 1; n <= PF_PLAN_MAX_NSEG; ++n) {
-          const int cand = pf_ceil_div(nk, n);
-          if (cand < PF_AUTO_MIN_SEG && n > 1) break;
-          if (cand == cur_seg) continue;
-          for (int h = 0; h < H; ++h)
-            if (n_kvt[h] == nk) seg[h] = pf_max(cand, PF_AUTO_MIN_SEG);
-          const double t = finish_of(seg);
-          if (t < cur_t * 0.998) {
-            cur_t = t;
-            best_seg = pf_max(cand, PF_AUTO_MIN_SEG);
-          }
+          if (n_kvt[h] == nk) seg[h] = pf_max(cand, PF_AUTO_MIN_SEG);
+        const double t = finish_of(seg);
+        if (t < cur_t * 0.998) {
+          cur_t = t;
+          best_seg = pf_max(cand, PF_AUTO_MIN_SEG);
         }
-        for (int h = 0; h < H; ++h)
-          if (n_kvt[h] == nk) seg[h] = best_seg;
-        changed = changed || best_seg != cur_seg;
       }
-      if (!changed) break;
+      for (int h = 0; h < H; ++h)
+        if (n_kvt[h] == nk) seg[h] = best_seg;
+      changed = changed || best_seg != cur_seg;
     }
-    if (cur_t < uniform_t * (1.0 - PF_PLAN_MIN_GAIN)) {
-      plan->per_head = 1;
-      for (int h = 0; h < H; ++h) plan->seg[h] = (uint16_t)pf_min(seg[h], 65535);
+    if (!changed) break;
+  }
+  if (cur_t >= uniform_t * (1.0 - PF_PLAN_MIN_GAIN)) return uniform_t;
+  plan->per_head = 1;
+  for (int h = 0; h < H; ++h) plan->seg[h] = (uint16_t)pf_min(seg[h], 65535);
+  return cur_t;
+}
+}  // namespace
+
+int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
+  const int H = pool->n_heads;
+  const int variant = pf_resolve_variant(pool->head_dim);
+  const bool queue = pf_attn_queue_mode(variant);
+  const LaunchShape S = launch_shape(variant, q_tokens, queue);
+  memset(plan, 0, sizeof(*plan));
+  plan->uniform = PF_DEFAULT_SEG_TILES;
+  std::vector<int> key(H + 2);
+  long long total = 0, tiles = 0;
+  for (int h = 0; h < H; ++h) {
+    const int nsel = pf_sel_count_impl(pool->policy_host[h], T);
+    key[h] = pf_ceil_div(nsel * pool->tokens_per_frame + q_tokens, PF_BK);
+    total += pf_ceil_div(key[h], PF_AUTO_MIN_SEG);
+    tiles += key[h];
+  }
+  if (total * S.n_qt > 50000) return variant;                     // keep the replay cheap on huge launches
+  const bool uniform_only = H > PF_PLAN_HEADS || tuning().plan_uniform != 0;
+  const bool may_thin = tuning().attn_variant < 0 && pool->head_dim == 128 && queue;
+  key[H] = q_tokens;
+  key[H + 1] = variant * 8 + (may_thin ? 4 : 0) + (queue ? 2 : 0) + (uniform_only ? 1 : 0);
+  {
+    std::lock_guard<std::mutex> lock(g_plan_mutex);
+    auto hit = g_plan_cache.find(key);
+    if (hit != g_plan_cache.end()) {
+      *plan = hit->second.plan;
+      return hit->second.variant;
     }
   }
-
+  const std::vector<int> n_kvt(key.begin(), key.begin() + H);
+  Remembered R;
+  R.variant = variant;
+  const double finish = plan_segments(n_kvt, S, uniform_only, plan);
+  // Small launches: with 32 query rows per block there are eight times the blocks, at ~1.5x the time per row; which side
+  // wins is left to the replay.  Looked at only where it could: its work spread evenly over the chip would finish earlier.
+  if (may_thin) {
+    const LaunchShape thin = launch_shape(PF_THIN_VARIANT, q_tokens, queue);
+    const double even = thin.n_qt * (kThinTile * tiles + kThinBlock * H) / (PF_NUM_XCD * thin.slots_per_die);
+    if (even < finish && total * thin.n_qt <= PF_THIN_MAX_BLOCKS) {
+      PfSegPlan tp;
+      memset(&tp, 0, sizeof(tp));
+      if (plan_segments(n_kvt, thin, true, &tp) < finish) {
+        *plan = tp;
+        R.variant = PF_THIN_VARIANT;
+      }
+    }
+  }
+  R.plan = *plan;
   std::lock_guard<std::mutex> lock(g_plan_mutex);
   if (g_plan_cache.size() >= PF_PLAN_CACHE) g_plan_cache.clear();
-  g_plan_cache.emplace(key, *plan);
+  g_plan_cache.emplace(key, R);
+  return R.variant;
 }
 
 bool pf_attn_queue_mode(int variant) { return variant >= 1 && tuning().attn_queue != 0; }
 
 int pf_resolve_variant(int head_dim) {
   int v = tuning().attn_variant;
+  if (v == PF_THIN_VARIANT) return v;
   if (v < 0 || v >= PF_NUM_VARIANTS) v = PF_DEFAULT_VARIANT;
   return head_dim == 128 ? v : 0;                   // the pipelined kernels exist for head_dim 128 only
 }
@@ -328,10 +377,15 @@ static void worst_case(const pf_pool *pool, int q_tokens, int seg_tiles, int var
 extern "C" size_t pf_index_work_bytes(const pf_pool *pool, int q_tokens) {
   if (pf_validate_pool(pool) != PF_OK || q_tokens < 1) return 0;
   size_t need = 0;
-  for (int v = 0; v < PF_NUM_VARIANTS; ++v) {
+  for (int v = 0; v < PF_NUM_KERNELS; ++v) {
     long long mb, mp;
     int n_qt;
-    worst_case(pool, q_tokens, PF_MIN_SEG_TILES, v, &mb, &mp, &n_qt);
+    worst_case(pool, q_tokens, v == PF_THIN_VARIANT ? PF_AUTO_MIN_SEG : PF_MIN_SEG_TILES, v, &mb, &mp, &n_qt);
+    // the planner takes thin blocks only for small launches (padding: see pf_host_plan); then there are no more counters than blocks
+    if (v == PF_THIN_VARIANT && mb > PF_THIN_MAX_BLOCKS + (PF_NUM_XCD - 1) * n_qt) {
+      mb = PF_THIN_MAX_BLOCKS + (PF_NUM_XCD - 1) * (long long)n_qt;
+      n_qt = pf_min(n_qt, PF_THIN_MAX_BLOCKS / pool->n_heads);
+    }
     const size_t t = pf_work_layout(pool->n_heads, n_qt, mb).total;
     need = t > need ? t : need;
   }
@@ -344,7 +398,7 @@ extern "C" size_t pf_attn_workspace_bytes(const pf_pool *pool, int q_tokens) {
   // caller asks for shorter segments through pf_index.seg_tiles; pf_ragged_attn_fwd checks the actual need
   // against workspace_bytes.
   size_t need = 0;
-  for (int v = 0; v < PF_NUM_VARIANTS; ++v) {
+  for (int v = 0; v < PF_NUM_KERNELS; ++v) {
     long long mb, mp;
     int n_qt;
     worst_case(pool, q_tokens, pf_tuned_seg_tiles() ? pf_resolve_seg_tiles(0) : PF_AUTO_MIN_SEG, v, &mb, &mp, &n_qt);
@@ -359,13 +413,13 @@ extern "C" int pf_plan_segments(const pf_pool *pool, int T, int q_tokens, int32_
   if (pf_validate_pool(pool) != PF_OK || T < 0 || q_tokens < 1 || q_tokens > (1 << 24)) return PF_ERR_INVALID_ARG;
   for (int h = 0; h < pool->n_heads; ++h)
     if (pf_sel_count_impl(pool->policy_host[h], T) > pool->policy_host[h].slots) return PF_ERR_INVALID_ARG;
-  const int variant = pf_resolve_variant(pool->head_dim);
+  int variant = pf_resolve_variant(pool->head_dim);
   PfSegPlan plan;
   if (pf_tuned_seg_tiles()) {
     memset(&plan, 0, sizeof(plan));
     plan.uniform = pf_resolve_seg_tiles(0);
   } else {
-    pf_auto_plan(pool, T, q_tokens, variant, pf_attn_queue_mode(variant), &plan);
+    variant = pf_auto_plan(pool, T, q_tokens, &plan);
   }
   int teams, blocks, partials, max_sel;
   pf_host_plan(pool, T, q_tokens, variant, plan, &teams, &blocks, &partials, &max_sel);

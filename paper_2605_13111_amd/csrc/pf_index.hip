@@ -177,7 +177,7 @@ __global__ __launch_bounds__(INDEX_THREADS) void pf_build_index_kernel(IndexPara
     P.header->seg_tiles = P.plan.per_head ? 0 : P.plan.uniform;
     P.header->q_tokens = P.q_tokens;
   }
-  for (int b = tid; b < P.host_blocks; b += INDEX_THREADS) P.items[b].head = -1;
+  for (int b = tid; b < P.host_blocks; b += INDEX_THREADS) P.items[b].head_sel = -1;
   __syncthreads();
   if (tid == 0) P.header->error = s_error;
   if (s_error) return;                           // leave an all-empty plan: the attention launch does nothing
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(INDEX_THREADS) void pf_build_index_kernel(IndexPara
       const int row = k / PF_NUM_XCD, col = k % PF_NUM_XCD;
       const int xcd = (row & 1) ? PF_NUM_XCD - 1 - col : col;
       PfWorkItem it;
-      it.head = h;
+      it.head_sel = h | s_selcount[h] << 16;
       it.q0 = qi * P.bq;
       it.kt0 = pf_seg_begin(n_kvt, nseg, s);
       it.kt1 = pf_seg_begin(n_kvt, nseg, s + 1);
@@ -216,7 +216,7 @@ extern "C" int pf_build_index(const pf_pool *pool, pf_index *index, int q_tokens
   if (((uintptr_t)index->work) & 15u) return PF_ERR_INVALID_ARG;
   if (index->seg_tiles < 0) return PF_ERR_INVALID_ARG;
 
-  const int variant = pf_resolve_variant(pool->head_dim);
+  int variant = pf_resolve_variant(pool->head_dim);
   // segment lengths: the caller's, else the PF_SEG_TILES override, else planned for this launch
   const bool fixed = index->seg_tiles > 0 || pf_tuned_seg_tiles() > 0;
   PfSegPlan plan;
@@ -224,7 +224,7 @@ extern "C" int pf_build_index(const pf_pool *pool, pf_index *index, int q_tokens
     memset(&plan, 0, sizeof(plan));
     plan.uniform = pf_resolve_seg_tiles(index->seg_tiles);
   } else {
-    pf_auto_plan(pool, pool->T_host, q_tokens, variant, pf_attn_queue_mode(variant), &plan);
+    variant = pf_auto_plan(pool, pool->T_host, q_tokens, &plan);
   }
   int n_teams, n_blocks, n_partials, max_sel_needed;
   pf_host_plan(pool, pool->T_host, q_tokens, variant, plan, &n_teams, &n_blocks, &n_partials, &max_sel_needed);

@@ -18,10 +18,12 @@ constexpr int PF_MAX_HEADS = 1024;      // one index-kernel thread per head
 constexpr int PF_NUM_XCD = 8;           // MI355X: 8 accelerator dies, workgroup i runs on die i % 8
 constexpr int PF_NUM_VARIANTS = 3;
 constexpr int PF_DEFAULT_VARIANT = 1;   // for head_dim 128; other head sizes always use variant 0
+constexpr int PF_THIN_VARIANT = 3;      // chosen by the planner only: every work item is 32 query rows whose keys the waves split
+constexpr int PF_THIN_MAX_BLOCKS = 4096;   // ... of launches with at most this many of them
+constexpr int PF_NUM_KERNELS = 4;
 
 // query rows per workgroup of kernel variant v: 0 = 4 waves x 32 rows, 1 = 8 waves x 32 rows, 2 = 4 waves x 64 rows
-PF_HD int pf_variant_bq(int variant) { return variant == 0 ? 128 : 256; }
-
+PF_HD int pf_variant_bq(int variant) { return variant == PF_THIN_VARIANT ? 32 : variant == 0 ? 128 : 256; }
 PF_HD int pf_ceil_div(int a, int b) { return (a + b - 1) / b; }
 PF_HD int pf_min(int a, int b) { return a < b ? a : b; }
 PF_HD int pf_max(int a, int b) { return a > b ? a : b; }
@@ -113,9 +115,9 @@ struct PfSegPlan {
 };
 PF_HD int pf_seg_begin(int n_kvt, int nseg, int s) { return (int)(((long long)s * n_kvt) / nseg); }
 
-// One workgroup's job.  head < 0 = nothing to do.
+// One workgroup's job.  head_sel < 0 = nothing to do.
 struct __attribute__((aligned(32))) PfWorkItem {
-  int32_t head;
+  int32_t head_sel;    // head | selected frames << 16 (both at most 1024): the kernel needs no second table to find the keys
   int32_t q0;          // first query row
   int32_t kt0, kt1;    // key tiles [kt0, kt1)
   int32_t nseg;        // segments of this (head, query tile)
@@ -123,6 +125,9 @@ struct __attribute__((aligned(32))) PfWorkItem {
   int32_t part0;       // partial slot of segment 0 of this (head, query tile); segment s uses part0 + s*n_qt
   int32_t group;       // arrival counter index = head*n_qt + query tile
 };
+
+PF_HD int pf_item_head(const PfWorkItem &it) { return it.head_sel & 0xffff; }
+PF_HD int pf_item_n_sel(const PfWorkItem &it) { return it.head_sel >> 16; }
 
 struct __attribute__((aligned(64))) PfWorkHeader {
   int32_t n_blocks;
@@ -161,8 +166,8 @@ bool pf_chunk_layout_ok(const pf_chunk_layout *lay, int n_heads, int tokens, int
 int pf_resolve_seg_tiles(int seg_tiles);                   // 0 -> default, else clamped to the minimum
 int pf_tuned_seg_tiles();                                  // the process-wide segment-length override, 0 = none
 int pf_resolve_variant(int head_dim);                      // kernel variant in use
-// Segment length that a host replay of the launch schedule finds best for this history length.
-void pf_auto_plan(const pf_pool *pool, int T, int q_tokens, int variant, bool queue, PfSegPlan *plan);
+// Kernel variant and segment lengths that a host replay of the launch schedule finds best for this history length.
+int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan);
 bool pf_attn_queue_mode(int variant);                      // does this kernel take its blocks from the work queue?
 // Host plan for the pool's current T: per-launch block count and partial count.
 void pf_host_plan(const pf_pool *pool, int T, int q_tokens, int variant, const PfSegPlan &plan,
