@@ -42,6 +42,13 @@ constexpr int ATT_WAVES = 4;
 // must be rescaled: weights stay below 2^8 (fp32 and bf16 share the 8-bit exponent, so both hold such
 // weights without loss of relative precision).
 constexpr float ATT_LAZY_LOG2 = 8.0f;
+// The same bound seen from a lane's sum of one tile's weights (no weight exceeds their sum), which the row sum needs anyway:
+// a wave forms its weights against the reference it has and looks for the tile's maximum only when a sum is too large, to move
+// the reference and form them again.  Without the maximum of every tile in front of them the weights take 17 instructions
+// fewer per tile, and none waits for a chain of maxima: eight layers at 57 frames 5675 -> 5577 us (1098 -> 1117 TFLOP/s),
+// one-frame chunks 1141 -> 1123 us.  The second forming runs once at most, so odd scores (infinite, or so large that
+// scaling rounds past the bound) cannot hold a wave.
+constexpr float ATT_MAX_TILE_SUM = 256.0f;
 
 struct TagT { static constexpr bool value = true; };
 struct TagF { static constexpr bool value = false; };
@@ -1201,16 +1208,17 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     }
   };
 
-  float mthr = m_run[0] + thr, mc = m_run[0] * c, l_odd = 0.0f;   // reference maximum + lazy margin, * scale; odd scores' row sum
-  // weights of two scores (key block kb, registers i and i+1): scale, exp2, add to the row sums (even scores into l_run,
-  // odd ones into l_odd; plain fp32 adds: a dot-product instruction goes through the matrix pipe and queues there behind
+  float mc = m_run[0] * c, l_odd = 0.0f;                         // reference maximum * scale; odd scores' row sum
+  // weights of two scores (key block kb, registers i and i+1): scale, exp2, add to the tile's sums (even scores into ts[0],
+  // odd ones into ts[1]; plain fp32 adds: a dot-product instruction goes through the matrix pipe and queues there behind
   // the other group's MFMAs, measured ~54 cycles each next to a saturated MFMA stream, against 4 alone), round to bf16
+  float ts[2];
   auto softmax_pair = [&](auto kbv, auto iv) __attribute__((always_inline)) {
     constexpr int kb = decltype(kbv)::value, i = decltype(iv)::value;
     const float e0 = fast_exp2(fmaf(s[kb][i], c, -mc));
     const float e1 = fast_exp2(fmaf(s[kb][i + 1], c, -mc));
-    l_run[0] += e0;
-    l_odd += e1;
+    ts[0] = kb + i == 0 ? e0 : ts[0] + e0;
+    ts[1] = kb + i == 0 ? e1 : ts[1] + e1;
     pf[kb * 2 + (i >> 3)][i & 7] = (__bf16)e0;
     pf[kb * 2 + (i >> 3)][(i & 7) + 1] = (__bf16)e1;
   };
@@ -1267,22 +1275,21 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
         for (int i = 0; i < 16; ++i)
           if (kb * 32 + 8 * (i >> 2) + 4 * g_l + (i & 3) >= valid) s[kb][i] = -INFINITY;
     }
-    // maximum of this lane's 32 scores (two chains, one per key block); the check against the reference maximum is
-    // local: the two lanes of a query column exchange their maxima only when one of them has to move it
-    float mx0, mx1;
-    asm("v_max_f32 %0, %1, %2" : "=v"(mx0) : "v"(s[0][0]), "v"(s[0][1]));   // asm: no canonicalising of the MFMA's results
-    asm("v_max_f32 %0, %1, %2" : "=v"(mx1) : "v"(s[1][0]), "v"(s[1][1]));
+    auto weights = [&]() __attribute__((always_inline)) {
+      static_for<0, 16>([&](auto j) { softmax_pair(IntC<decltype(j)::value / 8>(), IntC<2 * (decltype(j)::value % 8)>()); });
+    };
+    weights();
 #pragma unroll
-    for (int i = 2; i < 16; i += 2) {
-      mx0 = fmaxf(fmaxf(mx0, s[0][i]), s[0][i + 1]);
-      mx1 = fmaxf(fmaxf(mx1, s[1][i]), s[1][i + 1]);
-    }
-    const float mxl = fmaxf(mx0, mx1);
-    if (__builtin_expect(__builtin_amdgcn_fcmpf(mxl, mthr, 2 /* ogt */) != 0, 0)) {
-      const float m_new = fmaxf(m_run[0], partner_max(mxl));
+    for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(pf[i]));   // rounded here: sunk past the branch, all 32 weights would stay in registers
+    if (__builtin_expect(__builtin_amdgcn_fcmpf(ts[0] + ts[1], ATT_MAX_TILE_SUM, 2 /* ogt */) != 0, 0)) {
+      float mx = s[0][0];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kb][i]);
+      const float m_new = fmaxf(m_run[0], partner_max(mx));
       const float alpha = fast_exp2((m_run[0] - m_new) * c);
       m_run[0] = m_new;
-      mthr = m_new + thr;
       mc = m_new * c;
       l_run[0] *= alpha;
       l_odd *= alpha;
@@ -1290,8 +1297,10 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[0][db][i] *= alpha;
+      weights();
     }
-    static_for<0, 16>([&](auto j) { softmax_pair(IntC<decltype(j)::value / 8>(), IntC<2 * (decltype(j)::value % 8)>()); });
+    l_run[0] += ts[0];
+    l_odd += ts[1];
     __builtin_amdgcn_s_barrier();
   };
 

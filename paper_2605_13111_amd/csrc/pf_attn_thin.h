@@ -61,19 +61,21 @@ __device__ __forceinline__ void thin_locate(ThinRun &R, int t, const HeadKV &H) 
   }
 }
 
-// Send the copies of one tensor's rows t .. t+31 into `dst` (NCOPY instructions whichever way).
-template <int D, bool IS_V>
-__device__ __forceinline__ void thin_copy(ThinRun &R, int t, const HeadKV &H, char *dst, int lane) {
+// Send the copies of one tensor's rows t .. t+ROWS-1 into `dst` (a place whose row number in its tile
+// is a multiple of 16, the period of the chunk permutations; ROWS / Thin<D>::COPY_ROWS instructions whichever way).
+template <int D, bool IS_V, int ROWS = THIN_KEYS>
+__device__ __forceinline__ void thin_copy(const ThinRun &R, int t, const HeadKV &H, char *dst, int lane) {
   typedef Thin<D> C;
+  constexpr int NC = ROWS / C::COPY_ROWS;
   typedef const __attribute__((address_space(1))) void *gptr_t;
   typedef __attribute__((address_space(3))) void *lptr_t;
   const int rr = lane / C::CHUNKS, p = lane % C::CHUNKS;
-  if (__builtin_expect(t + THIN_KEYS <= R.end, 1)) {             // whole step inside the run: scalar base, per-lane offset
+  if (__builtin_expect(t + ROWS <= R.end, 1)) {                  // whole step inside the run: scalar base, per-lane offset
     const long long e = (long long)(t - R.t0) * R.stride;
     const unsigned row_b = (unsigned)(R.stride * 2);
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)((IS_V ? R.v : R.k) + e), 0, (int)(THIN_KEYS * row_b), 0x00020000u);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)((IS_V ? R.v : R.k) + e), 0, (int)(ROWS * row_b), 0x00020000u);
     const unsigned low = (unsigned)((p ^ (IS_V ? C::swz_v(rr) : C::swz_k(rr))) << 4);
-    static_for<0, C::NCOPY>([&](auto gi) {
+    static_for<0, NC>([&](auto gi) {
       constexpr int G = decltype(gi)::value;
       constexpr unsigned flip = (unsigned)((IS_V ? C::swz_v(G * C::COPY_ROWS) : C::swz_k(G * C::COPY_ROWS)) << 4);
       __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)(dst + G * 1024), 16, (low ^ flip) + (unsigned)rr * row_b, G * C::COPY_ROWS * row_b, 0, 0);
@@ -84,7 +86,7 @@ __device__ __forceinline__ void thin_copy(ThinRun &R, int t, const HeadKV &H, ch
   // Rare: its per-lane values are worked out here, not held in registers through the loop
   int lane_l = lane;
   asm volatile("" : "+v"(lane_l));
-  for (int G = 0; G < C::NCOPY; ++G) {
+  for (int G = 0; G < NC; ++G) {
     const int row = G * C::COPY_ROWS + lane_l / C::CHUNKS;
     const int tt = pf_min(t + row, H.lkv - 1);
     const bool in_chunk = tt >= H.hist_tokens;
@@ -113,7 +115,10 @@ __device__ __forceinline__ void thin_wait_lds() {
 }
 
 // Fragment reads by hand: the compiler would wait for all outstanding copies before an LDS read it knows about
-__device__ __forceinline__ void thin_read_k(u32x4 &f, unsigned a) { asm volatile("ds_read_b128 %0, %1" : "=v"(f) : "v"(a)); }
+template <int OFF = 0>
+__device__ __forceinline__ void thin_read_k(u32x4 &f, unsigned a) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f) : "v"(a), "n"(OFF));
+}
 template <int OFF>
 __device__ __forceinline__ void thin_read_vt(u32x2 &f, unsigned a) {
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f) : "v"(a), "n"(OFF));
@@ -125,7 +130,7 @@ __device__ __forceinline__ void thin_keys(const AttnParams &P, const PfWorkItem 
                                           int lane, f32x16 (&o)[D / 32], float &m_run, float &l_run) {
   typedef Thin<D> C;
   const int l32 = lane & 31, g = lane >> 5;
-  const float c = P.scale_log2, thr = ATT_LAZY_LOG2 / c;
+  const float c = P.scale_log2;
   char *memK = mem, *memV = mem + C::TENSOR_BYTES;
   ThinRun R;
   thin_locate<D>(R, ta, H);
@@ -151,7 +156,7 @@ __device__ __forceinline__ void thin_keys(const AttnParams &P, const PfWorkItem 
     const int c0 = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
     av = ldsV + rowv * C::ROW_BYTES + ((c0 ^ C::swz_v(rowv)) << 4) + 8 * (lane & 1);
   }
-  float mthr = m_run + thr, mc = m_run * c, l_odd = 0.0f;
+  float mc = m_run * c, l_odd = 0.0f;
   constexpr int NVF = 2 * C::NDB;                                // V^T fragments of a step, two LDS reads each
   constexpr int VRING = NVF < 6 ? NVF : 6;                       // requested ahead (at most 15 LDS reads may be in flight)
   for (int t = ta; t < tb; t += THIN_KEYS) {
@@ -184,14 +189,27 @@ __device__ __forceinline__ void thin_keys(const AttnParams &P, const PfWorkItem 
         if (8 * (i >> 2) + 4 * g_l + (i & 3) >= valid) s[i] = -INFINITY;
     }
     // ---- online softmax, one query column per lane (as in the full items) ----
-    float mx = fmaxf(s[0], s[1]);
+    bf16x8 pf[2];
+    float ts[2];
+    auto weights = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 2; i < 16; i += 2) mx = fmaxf(fmaxf(mx, s[i]), s[i + 1]);
-    if (__builtin_expect(__builtin_amdgcn_fcmpf(mx, mthr, 2 /* ogt */) != 0, 0)) {
+      for (int i = 0; i < 16; i += 2) {
+        const float e0 = fast_exp2(fmaf(s[i], c, -mc)), e1 = fast_exp2(fmaf(s[i + 1], c, -mc));
+        ts[0] = i == 0 ? e0 : ts[0] + e0;
+        ts[1] = i == 0 ? e1 : ts[1] + e1;
+        pf[i >> 3][i & 7] = (__bf16)e0;
+        pf[i >> 3][(i & 7) + 1] = (__bf16)e1;
+      }
+    };
+    weights();
+    asm volatile("" : "+v"(pf[0]), "+v"(pf[1]));                 // rounded here: sunk past the branch, all 16 weights would stay in registers
+    if (__builtin_expect(__builtin_amdgcn_fcmpf(ts[0] + ts[1], ATT_MAX_TILE_SUM, 2 /* ogt */) != 0, 0)) {
+      float mx = s[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
       const float m_new = fmaxf(m_run, partner_max(mx));
       const float alpha = fast_exp2((m_run - m_new) * c);
       m_run = m_new;
-      mthr = m_new + thr;
       mc = m_new * c;
       l_run *= alpha;
       l_odd *= alpha;
@@ -199,16 +217,10 @@ __device__ __forceinline__ void thin_keys(const AttnParams &P, const PfWorkItem 
       for (int db = 0; db < C::NDB; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
+      weights();
     }
-    bf16x8 pf[2];
-#pragma unroll
-    for (int i = 0; i < 16; i += 2) {
-      const float e0 = fast_exp2(fmaf(s[i], c, -mc)), e1 = fast_exp2(fmaf(s[i + 1], c, -mc));
-      l_run += e0;
-      l_odd += e1;
-      pf[i >> 3][i & 7] = (__bf16)e0;
-      pf[i >> 3][(i & 7) + 1] = (__bf16)e1;
-    }
+    l_run += ts[0];
+    l_odd += ts[1];
     // ---- O^T += V^T P^T ----
     if (more) thin_wait_vm<C::NCOPY>();                          // V of this step has landed (K of the next may still travel)
     else thin_wait_vm<0>();
