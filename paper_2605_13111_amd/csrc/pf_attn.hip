@@ -2,11 +2,13 @@
 //
 // One launch per layer.  A work item is BQ query rows of one head and a run of 64-key tiles of that
 // head's ragged key sequence; heads with many keys are cut into several runs whose partial results are
-// merged by the last workgroup to finish (no spinning).  pf_attn_kernel runs one item per workgroup;
-// pf_attn_pp_kernel keeps one workgroup per compute unit resident and lets it take items from per-die queues
-// until all are empty.  Two kernels share the operand layouts below:
+// merged by the last workgroup to finish (no spinning).  pf_attn_kernel and pf_attn_d64_kernel run one item per
+// workgroup; pf_attn_pp_kernel keeps one workgroup per compute unit resident and lets it take items from per-die
+// queues until all are empty.  The kernels share the operand layouts below:
+//   pf_attn_d64_kernel BQ = 128, 4 waves x 32 query rows, four workgroups per CU, tiles copied global -> LDS
+//                      directly; head_dim 64 (pf_attn_d64.h)
 //   pf_attn_kernel     BQ = 128, 4 waves x 32 query rows, two workgroups per CU, tiles staged through
-//                      registers into padded LDS rows; any head_dim in {64, 128}
+//                      registers into padded LDS rows; head_dim 128, by request only
 //   pf_attn_pp_kernel  BQ = 256, 8 waves x 32 query rows in two groups that alternate between a matrix phase
 //                      and a vector phase, tiles copied global -> LDS directly; head_dim 128 (the default there)
 //
@@ -600,6 +602,7 @@ __device__ __forceinline__ void attn_zero(f32x16 (&o)[NQB][D / 32], float (&m_ru
 }
 
 #include "pf_attn_thin.h"
+#include "pf_attn_d64.h"
 
 // ---------------------------------------------------------------------------------------------------
 // Kernel 0: 32 query rows per wave, two workgroups per CU.
@@ -629,16 +632,6 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void pf_attn_kernel(AttnParams P) {
   const PfWorkItem it = P.items[blockIdx.x];
   if (it.head_sel < 0) return;
   attn_item_classic<D, 1>(P, it, (__bf16 (*)[PF_BK * (D + 8)])smem, (__bf16 (*)[PF_BK * (D + 32)])(smem + K_BYTES), &sFlag);
-}
-
-// Thin items only, one per workgroup (head_dim 64).
-template <int D>
-__global__ __launch_bounds__(THIN_WAVES * 64, 2) void pf_attn_thin_kernel(AttnParams P) {
-  __shared__ __attribute__((aligned(1024))) char smem[Thin<D>::SMEM_BYTES];
-  __shared__ int32_t sFlag;
-  const PfWorkItem it = P.items[blockIdx.x];
-  if (it.head_sel < 0) return;
-  thin_item<D>(P, it, smem, &sFlag, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1208,7 +1201,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     }
   };
 
-  float mc = m_run[0] * c, l_odd = 0.0f;                         // reference maximum * scale; odd scores' row sum
+  float mc = m_run[0] * c;                         // reference maximum * scale; odd scores' row sum
   // weights of two scores (key block kb, registers i and i+1): scale, exp2, add to the tile's sums (even scores into ts[0],
   // odd ones into ts[1]; plain fp32 adds: a dot-product instruction goes through the matrix pipe and queues there behind
   // the other group's MFMAs, measured ~54 cycles each next to a saturated MFMA stream, against 4 alone), round to bf16
@@ -1292,15 +1285,13 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
       m_run[0] = m_new;
       mc = m_new * c;
       l_run[0] *= alpha;
-      l_odd *= alpha;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[0][db][i] *= alpha;
       weights();
     }
-    l_run[0] += ts[0];
-    l_odd += ts[1];
+    l_run[0] += ts[0] + ts[1];
     __builtin_amdgcn_s_barrier();
   };
 
@@ -1317,7 +1308,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
   }
   m_phase(TagT(), TagF(), 0, sv, 0);
   if (grp == 0) __builtin_amdgcn_s_barrier();                  // group 0 waits for group 1's last phase
-  l_run[0] += l_odd;
   __syncthreads();
   } else {
     // ================= 4 waves x 64 query rows, one wave per SIMD =================
@@ -1584,10 +1574,8 @@ static int launch_attn(const AttnParams &P, int head_dim, int variant, int n_blo
                        dim3(4 * 64), 0, stream, P);
   else if (head_dim == 128 && variant == 0)
     hipLaunchKernelGGL((pf_attn_kernel<128>), dim3(n_blocks), dim3(ATT_THREADS), 0, stream, P);
-  else if (head_dim == 64 && variant == PF_THIN_VARIANT)
-    hipLaunchKernelGGL((pf_attn_thin_kernel<64>), dim3(n_blocks), dim3(THIN_WAVES * 64), 0, stream, P);
   else if (head_dim == 64 && variant == 0)
-    hipLaunchKernelGGL((pf_attn_kernel<64>), dim3(n_blocks), dim3(ATT_THREADS), 0, stream, P);
+    hipLaunchKernelGGL(pf_attn_d64_kernel, dim3(n_blocks), dim3(D64_WAVES * 64), 0, stream, P);
   else
     return PF_ERR_UNSUPPORTED;                      // kernel 1 exists for head_dim 128 only
   return hipGetLastError() == hipSuccess ? PF_OK : PF_ERR_HIP;

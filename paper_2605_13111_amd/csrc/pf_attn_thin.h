@@ -156,7 +156,7 @@ __device__ __forceinline__ void thin_keys(const AttnParams &P, const PfWorkItem 
     const int c0 = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
     av = ldsV + rowv * C::ROW_BYTES + ((c0 ^ C::swz_v(rowv)) << 4) + 8 * (lane & 1);
   }
-  float mc = m_run * c, l_odd = 0.0f;
+  float mc = m_run * c;
   constexpr int NVF = 2 * C::NDB;                                // V^T fragments of a step, two LDS reads each
   constexpr int VRING = NVF < 6 ? NVF : 6;                       // requested ahead (at most 15 LDS reads may be in flight)
   for (int t = ta; t < tb; t += THIN_KEYS) {
@@ -212,15 +212,13 @@ __device__ __forceinline__ void thin_keys(const AttnParams &P, const PfWorkItem 
       m_run = m_new;
       mc = m_new * c;
       l_run *= alpha;
-      l_odd *= alpha;
 #pragma unroll
       for (int db = 0; db < C::NDB; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[db][i] *= alpha;
       weights();
     }
-    l_run += ts[0];
-    l_odd += ts[1];
+    l_run += ts[0] + ts[1];
     // ---- O^T += V^T P^T ----
     if (more) thin_wait_vm<C::NCOPY>();                          // V of this step has landed (K of the next may still travel)
     else thin_wait_vm<0>();
@@ -243,7 +241,6 @@ __device__ __forceinline__ void thin_keys(const AttnParams &P, const PfWorkItem 
     });
     if (more) thin_copy<D, true>(R, t + THIN_KEYS, H, memV, lane);
   }
-  l_run += l_odd;
 }
 
 // One thin item.  smem: Thin<D>::SMEM_BYTES; every thread of the workgroup (512) calls this, nothing in smem is in use.

@@ -98,13 +98,20 @@ int pf_resolve_seg_tiles(int seg_tiles) {
 //      others stay fixed, a few rounds (pools of up to PF_PLAN_HEADS heads).
 // Plans are remembered per (key tiles of every head, query tiles, kernel, mode) in a hash table large enough for
 // whole rollouts, so a step whose shape has been seen before pays a lookup.
-static const int kSegCandidates[] = {48, 56, 64, 72, 80, 96, 112, 128, 144, 160, 176, 192, 224, 256, 320, 384};
+static const int kSegCandidates[] = {16, 24, 32, 48, 56, 64, 72, 80, 96, 112, 128, 144, 160, 176, 192, 224, 256, 320, 384};
 constexpr int PF_AUTO_MIN_SEG = 48;                 // shortest planned segment: bounds the partial-result workspace
+// head_dim 64: a launch that has no more than this many blocks even so may cut down to 16, 24 or 32 tiles.  Four workgroups fit
+// a compute unit there and the first ones gain the most: with 5 heads x 4680 queries x 74 tiles, 370 blocks take 78 us, 555
+// 63 us, 740 70 us; 6 heads x 600 queries x up to 150 tiles 47 us in 80 blocks, 39 us in 180; 12 heads x 1200 queries x up to
+// 132 tiles 59 us in 300 or 570 blocks, 69 us in 870.  The limit also bounds what such plans need of the workspace (22 MB).
+constexpr int PF_SHORT_SEG_BLOCKS = 640;
+static const int kShortSegs[] = {16, 24, 32};
 struct PlanCosts {
   double block, split, merge;                       // per block; per parked partial; per partial read back by the merging block
 };
 static const PlanCosts kCostsDirect = {8.0, 2.0, 2.0};
 static const PlanCosts kCostsQueue = {4.0, 2.0, 3.0};
+static const PlanCosts kCostsD64 = {2.0, 0.7, 0.7};  // a tile takes four times as long where four workgroups share a compute unit
 // A thin block (32 query rows, pf_attn_thin.h): its share of a full block's time per key tile, and its fixed cost.  A full
 // block's time shared by its eight groups of 32 rows would be 0.125: launches of thin blocks alone reach 600 - 675 TFLOP/s
 // where full ones reach 1020 - 1110 (one to eight layers at model shape), and are twice as fast where full ones leave most
@@ -117,23 +124,25 @@ constexpr size_t PF_PLAN_CACHE = 16384;            // remembered plans (about 30
 
 // Blocks of a launch: n_qt query tiles per (head, segment).
 struct LaunchShape {
-  int n_qt, slots_per_die;
-  bool thin, queue;
+  int n_qt, slots_per_die, min_seg;
+  bool thin, queue, d64;
 };
-static LaunchShape launch_shape(int variant, int q_tokens, bool queue) {
+static LaunchShape launch_shape(int variant, int head_dim, int q_tokens, bool queue) {
   LaunchShape S;
   const int bq = pf_variant_bq(variant);
   S.n_qt = pf_ceil_div(q_tokens, bq);
-  S.slots_per_die = 32 * (variant == 0 ? 2 : 1);                  // workgroups resident per die
+  S.slots_per_die = 32 * (variant != 0 ? 1 : head_dim == 64 ? 4 : 2);   // workgroups resident per die
   S.thin = variant == PF_THIN_VARIANT;
   S.queue = queue;
+  S.d64 = head_dim == 64;
+  S.min_seg = PF_AUTO_MIN_SEG;
   return S;
 }
 
 // Finish time of the launch in which head h has key tiles n_kvt[h] cut into segments of at most seg[h] tiles.
 static double model_finish(const std::vector<int> &n_kvt, const std::vector<int> &seg, const LaunchShape &S) {
   typedef std::priority_queue<double, std::vector<double>, std::greater<double> > MinHeap;
-  const PlanCosts &C = S.queue ? kCostsQueue : kCostsDirect;
+  const PlanCosts &C = S.d64 ? kCostsD64 : S.queue ? kCostsQueue : kCostsDirect;
   const int H = (int)n_kvt.size();
   // heads by descending segment length (ties: head id), as the index kernel ranks them
   std::vector<int> order(H), nsegs(H), len(H);
@@ -229,6 +238,7 @@ double plan_segments(const std::vector<int> &n_kvt, const LaunchShape &S, bool u
   std::vector<int> seg(H);
   double best_t = 0.0;
   for (size_t ci = 0; ci < sizeof(kSegCandidates) / sizeof(kSegCandidates[0]); ++ci) {
+    if (kSegCandidates[ci] < S.min_seg) continue;
     std::fill(seg.begin(), seg.end(), kSegCandidates[ci]);
     const double t = finish_of(seg);
     if (best_t == 0.0 || t < best_t * 0.995) {       // a longer segment must win clearly: it costs fewer partials
@@ -255,14 +265,14 @@ double plan_segments(const std::vector<int> &n_kvt, const LaunchShape &S, bool u
       int best_seg = cur_seg;
       for (int n = 1; n <= PF_PLAN_MAX_NSEG; ++n) {
         const int cand = pf_ceil_div(nk, n);
-        if (cand < PF_AUTO_MIN_SEG && n > 1) break;
+        if (cand < S.min_seg && n > 1) break;
         if (cand == cur_seg) continue;
         for (int h = 0; h < H; ++h)
-          if (n_kvt[h] == nk) seg[h] = pf_max(cand, PF_AUTO_MIN_SEG);
+          if (n_kvt[h] == nk) seg[h] = pf_max(cand, S.min_seg);
         const double t = finish_of(seg);
         if (t < cur_t * 0.998) {
           cur_t = t;
-          best_seg = pf_max(cand, PF_AUTO_MIN_SEG);
+          best_seg = pf_max(cand, S.min_seg);
         }
       }
       for (int h = 0; h < H; ++h)
@@ -276,13 +286,19 @@ double plan_segments(const std::vector<int> &n_kvt, const LaunchShape &S, bool u
   for (int h = 0; h < H; ++h) plan->seg[h] = (uint16_t)pf_min(seg[h], 65535);
   return cur_t;
 }
+
+bool plan_splits(const std::vector<int> &n_kvt, const PfSegPlan &plan) {
+  for (size_t h = 0; h < n_kvt.size(); ++h)
+    if (n_kvt[h] > plan.of((int)h)) return true;
+  return false;
+}
 }  // namespace
 
 int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
   const int H = pool->n_heads;
   const int variant = pf_resolve_variant(pool->head_dim);
   const bool queue = pf_attn_queue_mode(variant);
-  const LaunchShape S = launch_shape(variant, q_tokens, queue);
+  const LaunchShape S = launch_shape(variant, pool->head_dim, q_tokens, queue);
   memset(plan, 0, sizeof(*plan));
   plan->uniform = PF_DEFAULT_SEG_TILES;
   std::vector<int> key(H + 2);
@@ -297,7 +313,7 @@ int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
   const bool uniform_only = H > PF_PLAN_HEADS || tuning().plan_uniform != 0;
   const bool may_thin = tuning().attn_variant < 0 && pool->head_dim == 128 && queue;
   key[H] = q_tokens;
-  key[H + 1] = variant * 8 + (may_thin ? 4 : 0) + (queue ? 2 : 0) + (uniform_only ? 1 : 0);
+  key[H + 1] = (variant * 256 + pool->head_dim) * 8 + (may_thin ? 4 : 0) + (queue ? 2 : 0) + (uniform_only ? 1 : 0);
   {
     std::lock_guard<std::mutex> lock(g_plan_mutex);
     auto hit = g_plan_cache.find(key);
@@ -310,15 +326,31 @@ int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
   Remembered R;
   R.variant = variant;
   const double finish = plan_segments(n_kvt, S, uniform_only, plan);
+  // A launch whose heads fit one segment each needs no workspace, and callers may rely on that: the forms below are not
+  // allowed to bring partial results into it.
+  const bool splits = plan_splits(n_kvt, *plan);
+  if (splits && S.d64) {
+    LaunchShape fine = S;
+    for (int seg : kShortSegs) {
+      long long teams = 0;
+      for (int h = 0; h < H; ++h) teams += pf_ceil_div(n_kvt[h], seg);
+      if (teams * S.n_qt > PF_SHORT_SEG_BLOCKS) continue;
+      fine.min_seg = seg;
+      break;
+    }
+    PfSegPlan fp;
+    memset(&fp, 0, sizeof(fp));
+    if (fine.min_seg < S.min_seg && plan_segments(n_kvt, fine, uniform_only, &fp) < finish) *plan = fp;
+  }
   // Small launches: with 32 query rows per block there are eight times the blocks, at ~1.5x the time per row; which side
   // wins is left to the replay.  Looked at only where it could: its work spread evenly over the chip would finish earlier.
   if (may_thin) {
-    const LaunchShape thin = launch_shape(PF_THIN_VARIANT, q_tokens, queue);
+    const LaunchShape thin = launch_shape(PF_THIN_VARIANT, pool->head_dim, q_tokens, queue);
     const double even = thin.n_qt * (kThinTile * tiles + kThinBlock * H) / (PF_NUM_XCD * thin.slots_per_die);
     if (even < finish && total * thin.n_qt <= PF_THIN_MAX_BLOCKS) {
       PfSegPlan tp;
       memset(&tp, 0, sizeof(tp));
-      if (plan_segments(n_kvt, thin, true, &tp) < finish) {
+      if (plan_segments(n_kvt, thin, true, &tp) < finish && (splits || !plan_splits(n_kvt, tp))) {
         *plan = tp;
         R.variant = PF_THIN_VARIANT;
       }
@@ -335,7 +367,6 @@ bool pf_attn_queue_mode(int variant) { return variant >= 1 && tuning().attn_queu
 
 int pf_resolve_variant(int head_dim) {
   int v = tuning().attn_variant;
-  if (v == PF_THIN_VARIANT) return v;
   if (v < 0 || v >= PF_NUM_VARIANTS) v = PF_DEFAULT_VARIANT;
   return head_dim == 128 ? v : 0;                   // the pipelined kernels exist for head_dim 128 only
 }
@@ -402,6 +433,12 @@ extern "C" size_t pf_attn_workspace_bytes(const pf_pool *pool, int q_tokens) {
     long long mb, mp;
     int n_qt;
     worst_case(pool, q_tokens, pf_tuned_seg_tiles() ? pf_resolve_seg_tiles(0) : PF_AUTO_MIN_SEG, v, &mb, &mp, &n_qt);
+    if (pool->head_dim == 64 && v == 0 && !pf_tuned_seg_tiles()) {       // small launches may cut finer
+      long long mb_short, mp_short;
+      worst_case(pool, q_tokens, PF_MIN_SEG_TILES, v, &mb_short, &mp_short, &n_qt);
+      mp_short = mp_short < PF_SHORT_SEG_BLOCKS ? mp_short : PF_SHORT_SEG_BLOCKS;
+      mp = mp > mp_short ? mp : mp_short;
+    }
     const size_t t = (size_t)mp * pf_partial_bytes(pf_variant_bq(v), pool->head_dim);
     need = t > need ? t : need;
   }

@@ -1,0 +1,68 @@
+"""head_dim 64: GPU parity of its attention kernel at the edges of its tiles, and the bounds its launch plans keep."""
+import ctypes
+import random
+
+import pytest
+
+from paper_2605_13111_amd import binding as B
+from paper_2605_13111_amd import synth
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tpf,chunks,Lq,layout,seg_tiles", [
+    (1, [1], 1, "packed", 0),                    # two keys, one query row: three waves without rows
+    (64, [1], 32, "model", 0),                   # frames and tiles coincide; one wave has rows
+    (15, [3, 3, 3], 129, "model", 0),            # several frame borders inside one wave's 16 copied rows; a second query tile of one row
+    (17, [3, 3, 1], 127, "packed", 0),
+    (100, [3, 3, 3, 3], 128, "packed", 0),       # borders inside a copy's eight rows
+    (129, [3, 2, 3], 258, "model", 16),          # heads cut into the shortest segments, merged through the workspace
+    (700, [3, 3, 3], 600, "packed", 0),          # ... as the planner cuts a small launch by itself
+])
+def test_attention_head_dim_64(tpf, chunks, Lq, layout, seg_tiles):
+    import gpu_common as G
+    n = sum(chunks)
+    pols = [synth.anchor_all(n), synth.anchor_topk(5, 5), synth.wave(3, n), synth.wave(2, 16, cap=3, sink=1, recent=2), synth.veil(1, 3)]
+    a, r = G.run_case(pols, tpf, 64, chunks, Lq, seed=900 + tpf, layout=layout, seg_tiles=seg_tiles, label="d64")
+    print("tpf %d Lq %d max-abs %.2e rel %.2e" % (tpf, Lq, a, r))
+
+
+@pytest.mark.gpu
+def test_attention_head_dim_64_rising_scores():
+    """Queries 40 times as long: scores hundreds of exponent units apart, so the reference maximum moves often."""
+    import gpu_common as G
+    pols = [synth.anchor_all(6), synth.wave(2, 6), synth.veil(1, 3)]
+    G.run_case(pols, 100, 64, [3, 3], 150, seed=77, q_gain=40.0, label="d64-rising")
+
+
+def _host_pool(pols, tpf, head_dim):
+    H, fake = len(pols), 1 << 12                  # the planner reads the host fields only
+    hp = (B.pf_head_policy * H)(*[B.make_policy(p) for p in pols])
+    c = B.pf_pool(H, head_dim, tpf, 0, sum(int(p.slots) for p in pols), fake, fake, ctypes.cast(hp, ctypes.POINTER(B.pf_head_policy)),
+                  fake, fake, fake, fake, fake, fake, fake, 0, 0)
+    c._keep = hp
+    return c
+
+
+@pytest.mark.parametrize("head_dim,rows", [(64, (128,)), (128, (32, 256))])
+def test_plans_stay_inside_their_workspace_and_unsplit_launches_stay_unsplit(head_dim, rows):
+    """Over random pools: a plan's partial results fit pf_attn_workspace_bytes (in the smallest of the kernels' slot sizes at
+    least), and a launch whose heads are at most 48 key tiles long, which one segment covers, needs no workspace at all."""
+    rng = random.Random(5)
+    B.pf_set_tuning(attn_variant=-2, seg_tiles=0)
+    unsplit = short = 0
+    for _ in range(150):
+        T, H, n = rng.randint(0, 40), rng.randint(1, 24), rng.randint(1, 3)
+        tpf = rng.choice([1, 16, 77, 200, 333, 700, 1560])
+        pols = [p._replace(slots=max(1, B.slots_needed(p, max(T, 1)))) for p in synth.drawn_policies(H, rng.randint(0, 999), max(T, 1))]
+        c = _host_pool(pols, tpf, head_dim)
+        seg, blocks, partials = B.pf_plan_segments(c, T, n * tpf)
+        ws = int(B.lib().pf_attn_workspace_bytes(ctypes.byref(c), n * tpf))
+        assert partials * min(rows) * (head_dim + 2) * 4 <= ws
+        tiles = [-(-(B.pf_selected_count(p, T) + n) * tpf // 64) for p in pols]
+        if max(tiles) <= 48:
+            unsplit += 1
+            assert partials == 0
+        if head_dim == 64:
+            short += min(seg) < 48
+            assert min(seg) >= 48 or blocks <= 640 + 7 * -(-n * tpf // 128)
+    assert unsplit > 10 and (head_dim == 128 or short > 10)
