@@ -269,6 +269,123 @@ __global__ __launch_bounds__(POOL_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 }
 
 // ---------------------------------------------------------------------------------------------------
+// The same append where every head has at most 64 candidates (resident + new frames) and at most POOL_PREFETCH frames are
+// new, which covers a minute of video: lane j of EVERY wave holds candidate j, so a wave works the plan out for itself with
+// ballots and lane reads, without LDS, barriers or a move list, and the copy loop's slots are scalars (one scalar base per frame,
+// the thread's offset stays).  The order of the moves is the general kernel's.
+// Bound: HBM, behind a plan that all workgroups make at the same time before the first survivor can travel.  One 16-byte unit
+// per thread and frame and batches of four frames keep a wave at 42 registers, eight waves per SIMD, which hide more of that
+// than longer batches do: the 19 appends (and one index) that fill a layer with 57 frames take 454 us, in the general kernel
+// 528; batches of 8 470, two units per thread 488, non-temporal loads of the new frames faster there (457) but slower
+// where few frames move (292 against 285, 800 against 770).
+// ---------------------------------------------------------------------------------------------------
+constexpr int POOL_SMALL_CAND = 64;
+constexpr int POOL_SMALL_BATCH = 4;
+__global__ __launch_bounds__(POOL_THREADS) void pf_pool_append_small_kernel(PoolAppendParams P) {
+  const int h = blockIdx.y;
+  const bool is_v = blockIdx.z != 0;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const pf_head_policy pol = P.policy[h];
+  const int base = P.slot_base[h];
+  const int n_old = P.n_frames[h];
+  const int n_cand = n_old + P.n_new;
+  const int T_new = P.T + P.n_new;
+
+  // ---- the new frames' payload, requested before the plan is made (see the general kernel) ----
+  const pool_unit *fresh = (const pool_unit *)(is_v ? P.v_new : P.k_new) + (size_t)h * P.new_head_units;
+  const long long new_frame_units = (long long)(P.frame_units >> P.row_shift) * P.new_tok_units;
+  const int unit = blockIdx.x * POOL_THREADS + tid;
+  const bool valid = unit < P.frame_units;
+  const int unit_c = valid ? unit : 0;
+  const long long fresh_off = (long long)(unit_c >> P.row_shift) * P.new_tok_units + (unit_c & ((1 << P.row_shift) - 1));
+  pool_unit nf[POOL_PREFETCH];
+#pragma unroll
+  for (int j = 0; j < POOL_PREFETCH; ++j) nf[j] = (fresh + (size_t)pf_min(j, P.n_new - 1) * new_frame_units)[fresh_off];
+
+  // ---- plan: lane j = candidate j ----
+  const bool cand = lane < n_cand, old = lane < n_old;
+  int f = P.T + (lane - n_old);
+  float sc = 0.0f;
+  if (old) {
+    f = P.frame_ids[base + lane];
+    sc = P.frame_score[base + lane];
+  } else if (cand && P.scores) {
+    sc = P.scores[(size_t)h * P.n_new + (lane - n_old)];
+  }
+  const bool mid = cand && f >= pol.sink && f < T_new - pol.recent;
+  int rank = 0;                                               // intermediate candidates that beat this one
+  if (pol.type == PF_ANCHOR && pol.mode == PF_MODE_TOPK && pol.cap > 0) {
+    for (unsigned long long rest = __builtin_amdgcn_ballot_w64(mid); rest; rest &= rest - 1) {
+      const int g = __builtin_ctzll(rest);
+      const float sg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), g));
+      const int fg = __builtin_amdgcn_readlane(f, g);
+      rank += (sg > sc || (sg == sc && fg < f)) ? 1 : 0;
+    }
+  }
+  const bool keep = cand && (!mid || middle_kept(pol, T_new, f, rank));
+  const unsigned long long kept = __builtin_amdgcn_ballot_w64(keep);
+  const int dest = __builtin_popcountll(kept & ((1ull << lane) - 1ull));
+  // survivors that shift left, in ascending order
+  unsigned long long moves = __builtin_amdgcn_ballot_w64(keep && old && dest != lane);
+
+  pool_unit *pool = (pool_unit *)(is_v ? P.v_pool : P.k_pool) + (size_t)base * P.frame_units;
+  while (moves) {
+    pool_unit r[POOL_SMALL_BATCH];
+    unsigned long long m = moves;
+#pragma unroll
+    for (int b = 0; b < POOL_SMALL_BATCH; ++b) {              // unconditional loads (the last move again once they run out)
+      r[b] = (pool + (size_t)__builtin_ctzll(m) * P.frame_units)[unit_c];
+      const unsigned long long rest = m & (m - 1);
+      m = rest ? rest : m;
+    }
+#pragma unroll
+    for (int b = 0; b < POOL_SMALL_BATCH; ++b) {
+      if (moves) {
+        pool_unit *dp = pool + (size_t)__builtin_amdgcn_readlane(dest, __builtin_ctzll(moves)) * P.frame_units;
+        if (valid) dp[unit_c] = r[b];
+        moves &= moves - 1;
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < POOL_PREFETCH; ++j) {
+    if (j < P.n_new && (kept >> (n_old + j) & 1)) {
+      pool_unit *dp = pool + (size_t)__builtin_amdgcn_readlane(dest, n_old + j) * P.frame_units;
+      if (valid) dp[unit_c] = nf[j];
+    }
+  }
+
+  // ---- tables: by wave 0 of the head's last workgroup to arrive, after every wave has read the old ones (see the general
+  // kernel) ----
+#if PF_STRICT_FENCES
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+#endif
+  __syncthreads();
+  if (tid >= 64) return;
+  int arrived = 0;
+#if PF_STRICT_FENCES
+  if (tid == 0) arrived = __hip_atomic_fetch_add(&P.sync[h * PF_SYNC_STRIDE], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+#else
+  if (tid == 0) arrived = atomicAdd(&P.sync[h * PF_SYNC_STRIDE], 1);
+#endif
+  if (__builtin_amdgcn_readfirstlane(arrived) != 2 * P.blocks_per_head - 1) return;
+  const int n_kept = __builtin_popcountll(kept);
+  if (keep) {
+    P.frame_ids[base + dest] = f;
+    P.frame_score[base + dest] = sc;
+  }
+  if (lane >= n_kept && lane < pol.slots && cand) {           // slots freed by this append
+    P.frame_ids[base + lane] = -1;
+    P.frame_score[base + lane] = 0.0f;
+  }
+  if (lane == 0) {
+    P.n_frames[h] = n_kept;
+    P.sync[h * PF_SYNC_STRIDE] = 0;
+    if (h == 0) *P.T_dev = T_new;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------
 // Veil cache merging (Sec. 4.2): after an append, rebuild the merged frames of every Veil head that
 // has them.  Window j (0 = nearest) of head h covers frames w0 .. w0+m-1 with w0 = T-R-(j+1)m and goes to the
 // head's slot slots-1-j; row r of the merged frame is token `tok` of frame w0+i, where (i, tok) runs over
@@ -342,10 +459,13 @@ static int cache_append_impl(pf_pool *pool, const void *k_new, const void *v_new
   if ((((uintptr_t)k_new) & 15u) || (((uintptr_t)v_new) & 15u)) return PF_ERR_INVALID_ARG;
   if ((long long)pool->T_host + n_new > (1ll << 30)) return PF_ERR_INVALID_ARG;
   const int T_new = pool->T_host + n_new;
+  int most_cand = 0;
   for (int h = 0; h < pool->n_heads; ++h) {
     const pf_head_policy &p = pool->policy_host[h];
     if (pf_ret_count_impl(p, T_new) > p.slots - pf_veil_merged_slots(p)) return PF_ERR_CAPACITY;
-    if (pf_ret_count_impl(p, pool->T_host) + n_new > POOL_MAX_CAND) return PF_ERR_CAPACITY;
+    const int n_cand = pf_ret_count_impl(p, pool->T_host) + n_new;
+    if (n_cand > POOL_MAX_CAND) return PF_ERR_CAPACITY;
+    most_cand = pf_max(most_cand, n_cand);
   }
   // heads with cache merging need a second launch; its grid is checked before the first one is enqueued, so a
   // call that fails leaves host and device state as they were
@@ -368,12 +488,14 @@ static int cache_append_impl(pf_pool *pool, const void *k_new, const void *v_new
   P.T = pool->T_host;
   P.n_new = n_new;
   P.frame_units = pool->tokens_per_frame * pool->head_dim / 8;   // bf16: 8 elements per 16 bytes
-  P.blocks_per_head = pf_ceil_div(P.frame_units, POOL_CHUNK_UNITS);
+  const bool small = most_cand <= POOL_SMALL_CAND && n_new <= POOL_PREFETCH;
+  P.blocks_per_head = pf_ceil_div(P.frame_units, small ? POOL_THREADS : POOL_CHUNK_UNITS);
   P.row_shift = pool->head_dim == 128 ? 4 : 3;
   P.new_tok_units = layout ? layout->token_stride / 8 : (1 << P.row_shift);
   P.new_head_units = layout ? layout->head_stride / 8 : (long long)n_new * P.frame_units;
-  hipLaunchKernelGGL(pf_pool_append_kernel, dim3(P.blocks_per_head, pool->n_heads, 2), dim3(POOL_THREADS), 0,
-                     (hipStream_t)stream, P);
+  const dim3 grid(P.blocks_per_head, pool->n_heads, 2);
+  if (small) hipLaunchKernelGGL(pf_pool_append_small_kernel, grid, dim3(POOL_THREADS), 0, (hipStream_t)stream, P);
+  else hipLaunchKernelGGL(pf_pool_append_kernel, grid, dim3(POOL_THREADS), 0, (hipStream_t)stream, P);
   PF_HIP_CHECK(hipGetLastError());
   // heads with cache merging: a second launch rebuilds their merged frames from the frames just packed
   if (max_cap > 0) {
