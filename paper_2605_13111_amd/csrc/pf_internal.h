@@ -113,7 +113,10 @@ struct PfSegPlan {
   uint16_t seg[PF_PLAN_HEADS];
   PF_HD int of(int h) const { return per_head ? (int)seg[h] : uniform; }
 };
-PF_HD int pf_seg_begin(int n_kvt, int nseg, int s) { return (int)(((long long)s * n_kvt) / nseg); }
+PF_HD int pf_seg_begin(int n_kvt, int nseg, int s) {
+  if (s < (1 << 15) && n_kvt < (1 << 16)) return s * n_kvt / nseg;   // a 64-bit division is ten times as long on the device
+  return (int)(((long long)s * n_kvt) / nseg);
+}
 
 // One workgroup's job.  head_sel < 0 = nothing to do.
 struct __attribute__((aligned(32))) PfWorkItem {
