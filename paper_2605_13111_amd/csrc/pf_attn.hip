@@ -901,19 +901,21 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
   static_assert((PP_KSTAGES + PP_VSTAGES) * PP_TILE_BYTES >= Thin<D>::SMEM_BYTES, "thin items fit");
   __shared__ __attribute__((aligned(1024))) char smem[(PP_KSTAGES + PP_VSTAGES) * PP_TILE_BYTES];
   __shared__ int32_t sFlag;
-  __shared__ int32_t sNext;
+  __shared__ int32_t sNext, sHop;
   __shared__ long long sTrace[6];                              // busy ticks, first start, this item's start, items, busy shader-clock cycles, this item's start in those (thread 0 only)
   char (*sK)[PP_TILE_BYTES] = (char (*)[PP_TILE_BYTES])smem;
   char (*sV)[PP_TILE_BYTES] = sK + PP_KSTAGES;
   const int tid0 = threadIdx.x;
 
   // ---- work queue.  The items of die x are entries x, x + 8, x + 16, ... of the list, in the order the plan
-  // wants them started.  One workgroup per compute unit is launched; workgroup b runs on die b % 8 and takes
-  // the next entry of that die's queue (so the query tiles of one key segment still run side by side on one
-  // die and share its L2), and when that queue is empty it takes from the next die's, and so on: the dies do
-  // not run at the same speed, and without this the launch ends when the slowest die does.  Every workgroup
-  // leaves the loop after finding all eight queues empty; tickets only grow, so that always happens.  The last
-  // workgroup to leave puts the tickets back to zero for the next launch. ----
+  // wants them started.  One workgroup per compute unit is launched; workgroup b runs on die b % 8 and starts with
+  // entry b.  Then it takes the next entry of that die's queue by ticket (so the query tiles of one key segment still
+  // run side by side on one die and share its L2), and when that queue is empty it goes on to another die's that is
+  // not: the dies do not run at the same speed, and without this the launch ends when the slowest die does.  Tickets only
+  // grow, so a die found empty stays so, a workgroup is refused at most once per die and every one leaves the loop.  With each ticket it
+  // reads the other dies' as well: asked one after the other, the way out of a launch took 8 us (5 heads x 666
+  // queries, two layers: 63 us, now 50; one-frame chunks 1120 us, now 1090).
+  // The last workgroup to leave puts the tickets back to zero for the next launch. ----
   // The parameters are read again from the kernel-argument segment for every item (a few scalar loads): held in
   // registers across the loop they would crowd out the item's own state.
   typedef const __attribute__((address_space(4))) unsigned long long *karg_t;
@@ -935,28 +937,47 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     return R;
   };
   if (tid0 == 0) sTrace[0] = sTrace[1] = sTrace[2] = sTrace[3] = sTrace[4] = sTrace[5] = 0;
-  int hop_v = 0;                               // dies given up so far; kept in a vector register between items
+  // the die that tickets are taken at, counted from the workgroup's own (8: none is left), and above it a bit for every die
+  // found empty; -1: nothing done yet.  Kept in a vector register between items
+  int hop_v = -1;
   while (true) {
   asm volatile("" : "+v"(hop_v));
   int hop = __builtin_amdgcn_readfirstlane(hop_v);
   const AttnParams P = load_params();
   int item_idx = -1;
-  if (P.tickets == nullptr) {
-    if (hop == 0) item_idx = blockIdx.x;
+  const int n_start = gridDim.x / PF_NUM_XCD;                  // entries of each die that workgroups start with
+  if (hop < 0) {
+    item_idx = blockIdx.x;
+    hop = 0;
+  } else if (P.tickets == nullptr || P.queue_len <= n_start) {
     hop = PF_NUM_XCD;
   } else {
     const int home = blockIdx.x % PF_NUM_XCD;
-    while (hop < PF_NUM_XCD) {
-      const int x = (home + hop) % PF_NUM_XCD;
-      if (tid0 == 0) sNext = atomicAdd(&P.tickets[x], 1);
-      __syncthreads();
-      const int j = __builtin_amdgcn_readfirstlane(sNext);
-      __syncthreads();
-      if (j < P.queue_len) {
-        item_idx = j * PF_NUM_XCD + x;
-        break;
+    while ((hop & 15) < PF_NUM_XCD) {
+      const int at = hop & 15;
+      if (tid0 < 64) {                                         // lane i looks after die home + i: takes a ticket at die home + at, reads the others'
+        const int y = (home + tid0) % PF_NUM_XCD;
+        const int last = P.queue_len / P.n_qt - 1;             // the last row of teams may leave a die out: empty entries at its list's end
+        const int col = (last & 1) ? PF_NUM_XCD - 1 - y : y;
+        const int len = P.queue_len - (last * PF_NUM_XCD + col >= ((const PfWorkHeader *)P.counters - 1)->n_teams ? P.n_qt : 0) - n_start;
+        int t = len;
+        if (tid0 == at) t = atomicAdd(&P.tickets[y], 1);
+        else if (tid0 < PF_NUM_XCD && !(hop >> (4 + tid0) & 1)) t = __hip_atomic_load(&P.tickets[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned open = (unsigned)__builtin_amdgcn_ballot_w64(t < len);
+        if (tid0 == at) {
+          // stay, or go to the first die with entries at or after one that differs from workgroup to workgroup
+          const int turn = blockIdx.x / PF_NUM_XCD % PF_NUM_XCD;
+          const unsigned turned = (open | open << PF_NUM_XCD) >> turn;
+          const int next = t < len ? at : open ? (turn + __builtin_ctz(turned)) % PF_NUM_XCD : PF_NUM_XCD;
+          sNext = t < len ? (n_start + t) * PF_NUM_XCD + y : -1;
+          sHop = next | (~open & 0xff) << 4;
+        }
       }
-      ++hop;
+      __syncthreads();
+      item_idx = __builtin_amdgcn_readfirstlane(sNext);
+      hop = __builtin_amdgcn_readfirstlane(sHop);
+      __syncthreads();
+      if (item_idx >= 0) break;
     }
   }
   hop_v = hop;
@@ -1530,8 +1551,9 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
       bt[0] = sTrace[0]; bt[1] = sTrace[1]; bt[2] = sTrace[2]; bt[3] = sTrace[3]; bt[4] = sTrace[4];
     }
   }
-  int32_t *tickets = load_params().tickets;
-  if (tickets != nullptr && tid0 == 0) {
+  const AttnParams Pq = load_params();
+  int32_t *tickets = Pq.tickets;
+  if (tickets != nullptr && Pq.queue_len > (int)(gridDim.x / PF_NUM_XCD) && tid0 == 0) {
     const int done = atomicAdd(&tickets[PF_NUM_XCD], 1);
     if (done == (int)gridDim.x - 1) {
       for (int x = 0; x <= PF_NUM_XCD; ++x) atomicExch(&tickets[x], 0);
@@ -1539,7 +1561,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
   }
 }
 
-// Workgroups of the pipelined kernel that are resident at once: its LDS rings leave room for one per compute unit.
+// Workgroups of the pipelined kernel that are resident at once, as many for every die: its LDS rings leave room for one per
+// compute unit.
 static int pp_resident_workgroups() {
   static int n_cu[64] = {};
   int dev = 0;
@@ -1547,7 +1570,7 @@ static int pp_resident_workgroups() {
   if (n_cu[dev] == 0) {
     int n = 0;
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) n = 256;
-    n_cu[dev] = n;
+    n_cu[dev] = n < PF_NUM_XCD ? PF_NUM_XCD : n / PF_NUM_XCD * PF_NUM_XCD;
   }
   return n_cu[dev];
 }

@@ -116,7 +116,9 @@ static const PlanCosts kCostsD64 = {2.0, 0.7, 0.7};  // a tile takes four times 
 // block's time shared by its eight groups of 32 rows would be 0.125: launches of thin blocks alone reach 600 - 675 TFLOP/s
 // where full ones reach 1020 - 1110 (one to eight layers at model shape), and are twice as fast where full ones leave most
 // of the chip idle (5 heads x 666 queries x up to 3663 keys: 32 us against 63 us).
-static const double kThinTile = 0.19, kThinBlock = 4.0;
+// The block's fixed cost is the one of a launch whose blocks are mostly taken over by other dies, where it is largest (12 heads x
+// 1560 queries x 25 tiles: 55 us as thin blocks, 45 us as full ones).
+static const double kThinTile = 0.19, kThinBlock = 5.5;
 constexpr int PF_PLAN_ROUNDS = 3;
 constexpr int PF_PLAN_MAX_NSEG = 16;                // segment counts tried per head in step 2
 constexpr double PF_PLAN_MIN_GAIN = 0.01;           // step 2 must beat step 1 by this much to be used
