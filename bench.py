@@ -220,7 +220,8 @@ def main():
                      "traffic": traffic, "traffic_source": traffic_source,
                      "avg_launch_ms": round(attn_ms_avg, 4),
                      "flop_per_launch": flops_per_launch, "launches_timed": len(attn_ms)},
-        "pool_append": {"kernel": "pf_pool_append_kernel", "bound": "hbm",
+        "pool_append": {"kernel": "pf_pool_append_small_kernel" if max(int(p.slots) for L in layers for p in L[0].policies) <= 64 else "pf_pool_append_kernel",
+                        "bound": "hbm",
                         "what": "the append of %d frames that brings each layer's pool to %d frames "
                                 "(new frames + left-packed survivors, K and V, read + write), the layers' appends enqueued "
                                 "round-robin on %d streams as in a rollout, timed as one region" % (w.chunk_frames, T, APPEND_STREAMS),
