@@ -4,7 +4,7 @@
 // would use.  Two kernels share the steps:
 //   pf_classify_batch_kernel   sequences of 4 to CLS_BATCH_HIST frames (the paper analyses 69): the spectra of 16
 //                              sequences at a time as a matrix product on the fp64 matrix cores
-//   pf_classify_kernel         others: one workgroup per sequence, a direct DFT (their tables do not fit beside
+//   pf_classify_kernel         others, and launches of few long ones: one workgroup per sequence, a direct DFT (their tables do not fit beside
 //                              16 sequences in LDS)
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -145,6 +145,7 @@ __global__ __launch_bounds__(CLS_THREADS) void pf_classify_kernel(ClassifyParams
 // short chains at three waves per SIMD.  More, smaller workgroups (1024 of 32 rows: 79 us), larger ones of eight waves
 // (72 us) and fewer (512 of 64 rows: 62 us) lose more to half-full row groups and barriers than they hide.
 // ---------------------------------------------------------------------------------------------------
+constexpr int CLS_FEW_HIST = 80, CLS_FEW_SEQ = 768;   // longer sequences than this, but fewer: a workgroup each
 constexpr int CLS_BATCH_HIST = 256;     // longest sequence of the batched form (16 rows and the tables: 72 KB of LDS)
 constexpr int CLS_BATCH_MIN = 4;        // shortest sequence with a spectrum (three differences)
 constexpr int CLS_BATCH_LDS = 53 * 1024;  // three workgroups per compute unit where that leaves at least one round's rows
@@ -399,7 +400,10 @@ extern "C" int pf_classify_heads(const float *logits, int n_prompts, int n_heads
   P.n_hist = n_hist;
   P.alpha = alpha;
   P.beta = beta;
-  if (n_hist >= CLS_BATCH_MIN && n_hist <= CLS_BATCH_HIST) {
+  // Few long sequences finish earlier in a workgroup each: of 240 frames 48 take 13.8 us against 23.1 us in batches, 400 17.8 against
+  // 23.4 (1920 of 200 frames 56.6 against 21.5); of 100 frames 48 take 12.9 against 13.7, of 69 or fewer as long either way.
+  const bool few = n_hist > CLS_FEW_HIST && (long long)n_prompts * n_heads < CLS_FEW_SEQ;
+  if (n_hist >= CLS_BATCH_MIN && n_hist <= CLS_BATCH_HIST && !few) {
     // the longer the buffer, the fuller its groups of 16 rows; 48 rows for the paper's 69 frames
     ClassifyBatchParams B;
     B.c = P;
