@@ -113,12 +113,12 @@ static const PlanCosts kCostsDirect = {8.0, 2.0, 2.0};
 static const PlanCosts kCostsQueue = {4.0, 2.0, 3.0};
 static const PlanCosts kCostsD64 = {2.0, 0.7, 0.7};  // a tile takes four times as long where four workgroups share a compute unit
 // A thin block (32 query rows, pf_attn_thin.h): its share of a full block's time per key tile, and its fixed cost.  A full
-// block's time shared by its eight groups of 32 rows would be 0.125: launches of thin blocks alone reach 600 - 675 TFLOP/s
-// where full ones reach 1020 - 1110 (one to eight layers at model shape), and are twice as fast where full ones leave most
-// of the chip idle (5 heads x 666 queries x up to 3663 keys: 32 us against 63 us).
-// The block's fixed cost is the one of a launch whose blocks are mostly taken over by other dies, where it is largest (12 heads x
-// 1560 queries x 25 tiles: 55 us as thin blocks, 45 us as full ones).
-static const double kThinTile = 0.19, kThinBlock = 5.5;
+// block's time shared by its eight groups of 32 rows would be 0.125, but a thin block streams all its keys for 32 rows alone: where
+// many of them run at once that costs 0.30 (16 heads x 1038 queries x up to 503 tiles: 180 us as 1056 thin blocks, 124 us as
+// full ones; 5 heads x 1560 queries x up to 537 tiles 138 us against 108), and they pay where full blocks leave most of the chip
+// idle (5 heads x 666 queries x up to 58 tiles: 25 us against 57).  The fixed cost is the one of a launch whose blocks are mostly
+// taken over by other dies (12 heads x 1560 queries x 25 tiles: 55 us as thin blocks, 45 us as full ones).
+static const double kThinTile = 0.30, kThinBlock = 5.5;
 constexpr int PF_PLAN_ROUNDS = 3;
 constexpr int PF_PLAN_MAX_NSEG = 16;                // segment counts tried per head in step 2
 constexpr double PF_PLAN_MIN_GAIN = 0.01;           // step 2 must beat step 1 by this much to be used
@@ -345,14 +345,14 @@ int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
     if (fine.min_seg < S.min_seg && plan_segments(n_kvt, fine, uniform_only, &fp) < finish) *plan = fp;
   }
   // Small launches: with 32 query rows per block there are eight times the blocks, at ~1.5x the time per row; which side
-  // wins is left to the replay.  Looked at only where it could: its work spread evenly over the chip would finish earlier.
+  // wins is left to the replay, whose figures for thin blocks are good to about a tenth.  Looked at only where it could: its work spread evenly over the chip would finish earlier.
   if (may_thin) {
     const LaunchShape thin = launch_shape(PF_THIN_VARIANT, pool->head_dim, q_tokens, queue);
     const double even = thin.n_qt * (kThinTile * tiles + kThinBlock * H) / (PF_NUM_XCD * thin.slots_per_die);
     if (even < finish && total * thin.n_qt <= PF_THIN_MAX_BLOCKS) {
       PfSegPlan tp;
       memset(&tp, 0, sizeof(tp));
-      if (plan_segments(n_kvt, thin, true, &tp) < finish && (splits || !plan_splits(n_kvt, tp))) {
+      if (plan_segments(n_kvt, thin, true, &tp) < 0.9 * finish && (splits || !plan_splits(n_kvt, tp))) {
         *plan = tp;
         R.variant = PF_THIN_VARIANT;
       }
