@@ -51,6 +51,12 @@ constexpr float ATT_LAZY_LOG2 = 8.0f;
 // one-frame chunks 1141 -> 1123 us.  The second forming runs once at most, so odd scores (infinite, or so large that
 // scaling rounds past the bound) cannot hold a wave.
 constexpr float ATT_MAX_TILE_SUM = 256.0f;
+// Does any lane of the wave have too large a sum?  An unordered comparison: the start value -3e38 times a scale * log2(e) above
+// 1.134 is -infinity, against which a masked key's weight is NaN (-infinity + infinity) where an ordinary key's is infinite, and
+// where every lane holds a masked key no sum is an ordered one.  The maximum of the scores knows no NaN, so the weights formed again are finite.
+__device__ __forceinline__ bool tile_sum_too_large(float sum) {
+  return __builtin_amdgcn_fcmpf(sum, ATT_MAX_TILE_SUM, 10 /* ugt */) != 0;
+}
 
 struct TagT { static constexpr bool value = true; };
 struct TagF { static constexpr bool value = false; };
@@ -1295,7 +1301,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     weights();
 #pragma unroll
     for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(pf[i]));   // rounded here: sunk past the branch, all 32 weights would stay in registers
-    if (__builtin_expect(__builtin_amdgcn_fcmpf(ts[0] + ts[1], ATT_MAX_TILE_SUM, 2 /* ogt */) != 0, 0)) {
+    if (__builtin_expect(tile_sum_too_large(ts[0] + ts[1]), 0)) {
       float mx = s[0][0];
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(D64_WAVES * 64, 4) void pf_attn_d64_kernel(AttnPara
     weights();
 #pragma unroll
     for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(pf[i]));   // rounded here: sunk past the branch, all 32 weights would stay in registers
-    if (__builtin_expect(__builtin_amdgcn_fcmpf(ts[0] + ts[1], ATT_MAX_TILE_SUM, 2 /* ogt */) != 0, 0)) {
+    if (__builtin_expect(tile_sum_too_large(ts[0] + ts[1]), 0)) {
       float mx = s[0][0];
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)

@@ -203,7 +203,7 @@ __device__ __forceinline__ void thin_keys(const AttnParams &P, const PfWorkItem 
     };
     weights();
     asm volatile("" : "+v"(pf[0]), "+v"(pf[1]));                 // rounded here: sunk past the branch, all 16 weights would stay in registers
-    if (__builtin_expect(__builtin_amdgcn_fcmpf(ts[0] + ts[1], ATT_MAX_TILE_SUM, 2 /* ogt */) != 0, 0)) {
+    if (__builtin_expect(tile_sum_too_large(ts[0] + ts[1]), 0)) {
       float mx = s[0];
 #pragma unroll
       for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
