@@ -1678,7 +1678,6 @@ extern "C" int pf_ragged_attn_fwd(const pf_pool *pool, const pf_index *index, co
 // tight serving loops): the partial results of split heads go to a fixed array in the library's own device image.
 // Every GPU holds its own copy of the array at its own address, looked up once per device.
 // ---------------------------------------------------------------------------------------------------
-constexpr size_t PF_STATIC_SCRATCH_BYTES = 160ull << 20;
 static __device__ __align__(256) unsigned char scratch[PF_STATIC_SCRATCH_BYTES];
 
 static int static_scratch_ptr(void **out) {

@@ -289,11 +289,14 @@ double plan_segments(const std::vector<int> &n_kvt, const LaunchShape &S, bool u
   return cur_t;
 }
 
-bool plan_splits(const std::vector<int> &n_kvt, const PfSegPlan &plan) {
+// Partial results of a launch with n_qt query tiles per head.
+size_t plan_partials(const std::vector<int> &n_kvt, const PfSegPlan &plan, int n_qt) {
+  size_t n = 0;
   for (size_t h = 0; h < n_kvt.size(); ++h)
-    if (n_kvt[h] > plan.of((int)h)) return true;
-  return false;
+    if (n_kvt[h] > plan.of((int)h)) n += (size_t)pf_ceil_div(n_kvt[h], plan.of((int)h)) * n_qt;
+  return n;
 }
+bool plan_splits(const std::vector<int> &n_kvt, const PfSegPlan &plan) { return plan_partials(n_kvt, plan, 1) > 0; }
 }  // namespace
 
 int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
@@ -330,7 +333,24 @@ int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
   const double finish = plan_segments(n_kvt, S, uniform_only, plan);
   // A launch whose heads fit one segment each needs no workspace, and callers may rely on that: the forms below are not
   // allowed to bring partial results into it.
-  const bool splits = plan_splits(n_kvt, *plan);
+  bool splits = plan_splits(n_kvt, *plan);
+  if (splits && S.d64) {
+    // Callers may also rely on which launches do without scratch memory, or with the library's own array.  At head_dim 64 that is
+    // decided by a replay with the rates of two workgroups per compute unit: what it leaves whole stays whole, and what it fits into
+    // the array stays in it, although four workgroups per compute unit would often finish earlier in more, shorter segments
+    // (40 heads x 4680 queries x up to 1463 key tiles: 1480 blocks without partial results, or 16280 with 550 MB of them).
+    LaunchShape pair = S;
+    pair.slots_per_die = 64;
+    pair.d64 = false;
+    PfSegPlan base;
+    memset(&base, 0, sizeof(base));
+    plan_segments(n_kvt, pair, uniform_only, &base);
+    const size_t slot = pf_partial_bytes(pf_variant_bq(variant), pool->head_dim);
+    splits = plan_splits(n_kvt, base);
+    if (!splits || (plan_partials(n_kvt, base, S.n_qt) * slot <= PF_STATIC_SCRATCH_BYTES &&
+                    plan_partials(n_kvt, *plan, S.n_qt) * slot > PF_STATIC_SCRATCH_BYTES))
+      *plan = base;
+  }
   if (splits && S.d64) {
     LaunchShape fine = S;
     for (int seg : kShortSegs) {

@@ -162,6 +162,7 @@ static inline PfWorkLayout pf_work_layout(int n_heads, int n_qt, long long max_b
 
 // bytes of one partial-result slot: O [bq][D] fp32, then m [bq], l [bq]
 PF_HD size_t pf_partial_bytes(int bq, int head_dim) { return (size_t)bq * (head_dim + 2) * sizeof(float); }
+constexpr size_t PF_STATIC_SCRATCH_BYTES = 160ull << 20;   // the library's own array for them (pf_ragged_attn_fwd_static)
 
 // ---- host helpers ---------------------------------------------------------------------------
 int pf_validate_pool(const pf_pool *pool);                 // PF_OK or error

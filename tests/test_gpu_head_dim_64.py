@@ -66,3 +66,36 @@ def test_plans_stay_inside_their_workspace_and_unsplit_launches_stay_unsplit(hea
             short += min(seg) < 48
             assert min(seg) >= 48 or blocks <= 640 + 7 * -(-n * tpf // 128)
     assert unsplit > 10 and (head_dim == 128 or short > 10)
+
+
+@pytest.mark.parametrize("heads,policy,T,chunk,tpf,limit", [
+    (24, "veil", 6, 2, 700, 0), (64, "veil", 23, 3, 1560, 0), (40, "all", 57, 3, 1560, 0), (80, "all", 28, 1, 700, 0), (16, "veil", 124, 2, 1560, 0),
+    (64, "all", 235, 2, 700, 160 << 20), (64, "skewed", 39, 3, 1000, 160 << 20), (80, "skewed", 48, 2, 1560, 160 << 20),
+    (64, "wave", 85, 1, 1560, 160 << 20),
+])
+def test_launches_that_need_no_workspace_or_fit_the_library_array_keep_to_that(heads, policy, T, chunk, tpf, limit):
+    """Launches that can be made without a workspace, or through pf_ragged_attn_fwd_static (160 MiB), however much sooner more and
+    shorter segments would let them finish."""
+    n_all = {"veil": 0, "all": heads, "skewed": heads // 4 + 1, "wave": 0}[policy]
+    pols = [synth.anchor_all(T)] * n_all + [synth.wave(2, T) if policy == "wave" else synth.veil(1, 3)] * (heads - n_all)
+    c = _host_pool([p._replace(slots=max(1, B.slots_needed(p, T))) for p in pols], tpf, 64)
+    B.pf_set_tuning(attn_variant=-2, seg_tiles=0)
+    _, _, partials = B.pf_plan_segments(c, T, chunk * tpf)
+    assert partials * 128 * (64 + 2) * 4 <= limit
+
+
+@pytest.mark.gpu
+def test_a_whole_launch_runs_without_a_workspace():
+    import torch
+    H, T, tpf, Lq = 24, 4, 200, 2400                 # 19 query tiles; 3200 keys a head: 50 tiles, more than the shortest planned segment
+    pool = B.Pool([synth.anchor_all(T)] * H, tpf, 64)
+    B.pf_pool_reset(pool)
+    k, v = (synth.randn_bf16((H, T, tpf, 64), i, device="cuda:0") for i in (1, 2))
+    B.pf_cache_append(pool, k, v)
+    q, k_cur, v_cur = (synth.randn_bf16((H, Lq, 64), 3 + i, device="cuda:0") for i in range(3))
+    index = B.Index(pool, Lq)
+    B.pf_build_index(pool, index, Lq)
+    out = torch.full_like(q, float("nan"))
+    B.pf_ragged_attn_fwd(pool, index, q, k_cur, v_cur, out, None)
+    want = torch.nn.functional.scaled_dot_product_attention(*(t.float() for t in (q, torch.cat([k.flatten(1, 2), k_cur], 1), torch.cat([v.flatten(1, 2), v_cur], 1))))
+    assert (out.float() - want).abs().max() < 2e-2   # the oracle's bound
