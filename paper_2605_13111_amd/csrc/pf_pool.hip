@@ -278,9 +278,15 @@ __global__ __launch_bounds__(POOL_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 // than longer batches do: the 19 appends (and one index) that fill a layer with 57 frames take 454 us, in the general kernel
 // 528; batches of 8 470, two units per thread 488, non-temporal loads of the new frames faster there (457) but slower
 // where few frames move (292 against 285, 800 against 770).
+//
+// The arrivals bound it where frames are large: every workgroup adds one to its head's counter at the end, and here there are twice
+// as many of them.  Eight appends of one frame, 128 channels, general kernel / this one: 1560 tokens (98 blocks a head and tensor)
+// 1 head 45 / 43 us, 12 heads 78 / 59; 3120 tokens (195) 1 head 53 / 60, 4 heads 66 / 75, 12 heads 112 / 90 (three frames each 181 /
+// 164); 6240 tokens (390) 1 head 72 / 96, 12 heads 190 / 176 (three frames each 320 / 330); 40000 tokens, 1 head 273 / 485.
 // ---------------------------------------------------------------------------------------------------
 constexpr int POOL_SMALL_CAND = 64;
 constexpr int POOL_SMALL_BATCH = 4;
+constexpr int POOL_SMALL_BLOCKS = 128, POOL_SMALL_BLOCKS_MANY = 256, POOL_MANY_HEADS = 12;   // blocks a head and tensor at most, few and many heads
 __global__ __launch_bounds__(POOL_THREADS) void pf_pool_append_small_kernel(PoolAppendParams P) {
   const int h = blockIdx.y;
   const bool is_v = blockIdx.z != 0;
@@ -488,7 +494,8 @@ static int cache_append_impl(pf_pool *pool, const void *k_new, const void *v_new
   P.T = pool->T_host;
   P.n_new = n_new;
   P.frame_units = pool->tokens_per_frame * pool->head_dim / 8;   // bf16: 8 elements per 16 bytes
-  const bool small = most_cand <= POOL_SMALL_CAND && n_new <= POOL_PREFETCH;
+  const bool small = most_cand <= POOL_SMALL_CAND && n_new <= POOL_PREFETCH &&
+                     pf_ceil_div(P.frame_units, POOL_THREADS) <= (pool->n_heads < POOL_MANY_HEADS ? POOL_SMALL_BLOCKS : POOL_SMALL_BLOCKS_MANY);
   P.blocks_per_head = pf_ceil_div(P.frame_units, small ? POOL_THREADS : POOL_CHUNK_UNITS);
   P.row_shift = pool->head_dim == 128 ? 4 : 3;
   P.new_tok_units = layout ? layout->token_stride / 8 : (1 << P.row_shift);

@@ -53,3 +53,15 @@ def test_both_append_kernels_leave_the_same_pool():
     for a, b in ((few.frame_ids, more.frame_ids), (few.frame_score.view(torch.int32), more.frame_score.view(torch.int32)),
                  (few.k_pool.view(torch.int16), more.k_pool.view(torch.int16)), (few.v_pool.view(torch.int16), more.v_pool.view(torch.int16))):
         assert np.array_equal(a.cpu().numpy(), b[:n_common].cpu().numpy())
+
+
+@pytest.mark.parametrize("H,tpf", [(3, 2048), (3, 2049), (12, 4096), (12, 4097)])     # the last frame size of the small kernel, and one token more
+def test_append_on_either_side_of_the_largest_frames(H, tpf):
+    pols = [[synth.anchor_topk(2, 3), synth.wave(3, 8, cap=1, sink=1, recent=2), synth.veil(1, 2)][h % 3] for h in range(H)]
+    pool_o, pool_g = PoolOracle(pols, tpf, 128), B.Pool(pols, tpf, 128, device=DEV)
+    B.pf_pool_reset(pool_g)
+    for i, n in enumerate([2, 1, 2]):
+        k, v, sc = _new(H, n, tpf, 128, 500 + i)
+        pool_o.append(synth.bits(k), synth.bits(v), sc.numpy())
+        B.pf_cache_append(pool_g, k.to(DEV), v.to(DEV), sc.to(DEV))
+        G.check_pool(pool_g, pool_o)
