@@ -43,13 +43,21 @@ def _host_pool(pols, tpf, head_dim):
     return c
 
 
+def _rows_of(rows, seg, tiles, blocks, q_tokens):
+    """Query rows per block of a plan: a multiple of eight (head, segment) teams times the query tiles.  A chunk that one block of
+    either size covers does not tell them apart; then the larger."""
+    teams = sum(-(-t // s) for t, s in zip(tiles, seg))
+    return max(r for r in rows if -(-teams // 8) * 8 * -(-q_tokens // r) == blocks)
+
+
 @pytest.mark.parametrize("head_dim,rows", [(64, (128,)), (128, (32, 256))])
 def test_plans_stay_inside_their_workspace_and_unsplit_launches_stay_unsplit(head_dim, rows):
-    """Over random pools: a plan's partial results fit pf_attn_workspace_bytes (in the smallest of the kernels' slot sizes at
-    least), and a launch whose heads are at most 48 key tiles long, which one segment covers, needs no workspace at all."""
+    """Over random pools: a plan's partial results fit pf_attn_workspace_bytes, and a launch whose heads are at most 48 key tiles
+    long, which one segment covers, needs no workspace at all."""
     rng = random.Random(5)
     B.pf_set_tuning(attn_variant=-2, seg_tiles=0)
     unsplit = short = 0
+    planned = set()
     for _ in range(150):
         T, H, n = rng.randint(0, 40), rng.randint(1, 24), rng.randint(1, 3)
         tpf = rng.choice([1, 16, 77, 200, 333, 700, 1560])
@@ -57,15 +65,17 @@ def test_plans_stay_inside_their_workspace_and_unsplit_launches_stay_unsplit(hea
         c = _host_pool(pols, tpf, head_dim)
         seg, blocks, partials = B.pf_plan_segments(c, T, n * tpf)
         ws = int(B.lib().pf_attn_workspace_bytes(ctypes.byref(c), n * tpf))
-        assert partials * min(rows) * (head_dim + 2) * 4 <= ws
         tiles = [-(-(B.pf_selected_count(p, T) + n) * tpf // 64) for p in pols]
+        per_block = _rows_of(rows, seg, tiles, blocks, n * tpf)
+        planned.add(per_block)
+        assert partials * per_block * (head_dim + 2) * 4 <= ws
         if max(tiles) <= 48:
             unsplit += 1
             assert partials == 0
         if head_dim == 64:
             short += min(seg) < 48
             assert min(seg) >= 48 or blocks <= 640 + 7 * -(-n * tpf // 128)
-    assert unsplit > 10 and (head_dim == 128 or short > 10)
+    assert unsplit > 10 and (head_dim == 128 or short > 10) and planned == set(rows)
 
 
 @pytest.mark.parametrize("heads,policy,T,chunk,tpf,limit", [
