@@ -52,10 +52,11 @@ def compare_attention(out_g, want, rows=None, label=""):
 
 
 def run_case(pols, tpf, D, chunks, Lq, seed, with_scores=True, q_gain=1.0, seg_tiles=0, rows=None,
-             check_every_append=True, scale=0.0, device="cuda:0", label="case", layout="packed"):
+             check_every_append=True, scale=0.0, device="cuda:0", label="case", layout="packed", variant=None):
     """Full path on both sides.  Returns (worst max-abs, worst relative L2) of the attention output.
     layout="model": the GPU side holds the new frames and the chunk tensors as [tokens][heads][D] and goes
-    through the strided entry points (same values, so the oracle side does not change)."""
+    through the strided entry points (same values, so the oracle side does not change).
+    variant: the kernel variant that the index has to be planned for."""
     model = layout == "model"
 
     def as_model(t):              # [H, ..., D] on the CPU -> heads-first view of a [tokens][H][D] device tensor
@@ -84,6 +85,7 @@ def run_case(pols, tpf, D, chunks, Lq, seed, with_scores=True, q_gain=1.0, seg_t
         check_pool(pool_g, pool_o)
     index = B.Index(pool_g, Lq, seg_tiles=seg_tiles)
     B.pf_build_index(pool_g, index, Lq)
+    assert variant is None or index.c.variant == variant, "%s: planned for kernel variant %d" % (label, index.c.variant)
     sel_count, sel_frames = check_index(index, pool_o)
     q = synth.randn_bf16((H, Lq, D), seed * 1000 + 900) * q_gain
     k_cur = synth.randn_bf16((H, Lq, D), seed * 1000 + 901)

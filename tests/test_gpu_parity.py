@@ -12,14 +12,14 @@ import gpu_common as G
 
 pytestmark = pytest.mark.gpu
 
-DEFAULT_VARIANT = 1
+OWN_CHOICE = -2                                  # the library picks the kernel per launch: what a user gets
 
 
-@pytest.fixture(params=[0, 1, 2], ids=["w4x32", "pp8x32", "w4x64"])
+@pytest.fixture(params=[OWN_CHOICE, 0, 1, 2], ids=["own-choice", "w4x32", "pp8x32", "w4x64"])
 def variant(request):
     B.pf_set_tuning(attn_variant=request.param)
     yield request.param
-    B.pf_set_tuning(attn_variant=DEFAULT_VARIANT)
+    B.pf_set_tuning(attn_variant=OWN_CHOICE)
 
 
 def test_c1_tiny_full(variant):

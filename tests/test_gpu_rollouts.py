@@ -108,4 +108,4 @@ def test_c3_step_layers_with_the_64_row_kernel():
             _rollout(pols, w.tokens_per_frame, w.head_dim, 3, T // 3 + 1, 800 + layer, {T}, {T}, 16,
                      "c3_step layer %d, 64-row kernel" % layer, append_last=False)
     finally:
-        B.pf_set_tuning(attn_variant=1)
+        B.pf_set_tuning(attn_variant=-2)

@@ -15,6 +15,12 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 pytestmark = pytest.mark.skipif(not os.path.exists(B.LIB_PATH), reason="libpf.so not built")
 
 
+@pytest.fixture(autouse=True)
+def default_tuning():
+    yield
+    B.pf_set_tuning(attn_variant=-2, attn_queue=1, seg_tiles=0, plan_uniform=0)
+
+
 def test_library_exports_every_declared_symbol():
     header = open(os.path.join(ROOT, "include", "pf.h")).read()
     declared = set(re.findall(r"\b(pf_[a-z_]+)\s*\(", header))
@@ -209,7 +215,6 @@ def test_launch_plan_stays_inside_the_advertised_buffers():
                 assert 64 + 4 * (len(pols) * n_qt + 16) + 16 * len(pols) + 32 * n_blocks <= work_bytes
                 if env.get("plan_uniform"):
                     assert len(set(seg)) == 1
-    B.pf_set_tuning(attn_variant=1, attn_queue=1, seg_tiles=0, plan_uniform=0)
 
 
 def test_tuning_switches_validate_and_apply():
@@ -223,14 +228,15 @@ def test_tuning_switches_validate_and_apply():
     assert min(seg) >= 48
 
 
-def test_planning_a_streaming_rollout_is_cheap_once_seen():
+@pytest.mark.parametrize("variant", [-2, 1])             # the library's own choice of kernel, and the one kernel
+def test_planning_a_streaming_rollout_is_cheap_once_seen(variant):
     """The one-frame-chunk rollout asks for 30 layers x 40 history lengths = 1200 different launch plans.  The
     library remembers all of them: a second rollout pays a table lookup per call (budget: 50 us mean, measured
     ~3 us), and a first-time plan stays in the low milliseconds."""
     import time
     w = synth.WORKLOADS["c5_stream"]
     pools = [_fake_pool(synth.policies("c5_stream", layer=l), tpf=w.tokens_per_frame, D=w.head_dim) for l in range(w.n_layers)]
-    B.pf_set_tuning(attn_variant=1, attn_queue=1, seg_tiles=0, plan_uniform=0)
+    B.pf_set_tuning(attn_variant=variant, attn_queue=1, seg_tiles=0, plan_uniform=0)
 
     def rollout():
         plans, worst = [], 0.0
@@ -264,7 +270,6 @@ def test_tuning_accepts_every_kernel_variant():
     for v in (0, 1, 2):
         assert B.lib().pf_set_tuning(v, -1, -1, -1) == B.PF_OK
     assert B.lib().pf_set_tuning(3, -1, -1, -1) == B.PF_ERR_INVALID_ARG
-    B.pf_set_tuning(attn_variant=1)
 
 
 def test_build_refuses_a_listing_where_the_compiler_uses_the_hidden_registers():

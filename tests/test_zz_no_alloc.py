@@ -53,3 +53,10 @@ def test_static_scratch_entry_point_matches_the_workspace_entry_point():
     pols = [synth.anchor_all(30), synth.anchor_topk(5, 5), synth.wave(2, 30), synth.veil(1, 3)]
     a2, r2 = _case(pols, 48, 128, [3] * 10, 200, seed=82, seg_tiles=16, rows_n=None)
     print("static scratch: max-abs %.2e / %.2e, relative L2 %.2e / %.2e" % (a, a2, r, r2))
+
+
+def test_static_scratch_with_thin_items():
+    """A small launch that the library cuts into 32-row items, its heads split."""
+    pols = [synth.anchor_all(9), synth.anchor_topk(5, 5), synth.wave(3, 9), synth.veil(1, 3)]
+    a, r = _case(pols, 333, 128, [3] * 3, 666, seed=83, seg_tiles=0, rows_n=None)
+    print("static scratch, thin items: max-abs %.2e, relative L2 %.2e" % (a, r))
