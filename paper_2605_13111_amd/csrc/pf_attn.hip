@@ -10,15 +10,17 @@
 //   pf_attn_kernel     BQ = 128, 4 waves x 32 query rows, two workgroups per CU, tiles staged through
 //                      registers into padded LDS rows; head_dim 128, by request only
 //   pf_attn_pp_kernel  BQ = 256, 8 waves x 32 query rows in two groups that alternate between a matrix phase
-//                      and a vector phase, tiles copied global -> LDS directly; head_dim 128 (the default there)
+//                      and a vector phase, tiles copied global -> LDS directly; head_dim 128 (the default there).  Also
+//                      BQ = 32 for small launches, the keys split over the eight waves (pf_attn_thin.h), and BQ = 256
+//                      as 4 waves x 64 rows, by request only
 //
 // Per tile, on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulate):
 //   S^T = K . Q^T     A operand = K rows from LDS, B operand = Q^T held in registers
 //   O^T += V^T . P^T  A operand = V^T via the LDS transpose read, B operand = P^T straight from the
 //                     S^T accumulators (the key permutation of the accumulator layout is applied to
 //                     the V rows instead, since a sum over keys has no order)
-// so every lane owns ONE query column: the running maximum and sum of the online softmax live in
-// one register each and need a single exchange with lane^32 per tile.
+// so every lane owns ONE query column: the reference maximum and sum of the online softmax live in
+// one register each; lane^32 is asked for its maximum only where the reference moves, and for its sum at the end.
 #include <stddef.h>
 #include <stdlib.h>
 #include "pf_internal.h"
@@ -43,7 +45,7 @@ constexpr int ATT_WAVES = 4;
 // Exponent headroom (log2 units) a score may have over the reference maximum before the accumulators
 // must be rescaled: weights stay below 2^8 (fp32 and bf16 share the 8-bit exponent, so both hold such
 // weights without loss of relative precision).
-constexpr float ATT_LAZY_LOG2 = 8.0f;
+constexpr float ATT_LAZY_LOG2 = 8.0f;            // pf_attn_kernel and the 64-row form
 // The same bound seen from a lane's sum of one tile's weights (no weight exceeds their sum), which the row sum needs anyway:
 // a wave forms its weights against the reference it has and looks for the tile's maximum only when a sum is too large, to move
 // the reference and form them again.  Without the maximum of every tile in front of them the weights take 17 instructions
@@ -109,23 +111,13 @@ __device__ __forceinline__ float partner_sum(float x) {
 }
 
 // Partial results cross workgroups that may run on different dies, each with its own L2.  They are written
-// and read with device-scope (relaxed atomic) accesses, which go through to the memory side that all dies
-// share; no L2 write-back fence is needed, only the wait for the stores' completion before the arrival
-// counter is bumped.  Building with -DPF_STRICT_FENCES=1 adds the release fence the memory model asks for in
-// front of every arrival (here and in the pool append): the known-correct form, measured against this one.
-__device__ __forceinline__ void st_dev2(float *p, float a, float b) {
-  const unsigned long long v = (unsigned long long)__float_as_uint(a) | ((unsigned long long)__float_as_uint(b) << 32);
-  __hip_atomic_store((unsigned long long *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float2 ld_dev2(const float *p) {
-  const unsigned long long v = __hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
-}
+// with device-scope stores, which go through to the memory side that all dies share; no L2 write-back fence is
+// needed, only the wait for the stores' completion before the arrival counter is bumped (the merging workgroup
+// drops what its own caches hold before it reads).  Building with -DPF_STRICT_FENCES=1 adds the release fence the
+// memory model asks for in front of every arrival (here and in the pool append): the known-correct form, measured
+// against this one.
 __device__ __forceinline__ void st_dev1(float *p, float a) {
   __hip_atomic_store(p, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float ld_dev1(const float *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -397,7 +389,7 @@ __device__ __forceinline__ void classic_loop(const HeadKV &H, int kt0, int kt1, 
 // ---------------------------------------------------------------------------------------------------
 constexpr int attn_stage_floats(int bq, int d) { return bq * (d + 4) + 2 * bq; }
 
-// 16-byte device-scope store: written through to the memory all dies share (see st_dev2).
+// 16-byte device-scope store: written through to the memory all dies share (see st_dev1).
 __device__ __forceinline__ void st_dev4(float *p, f32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
 }
@@ -664,7 +656,6 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void pf_attn_kernel(AttnParams P) {
 //   V tile   chunk c of row r sits at position c ^ ((r & 3) << 2)  (a transpose read takes 64 bytes from each
 //                                                                   of 4 rows per 32 lanes: 4 x 64 B = all banks once)
 // ---------------------------------------------------------------------------------------------------
-constexpr int PP_WAVES = 8;
 constexpr int PP_KSTAGES = 4;                                   // K of tile u is read in phase M(u)
 constexpr int PP_VSTAGES = 5;                                   // V of tile u is read one phase later, in M(u+1)
 constexpr int PP_TILE_BYTES = PF_BK * 128 * 2;                  // one tensor's tile, head_dim 128, unpadded
@@ -1228,7 +1219,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     }
   };
 
-  float mc = m_run[0] * c;                         // reference maximum * scale; odd scores' row sum
+  float mc = m_run[0] * c;                         // reference maximum * scale
   // weights of two scores (key block kb, registers i and i+1): scale, exp2, add to the tile's sums (even scores into ts[0],
   // odd ones into ts[1]; plain fp32 adds: a dot-product instruction goes through the matrix pipe and queues there behind
   // the other group's MFMAs, measured ~54 cycles each next to a saturated MFMA stream, against 4 alone), round to bf16

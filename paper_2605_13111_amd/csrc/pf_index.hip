@@ -13,7 +13,7 @@ struct IndexParams {
   const float *frame_score;
   int32_t *sel_count, *sel_frames, *sel_slots, *cu_seqlens;
   PfWorkHeader *header;
-  int32_t *counters, *scratch;
+  int32_t *counters;
   PfWorkItem *items;
   long long total_slots;
   int n_heads, T, tpf, max_sel, q_tokens, n_qt, bq, variant;
@@ -281,7 +281,6 @@ extern "C" int pf_build_index(const pf_pool *pool, pf_index *index, int q_tokens
   P.cu_seqlens = index->cu_seqlens;
   P.header = (PfWorkHeader *)w;
   P.counters = (int32_t *)(w + L.counters_off);
-  P.scratch = (int32_t *)(w + L.scratch_off);
   P.items = (PfWorkItem *)(w + L.items_off);
   P.total_slots = pool->total_slots;
   P.n_heads = pool->n_heads;

@@ -22,8 +22,10 @@ constexpr int PF_THIN_VARIANT = 3;      // chosen by the planner only: every wor
 constexpr int PF_THIN_MAX_BLOCKS = 4096;   // ... of launches with at most this many of them
 constexpr int PF_NUM_KERNELS = 4;
 
-// query rows per workgroup of kernel variant v: 0 = 4 waves x 32 rows, 1 = 8 waves x 32 rows, 2 = 4 waves x 64 rows
+// query rows per workgroup of kernel variant v: 0 = 4 waves x 32 rows, 1 = 8 waves x 32 rows, 2 = 4 waves x 64 rows,
+// PF_THIN_VARIANT = 32 rows, all waves
 PF_HD int pf_variant_bq(int variant) { return variant == PF_THIN_VARIANT ? 32 : variant == 0 ? 128 : 256; }
+
 PF_HD int pf_ceil_div(int a, int b) { return (a + b - 1) / b; }
 PF_HD int pf_min(int a, int b) { return a < b ? a : b; }
 PF_HD int pf_max(int a, int b) { return a > b ? a : b; }
@@ -144,18 +146,17 @@ struct __attribute__((aligned(64))) PfWorkHeader {
   int32_t pad[8];
 };
 
-// Layout of pf_index.work: header | counters[n_heads*n_qt + PF_QUEUE_INTS] | head scratch[4*n_heads] | items[n_blocks]
+// Layout of pf_index.work: header | counters[n_heads*n_qt + PF_QUEUE_INTS] | items[n_blocks]
 // (the last PF_QUEUE_INTS counters are the attention kernel's work-queue tickets)
 constexpr int PF_QUEUE_INTS = 16;
 struct PfWorkLayout {
-  size_t counters_off, scratch_off, items_off, total;
+  size_t counters_off, items_off, total;
 };
 static inline size_t pf_align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 static inline PfWorkLayout pf_work_layout(int n_heads, int n_qt, long long max_blocks) {
   PfWorkLayout L;
   L.counters_off = sizeof(PfWorkHeader);
-  L.scratch_off = pf_align_up(L.counters_off + sizeof(int32_t) * ((size_t)n_heads * n_qt + PF_QUEUE_INTS), 64);
-  L.items_off = pf_align_up(L.scratch_off + sizeof(int32_t) * 4 * (size_t)n_heads, 64);
+  L.items_off = pf_align_up(L.counters_off + sizeof(int32_t) * ((size_t)n_heads * n_qt + PF_QUEUE_INTS), 64);
   L.total = L.items_off + sizeof(PfWorkItem) * (size_t)max_blocks;
   return L;
 }
