@@ -112,13 +112,19 @@ struct PlanCosts {
 static const PlanCosts kCostsDirect = {8.0, 2.0, 2.0};
 static const PlanCosts kCostsQueue = {4.0, 2.0, 3.0};
 static const PlanCosts kCostsD64 = {2.0, 0.7, 0.7};  // a tile takes four times as long where four workgroups share a compute unit
-// A thin block (32 query rows, pf_attn_thin.h): its share of a full block's time per key tile, and its fixed cost.  A full
-// block's time shared by its eight groups of 32 rows would be 0.125, but a thin block streams all its keys for 32 rows alone: where
-// many of them run at once that costs 0.30 (16 heads x 1038 queries x up to 503 tiles: 180 us as 1056 thin blocks, 124 us as
-// full ones; 5 heads x 1560 queries x up to 537 tiles 138 us against 108), and they pay where full blocks leave most of the chip
-// idle (5 heads x 666 queries x up to 58 tiles: 25 us against 57).  The fixed cost is the one of a launch whose blocks are mostly
-// taken over by other dies (12 heads x 1560 queries x 25 tiles: 55 us as thin blocks, 45 us as full ones).
-static const double kThinTile = 0.30, kThinBlock = 5.5;
+// A thin block (32 query rows, pf_attn_thin.h): its share of a full block's time per key tile, its fixed cost, and what parking a
+// partial result adds to it.  A full block's time shared by its eight groups of 32 rows would be 0.125, but a thin block streams all
+// its keys for 32 rows alone: where many of them run at once that costs 0.30 (16 heads x 1038 queries x up to 503 tiles: 180 us as
+// 1056 thin blocks, 124 us as full ones; 5 heads x 1560 queries x up to 537 tiles 138 us against 108), and they pay where full
+// blocks leave most of the chip idle (5 heads x 666 queries x up to 58 tiles: 25 us against 57).  The fixed cost is the one of a
+// launch whose blocks are mostly taken over by other dies (12 heads x 1560 queries x 25 tiles: 55 us as thin blocks, 45 us as full
+// ones).  Parking was charged 0.25 to 1 at first: launches of split thin blocks took 5 to 20 tiles longer than replayed, 4 per
+// block (7 heads x 1380 queries x up to 54 tiles: 65 us as 704 thin blocks in halves, 55 us as full ones).
+static const double kThinTile = 0.30, kThinBlock = 5.5, kThinPark = 4.0;
+// ... must finish this much earlier than full ones by the replay, which is good to about a tenth; and what kCostsQueue.merge, fitted to
+// launches of two to four segments a head, charges too much for one with many: 20 segments are replayed at 122 tiles and take 86
+// (2 heads x 1192 queries x 1118 tiles), 10 at 81 and take 61, 5 at 66 and take 61.
+static const double kThinGain = 0.9, kMergeOver = 2.0;
 constexpr int PF_PLAN_ROUNDS = 3;
 constexpr int PF_PLAN_MAX_NSEG = 16;                // segment counts tried per head in step 2
 constexpr double PF_PLAN_MIN_GAIN = 0.01;           // step 2 must beat step 1 by this much to be used
@@ -165,7 +171,7 @@ static double model_finish(const std::vector<int> &n_kvt, const std::vector<int>
       const int tiles = pf_seg_begin(nk, nseg, sgi + 1) - pf_seg_begin(nk, nseg, sgi);
       // the merge falls to whichever segment arrives last; the replay charges it to the last one launched
       const double park = (nseg > 1 ? C.split : 0.0) + (nseg > 1 && sgi == nseg - 1 ? C.merge * nseg : 0.0);
-      teams[xcd].push_back(S.thin ? kThinTile * tiles + kThinBlock + park / 8 : tiles + C.block + park);
+      teams[xcd].push_back(S.thin ? kThinTile * tiles + kThinBlock + (nseg > 1 ? kThinPark : 0.0) : tiles + C.block + park);
     }
   }
   double finish = 0.0;
@@ -364,15 +370,18 @@ int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
     memset(&fp, 0, sizeof(fp));
     if (fine.min_seg < S.min_seg && plan_segments(n_kvt, fine, uniform_only, &fp) < finish) *plan = fp;
   }
-  // Small launches: with 32 query rows per block there are eight times the blocks, at ~1.5x the time per row; which side
-  // wins is left to the replay, whose figures for thin blocks are good to about a tenth.  Looked at only where it could: its work spread evenly over the chip would finish earlier.
+  // Small launches: with 32 query rows per block there are eight times the blocks, at 2.4 times the time per row; which side wins is
+  // left to the replay.  Looked at only where it could: its work spread evenly over the chip would finish earlier.
   if (may_thin) {
+    int most = 1;
+    for (int h = 0; h < H; ++h) most = pf_max(most, pf_ceil_div(n_kvt[h], plan->of(h)));
+    const double full = finish - (most > 1 ? kMergeOver * most : 0.0);
     const LaunchShape thin = launch_shape(PF_THIN_VARIANT, pool->head_dim, q_tokens, queue);
     const double even = thin.n_qt * (kThinTile * tiles + kThinBlock * H) / (PF_NUM_XCD * thin.slots_per_die);
-    if (even < finish && total * thin.n_qt <= PF_THIN_MAX_BLOCKS) {
+    if (even < full && total * thin.n_qt <= PF_THIN_MAX_BLOCKS) {
       PfSegPlan tp;
       memset(&tp, 0, sizeof(tp));
-      if (plan_segments(n_kvt, thin, true, &tp) < 0.9 * finish && (splits || !plan_splits(n_kvt, tp))) {
+      if (plan_segments(n_kvt, thin, true, &tp) < kThinGain * full && (splits || !plan_splits(n_kvt, tp))) {
         *plan = tp;
         R.variant = PF_THIN_VARIANT;
       }

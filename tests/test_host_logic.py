@@ -266,6 +266,28 @@ def test_launch_plan_rejects_bad_arguments():
     assert lib.pf_plan_segments(ctypes.byref(pool), 3, 4680, None, None, None) == B.PF_OK
 
 
+@pytest.mark.parametrize("heads,policy,T,n,tpf,rows", [
+    # us as 32-row / 256-row work items
+    (5, "all", 3, 1, 666, 32),                   # 21 / 65
+    (8, "all", 10, 2, 300, 32),                  # 28 / 60
+    (20, "veil", 8, 1, 400, 32),                 # 40 / 54
+    (20, "veil", 8, 1, 800, 256),                # 68 / 63
+    (2, "all", 20, 1, 1560, 256),                # 105 / 92: heads cut into 11 segments
+    (2, "all", 50, 1, 1096, 256),                # 128 / 107
+    (5, "all", 38, 3, 348, 256),                 # 98 / 90
+    (5, "all", 20, 1, 1560, 256),                # 217 / 158
+    (8, "all", 40, 1, 540, 256),                 # 118 / 91
+    (12, "veil", 0, 1, 1560, 256),               # 54 / 42
+])
+def test_small_launches_are_planned_for_the_kernel_that_measured_faster(heads, policy, T, n, tpf, rows):
+    from test_gpu_head_dim_64 import _host_pool, _rows_of
+    pol = synth.anchor_all(max(T, 1)) if policy == "all" else synth.veil(1, 3)
+    pol = pol._replace(slots=max(1, B.slots_needed(pol, max(T, 1))))
+    B.pf_set_tuning(attn_variant=-2, attn_queue=1, seg_tiles=0, plan_uniform=0)
+    seg, blocks, _ = B.pf_plan_segments(_host_pool([pol] * heads, tpf, 128), T, n * tpf)
+    assert _rows_of((32, 256), seg, [_tiles(pol, T, tpf, n * tpf)] * heads, blocks, n * tpf) == rows
+
+
 def test_tuning_accepts_every_kernel_variant():
     for v in (0, 1, 2):
         assert B.lib().pf_set_tuning(v, -1, -1, -1) == B.PF_OK
