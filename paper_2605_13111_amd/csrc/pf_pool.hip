@@ -274,10 +274,10 @@ __global__ __launch_bounds__(POOL_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 // ballots and lane reads, without LDS, barriers or a move list, and the copy loop's slots are scalars (one scalar base per frame,
 // the thread's offset stays).  The order of the moves is the general kernel's.
 // Bound: HBM, behind a plan that all workgroups make at the same time before the first survivor can travel.  One 16-byte unit
-// per thread and frame and batches of four frames keep a wave at 42 registers, eight waves per SIMD, which hide more of that
-// than longer batches do: the 19 appends (and one index) that fill a layer with 57 frames take 454 us, in the general kernel
-// 528; batches of 8 470, two units per thread 488, non-temporal loads of the new frames faster there (457) but slower
-// where few frames move (292 against 285, 800 against 770).
+// per thread and frame and batches of four frames keep a wave at 46 registers, eight waves per SIMD, which hide more of that
+// than longer batches do: the 19 appends (and one index) that fill a layer with 57 frames take 448 us, with the general kernel
+// 535; in a run where this form took 457, batches of 8 took 470, two units per thread 488, and non-temporal loads of the new
+// frames, faster there, were slower where few frames move (292 against 285, 800 against 770).
 //
 // The arrivals bound it where frames are large: every workgroup adds one to its head's counter at the end, and here there are twice
 // as many of them.  Eight appends of one frame, 128 channels, general kernel / this one: 1560 tokens (98 blocks a head and tensor)
