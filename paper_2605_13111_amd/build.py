@@ -49,6 +49,17 @@ def check_hidden_registers(listing):
     return highest
 
 
+def check_scalar_operands(listing):
+    """A buffer copy whose descriptor or scalar offset the compiler holds in vector registers becomes a loop over the
+    lanes' values.  Every such operand of the attention kernels is the same in all lanes, so a loop is time lost, and one
+    that reloads spilled descriptor words inside (seen where two copies under complementary masks had been merged into
+    one with a selected descriptor) reads its second turn's base from the wrong registers.  Raises if the listing has one."""
+    lines = [ln.split(";")[0].strip() for ln in listing.split("\n")]
+    for a, b in zip(lines, lines[1:]):
+        if a.startswith("buffer_load") and b.startswith("s_xor_b64 exec, exec"):
+            raise RuntimeError("a buffer copy loops over its lanes' operands: " + a)
+
+
 def build(verbose=False, extra=()):
     """extra: more hipcc flags; PF_HIPCC_FLAGS in the environment adds to them (e.g. -DPF_STRICT_FENCES=1: release
     fences in front of the cross-workgroup arrival counters, the form the memory model asks for)."""
@@ -77,6 +88,7 @@ def build(verbose=False, extra=()):
     if failed or lst.returncode != 0:
         raise RuntimeError("hipcc failed")
     highest = check_hidden_registers(listing)
+    check_scalar_operands(listing)
     if verbose:
         print("64-row attention kernel: highest accumulation register used by the compiler: a%d" % highest, flush=True)
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)

@@ -195,45 +195,6 @@ __device__ __forceinline__ void attn_store_rows(const u32x4 (&reg)[NP], __bf16 *
   for (int p = 0; p < NP; ++p) *(u32x4 *)(&dst[(lrow + p * RPP) * STRIDE + lchunk * 8]) = reg[p];
 }
 
-// Where a tile's rows come from, for the direct global -> LDS copies of the two-group kernel.
-struct TileSrc {
-  bool simple;            // tile inside one frame (or the chunk) and not ragged: base + row * stride
-  bool strided;           // simple chunk tile whose rows are cur_stride elements apart instead of D
-  bool split;             // whole tile made of two dense runs: rows below n1 end one frame, the others start the next
-                          // frame (or the packed chunk); never together with simple
-  const __bf16 *kb, *vb;  // first row of the tile (simple case); of the first run (split case)
-  const __bf16 *kb2, *vb2; // split case: where row 0 of the tile WOULD sit if the second run began there (second run's
-                          // first row minus n1 rows), so that both runs are addressed by the row number in the tile
-  int n1;                 // split case: rows of the first run, 1 .. 63
-  int kt;
-};
-__device__ __forceinline__ TileSrc tile_src(int kt, TilePos pos, const HeadKV &H, int D) {
-  TileSrc t;
-  const int last = H.lkv - 1 - kt * PF_BK;
-  const bool in_hist = pos.j < H.n_sel;
-  t.simple = last >= PF_BK - 1 && (!in_hist || pos.r + PF_BK <= H.tpf);
-  t.strided = !in_hist && H.cur_stride != D;
-  t.kt = kt;
-  // a whole history tile that crosses exactly one border: frames of at least a tile, and the next run (a frame, or the
-  // chunk with rows D apart) holds the rest of the tile
-  t.n1 = H.tpf - pos.r;
-  t.split = !t.simple && in_hist && last >= PF_BK - 1 && H.tpf >= PF_BK && t.n1 > 0 && t.n1 < PF_BK &&
-            (pos.j + 1 < H.n_sel || H.cur_stride == D);
-  size_t e = 0;
-  if (t.simple) e = in_hist ? ((size_t)H.slots[pos.j] * H.tpf + pos.r) * D : (size_t)pos.r * H.cur_stride;
-  if (t.split) e = ((size_t)H.slots[pos.j] * H.tpf + pos.r) * D;
-  t.kb = (in_hist ? H.k_pool : H.k_cur) + e;
-  t.vb = (in_hist ? H.v_pool : H.v_cur) + e;
-  t.kb2 = t.kb;
-  t.vb2 = t.vb;
-  if (t.split) {
-    const bool next_hist = pos.j + 1 < H.n_sel;
-    const long long e2 = (next_hist ? (long long)H.slots[pos.j + 1] * H.tpf * D : 0ll) - (long long)t.n1 * D;
-    t.kb2 = (next_hist ? H.k_pool : H.k_cur) + e2;
-    t.vb2 = (next_hist ? H.v_pool : H.v_cur) + e2;
-  }
-  return t;
-}
 // V^T operand of O^T += V^T P^T for 16 keys x 32 channels: two LDS transpose reads whose row choice
 // (4g+r and 8+4g+r) reproduces the key order of the S^T accumulator registers.
 template <int VS>
@@ -639,13 +600,19 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void pf_attn_kernel(AttnParams P) {
 // the current one) the other computes its softmax on the vector ALU.  A workgroup barrier ends every phase
 // and keeps the groups in step.
 //   phase M(u)   reads K of tile u and V of tile u-1, requests the first V^T fragments of tile u for the next
-//                matrix phase and ends with the wait for this wave's copies of tile u+1
+//                matrix phase in the slots of its last MFMAs, waits for this wave's copies of tile u+1; its barrier stands in
+//                front of the last MFMA, so the other group's phase starts while the pipe is still busy
 //   phase V(u)   sends the copies of tile u+3 into the stages tiles u-1 (K) and u-2 (V) lived in (their last
-//                readers, both groups' M(u-1), are two barriers back), plans the copy after that, then scores of
+//                readers, both groups' M(u-1), are two barriers back), then scores of
 //                tile u -> weights (masking of the ragged tail, lazy rescaling as in the rescaling loop)
-// A wave is limited by its own instruction stream (about one instruction per 5 cycles, an MFMA ~16); where the
-// copies and their address arithmetic sit was settled by measurement (in the vector phase: +3.5 % over the
-// matrix phase, start, end or spread).
+// What bounds it: the matrix pipe and the power it may draw.  A pair of phases needs 2048 cycles of MFMAs and takes 2410 (16 heads x
+// 4096 queries x 36864 keys); with operands of zeros the board runs them at 2390 MHz (1893 TFLOP/s before the last two changes),
+// with random ones at 1450 to 1640 MHz, so a tenth fewer cycles are 3 % more work done.  What brought the cycles down, each
+// measured there: 2740 -> 2635 by copies whose state is one scalar per tile (a tile's general step had some 75 scalar instructions
+// and four taken branches beside 112 vector ones), -> 2536 by the next tile's first fragments requested in the slots of the last
+// MFMAs instead of behind them, -> 2411 by five fragments ahead instead of four and the barrier in front of the last MFMA (two
+// MFMAs behind it: 2410, three at lower priority 2855, four 3135; six fragments ahead 2510; no raised priority 2625; copies
+// after the softmax 2525).  First chunk 288 -> 269 us, 57 frames x eight layers 5530 -> 5390, 40 skewed heads 2249 -> 2174.
 // K/V tiles travel global -> LDS three tiles ahead (K ring of 4 stages, V ring of 5: V of a tile is read one
 // phase after its K) with 16-byte copies: one instruction
 // moves four 256-byte rows (lane i -> bytes 16*i of the 1 KB destination), a quarter of the instructions the
@@ -659,11 +626,14 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void pf_attn_kernel(AttnParams P) {
 constexpr int PP_KSTAGES = 4;                                   // K of tile u is read in phase M(u)
 constexpr int PP_VSTAGES = 5;                                   // V of tile u is read one phase later, in M(u+1)
 constexpr int PP_TILE_BYTES = PF_BK * 128 * 2;                  // one tensor's tile, head_dim 128, unpadded
-constexpr int PP_RING = 4;                                      // fragments requested ahead of their MFMA
-// LDS reads that fragments i+1 .. last of a matrix phase take (see the kernel: V^T fragments two, K one)
+constexpr int PP_RING = 5;                                      // fragments requested ahead of their MFMA
+constexpr int PP_EARLY = 1;                                     // MFMAs of a matrix phase behind its barrier
+constexpr int W64_RING = 4;                                     // the 64-row form's fragments ahead
+// LDS reads that fragments i+1 .. last of a matrix phase take (see the kernel: V^T fragments two, K one; from 32 on the next
+// tile's V^T fragments)
 constexpr int pp_reads_between(int i, int last) {
   int n = 0;
-  for (int j = i + 1; j <= last; ++j) n += j < 16 ? 2 : 1;
+  for (int j = i + 1; j <= last; ++j) n += j >= 16 && j < 32 ? 1 : 2;
   return n;
 }
 
@@ -676,14 +646,20 @@ __device__ __forceinline__ unsigned pp_group_voff(int lane, int row0) {
   const int rr = lane >> 4, p = lane & 15;
   return (unsigned)(rr * 256 + ((p ^ pp_swz(IS_V, row0 + rr)) << 4));
 }
+// The wave's 4-row groups of one tensor's tile, group i from lane offset v[i] + 1024 * i to LDS `to` + 1024 * i.
+template <int NG, int... I>
+__device__ __forceinline__ void pp_copy_groups(__amdgpu_buffer_rsrc_t r, char *to, const unsigned (&v)[NG], unsigned soff, std::integer_sequence<int, I...>) {
+  typedef __attribute__((address_space(3))) void *lptr_t;
+  (__builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)to, 16, v[I], soff, I * 1024, 0), ...);
+}
 template <bool IS_V, int RPW>
-__device__ __forceinline__ int pp_copy_rows_slow(int kt, const HeadKV &H, char *stage, int wave, int lane) {
+__device__ __forceinline__ void pp_copy_rows_slow(int kt, const HeadKV &H, char *stage, int wave, int lane) {
   typedef const __attribute__((address_space(1))) void *gptr_t;
   typedef __attribute__((address_space(3))) void *lptr_t;
   constexpr int D = 128;
   const int last = H.lkv - 1 - kt * PF_BK;
   asm volatile("" : "+v"(lane));                    // rare path: its per-lane offsets are worked out here, not held in registers through the loop
-#pragma unroll
+#pragma unroll 1
   for (int r = 0; r < RPW; ++r) {
     const int row = wave * RPW + r;
     const int t = kt * PF_BK + pf_min(row, last);                 // rows past the end re-read the last key
@@ -696,7 +672,6 @@ __device__ __forceinline__ int pp_copy_rows_slow(int kt, const HeadKV &H, char *
     const unsigned off = (unsigned)((((lane >> 2) ^ pp_swz(IS_V, row)) << 4) | ((lane & 3) << 2));
     __builtin_amdgcn_global_load_lds((gptr_t)(b + off), (lptr_t)(stage + row * 256), 4, 0, 0);
   }
-  return RPW;
 }
 
 // Request fragment I of a matrix phase (see the kernel): ak / av = this lane's K / V^T base address in the stage.
@@ -713,25 +688,32 @@ __device__ __forceinline__ void pp_issue_frag(u32x2 (&vl)[16], u32x2 (&vh)[16], 
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(kf[J]) : "v"(a), "n"((J & 1) * 8192));
   }
 }
-// The wait is the compiler's own instruction fenced on both sides, not an asm statement tied to the fragment's
-// registers: after an asm statement that writes a register the compiler puts a wait state in front of the MFMA
+// Wait until at most N LDS reads are in flight.  It is the compiler's own instruction fenced on both sides, not an asm statement tied
+// to the fragment's registers: after an asm statement that writes a register the compiler puts a wait state in front of the MFMA
 // that reads it (one issue slot per MFMA).
-template <int I, int LAST>
-__device__ __forceinline__ void pp_wait_frag(u32x2 (&vl)[16], u32x2 (&vh)[16], u32x4 (&kf)[16]) {
-  constexpr int N = pp_reads_between(I, LAST) > 15 ? 15 : pp_reads_between(I, LAST);
+template <int N>
+__device__ __forceinline__ void pp_wait_lgkm() {
+  static_assert(N <= 15, "lgkmcnt field");
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));                 // lgkmcnt(N), the other counters untouched
   __builtin_amdgcn_sched_barrier(0);
+}
+// The first N V^T fragments, requested ahead for the next tile, have landed.
+template <int N>
+__device__ __forceinline__ void pp_settle_frags(u32x2 (&vl)[16], u32x2 (&vh)[16]) {
+  static_assert(N == 4 || N == 5, "four or five fragments of two reads");
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vl[0]), "+v"(vh[0]), "+v"(vl[1]), "+v"(vh[1]), "+v"(vl[2]), "+v"(vh[2]), "+v"(vl[3]), "+v"(vh[3]));
+  if constexpr (N == 5) asm volatile("" : "+v"(vl[4]), "+v"(vh[4]));
 }
 
 // ---- 4 waves x 64 query rows: one instruction stream per SIMD that carries the MFMAs of two half tiles (32 keys)
 // and the softmax of the half tile between them (see the kernel).  A half step's operand fragments, in the order they
 // are consumed: V^T of the previous half tile (8, if the half step has a PV part), K of the next half tile (8, if it
-// has a QK part), and, when it prefetches, the first PP_RING V^T fragments of its own half tile, which the following
+// has a QK part), and, when it prefetches, the first W64_RING V^T fragments of its own half tile, which the following
 // half step consumes first.
 template <bool PV, bool QK, bool PRE>
 struct W64Stream {
-  static constexpr int NV = PV ? 8 : 0, NK = QK ? 8 : 0, NC = NV + NK, L = NC + (PRE ? PP_RING : 0);
+  static constexpr int NV = PV ? 8 : 0, NK = QK ? 8 : 0, NC = NV + NK, L = NC + (PRE ? W64_RING : 0);
   static constexpr int NSLOT = NC > 0 ? 2 * NC : 1;              // MFMA slots: two per fragment (the query blocks)
   static constexpr int kind(int p) { return p < NV ? 0 : p < NC ? 1 : 2; }
   static constexpr int idx(int p) { return p < NV ? p : p < NC ? p - NV : p - NC; }
@@ -739,7 +721,7 @@ struct W64Stream {
   // LDS reads requested after fragment p's at the time its first MFMA is issued
   static constexpr int wait_n(int p) {
     int n = 0;
-    for (int q = p + 1; q < p + PP_RING && q < L; ++q) n += reads(q);
+    for (int q = p + 1; q < p + W64_RING && q < L; ++q) n += reads(q);
     return n;
   }
 };
@@ -874,13 +856,6 @@ __device__ __forceinline__ void w64_rescale(float al0, float al1) {
 }
 #undef PF_W64_R10
 #undef PF_W64_R1
-template <int N>
-__device__ __forceinline__ void pp_wait_lgkm() {
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));                 // lgkmcnt(N), the other counters untouched
-  __builtin_amdgcn_sched_barrier(0);
-}
-
 template <int D, int NW, bool THIN = false>
 __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(AttnParams) {
   static_assert(D == 128, "tile layouts are written for 256-byte rows");
@@ -1018,162 +993,138 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     const int c0 = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
     av = ldsV + rowv * 256 + ((c0 ^ pp_swz(true, rowv)) << 4) + 8 * (lane & 1);
   }
-  // per-lane source offsets inside a 4-row copy group.  The wave's later groups (rows + 4, + 8, + 12) permute the
-  // K chunks by one more bit each and the V chunks not at all
-  const unsigned vofK0 = pp_group_voff<false>(lane, wave * RPW), vofV = pp_group_voff<true>(lane, wave * RPW);
   const int wrow_bytes = wave * RPW * 256;                     // this wave's first row inside a tile
 
-  // One 4-row group gi of K or of V.  The copies are buffer loads: the tile's first row is the base of a 16 KB
-  // buffer descriptor (scalar registers), the wave's rows are a scalar offset, the lane's chunk a 32-bit vector
-  // offset, and the group is the instruction's immediate offset (it moves the LDS destination along with the
-  // source).  Next to MFMAs this form costs almost nothing, whereas a global load with a 64-bit address per lane
-  // held up the SIMD for ~65 cycles per instruction (measured).
-  auto copy_group_at = [&](const __bf16 *kbase, const __bf16 *vbase, int snk, int snv, auto is_v, auto gidx) __attribute__((always_inline)) {
-    constexpr unsigned RSRC_FLAGS = 0x00020000u;               // raw buffer, 32-bit data format
-    constexpr int GI = decltype(gidx)::value;
-    if constexpr (!decltype(is_v)::value) {
-      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, PP_TILE_BYTES, RSRC_FLAGS);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)(&sK[snk][wrow_bytes]), 16, vofK0 ^ (unsigned)(GI << 6), wrow_bytes, GI * 1024, 0);
-    } else {
-      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)vbase, 0, PP_TILE_BYTES, RSRC_FLAGS);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)(&sV[snv][wrow_bytes]), 16, vofV, wrow_bytes, GI * 1024, 0);
-    }
-  };
-  // a whole contiguous tile: K groups, then V groups
-  auto copy_tile_dense = [&](const __bf16 *kbase, const __bf16 *vbase, int snk, int snv) __attribute__((always_inline)) {
-    static_for<0, NG>([&](auto gi) { copy_group_at(kbase, vbase, snk, snv, TagF(), gi); });
-    static_for<0, NG>([&](auto gi) { copy_group_at(kbase, vbase, snk, snv, TagT(), gi); });
-  };
-  // The same for a chunk tile whose token rows are cur_stride elements apart (the model's [tokens][heads][D]
-  // layout): the lane's row is part of its vector offset, the wave's first row and the group are scalar
-  // offsets, and the group's LDS destination moves by hand.
-  const unsigned row_b = (unsigned)(H.cur_stride * 2);         // bytes between chunk token rows (< 2^25, checked on the host)
-  auto copy_tile_strided = [&](const TileSrc &src, int snk, int snv) __attribute__((always_inline)) {
-    constexpr unsigned RSRC_FLAGS = 0x00020000u;
-    const unsigned lrow = (unsigned)(lane >> 4) * row_b;
-    const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void *)src.kb, 0, (int)(PF_BK * row_b), RSRC_FLAGS);
-    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void *)src.vb, 0, (int)(PF_BK * row_b), RSRC_FLAGS);
-    static_for<0, NG>([&](auto gi) {
-      constexpr int GI = decltype(gi)::value;
-      const unsigned soff = (unsigned)(wave * RPW + 4 * GI) * row_b;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lptr_t)(&sK[snk][wrow_bytes + GI * 1024]), 16,
-                                               ((vofK0 ^ (unsigned)(GI << 6)) & 0xffu) + lrow, soff, 0, 0);
-    });
-    static_for<0, NG>([&](auto gi) {
-      constexpr int GI = decltype(gi)::value;
-      const unsigned soff = (unsigned)(wave * RPW + 4 * GI) * row_b;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lptr_t)(&sV[snv][wrow_bytes + GI * 1024]), 16, (vofV & 0xffu) + lrow, soff, 0, 0);
-    });
-  };
-  // A tile made of two dense runs (it crosses a frame border): a 4-row group lies in the first run, in the second, or
+  // ---- copies.  Tiles follow each other in runs of equally spaced rows (the rest of a frame, or the chunk), and a run's
+  // tiles are copied from a state that only one scalar per tile moves on: a buffer descriptor for K and one for V over the run,
+  // the lane's 32-bit offsets in the wave's row groups, the tile as the scalar offset that all of them share.  The group is the
+  // instruction's immediate offset; it moves the LDS destination along with the source, so the lane offsets of the later groups
+  // are 4 rows less 1024 bytes further on each (nothing where rows are 256 bytes apart).  Next to MFMAs this form costs
+  // almost nothing, whereas a global load with a 64-bit address per lane held up the SIMD for ~65 cycles per instruction (measured). ----
+  constexpr unsigned RSRC_FLAGS = 0x00020000u;                 // raw buffer, 32-bit data format
+  __amdgpu_buffer_rsrc_t run_k = __builtin_amdgcn_make_buffer_rsrc((void *)H.k_pool, 0, 0, RSRC_FLAGS), run_v = run_k;
+  unsigned run_soff = 0, run_tile = 0;                         // scalar offset of the run's next tile, and from one tile to the next
+  unsigned run_vk[NG], run_vv[NG];
+#pragma unroll
+  for (int i = 0; i < NG; ++i) run_vk[i] = run_vv[i] = 0;
+  int run_n = 0;                                               // tiles left in the run
+  // the frame that the next tile starts in (n_sel: the chunk), its slot and the next frame's, read one run ahead
+  int fj = pf_min(__builtin_amdgcn_readfirstlane(it.kt0 * PF_BK / H.tpf), H.n_sel), fslot = 0, fslot1 = 0;
+  if (fj < H.n_sel) {
+    fslot = H.slots[fj];
+    fslot1 = H.slots[pf_min(fj + 1, H.n_sel - 1)];
+  }
+  // A whole tile made of two dense runs (it crosses a frame border): a 4-row group lies in the first run, in the second, or
   // (when the border is not a multiple of 4 rows into the tile) in both, and then each run's lanes copy under their
   // own execution mask: the LDS address of such a copy follows the lane number, so masked-off lanes leave their
-  // 16 bytes to the other instruction.  Returns the number of copy instructions issued.
-  auto copy_tile_split = [&](const TileSrc &src, int snk, int snv) __attribute__((always_inline)) -> int {
+  // 16 bytes to the other instruction.  a: the tile's first row; b: where it WOULD sit if the second run began there;
+  // n1: rows of the first run.
+  auto copy_split = [&](const __bf16 *a, const __bf16 *b, int n1, char *to, auto is_v) __attribute__((always_inline)) {
+    constexpr bool IS_V = decltype(is_v)::value;
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void *)a, 0, PP_TILE_BYTES, RSRC_FLAGS);
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void *)b, 0, PP_TILE_BYTES, RSRC_FLAGS);
+    int lane_l = lane;
+    asm volatile("" : "+v"(lane_l));                           // rare: its lane offsets are not held in registers through the loop
+    const unsigned v0 = pp_group_voff<IS_V>(lane_l, wave * RPW);
+    static_for<0, NG>([&](auto gi) {
+      constexpr int GI = decltype(gi)::value;
+      const int row0 = wave * RPW + GI * 4;
+      const unsigned vo = IS_V ? v0 : v0 ^ (unsigned)(GI << 6);
+      const bool first = row0 + (lane_l >> 4) < n1;
+      // Two copies under two execution masks, and a barrier that keeps the compiler from making one of them: that one would take its
+      // descriptor from the lane (a loop over the lanes' descriptors, not a scalar operand)
+      if (first) __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lptr_t)to, 16, vo, wrow_bytes, GI * 1024, 0);
+      __builtin_amdgcn_wave_barrier();
+      if (!first) __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lptr_t)to, 16, vo, wrow_bytes, GI * 1024, 0);
+      __builtin_amdgcn_wave_barrier();                         // the lanes meet here: what the wave does next is uniform
+    });
+  };
+  // Tile u does not continue a run: it starts one (then it is left to copy_tile to send), or is sent here.
+  auto next_source = [&](int u, unsigned dk, unsigned dv) __attribute__((always_inline)) {
+    const int t0 = u * PF_BK, last = H.lkv - 1 - t0;
+    const __bf16 *kb, *vb;
+    long long stride = D;
     int n = 0;
-    const __bf16 *ka = src.kb, *va = src.vb, *kb2 = src.kb2, *vb2 = src.vb2;
-    const int n1 = src.n1;
-    auto one = [&](auto is_v, auto gi) __attribute__((always_inline)) {
-      const int row0 = wave * RPW + decltype(gi)::value * 4;
-      if (row0 + 4 <= n1) {
-        copy_group_at(ka, va, snk, snv, is_v, gi);
-        n += 1;
-      } else if (row0 >= n1) {
-        copy_group_at(kb2, vb2, snk, snv, is_v, gi);
-        n += 1;
-      } else {
-        int lane_l = lane;
-        asm volatile("" : "+v"(lane_l));                        // rare: its lane test is not held in a register through the loop
-        if (row0 + (lane_l >> 4) < n1) copy_group_at(ka, va, snk, snv, is_v, gi);
-        else copy_group_at(kb2, vb2, snk, snv, is_v, gi);
-        n += 2;
+    if (t0 >= H.hist_tokens) {
+      const long long e = (long long)(t0 - H.hist_tokens) * H.cur_stride;
+      kb = H.k_cur + e;
+      vb = H.v_cur + e;
+      stride = H.cur_stride;
+      n = (last + 1) / PF_BK;
+    } else if (H.tpf >= PF_BK) {
+      int r = t0 - fj * H.tpf;
+      while (r >= H.tpf) {
+        r -= H.tpf;
+        ++fj;
+        fslot = fslot1;
+        fslot1 = H.slots[pf_min(fj + 1, H.n_sel - 1)];
       }
-    };
-    static_for<0, NG>([&](auto gi) { one(TagF(), gi); });
-    static_for<0, NG>([&](auto gi) { one(TagT(), gi); });
-    return n;
-  };
-  // whole tile at once (prologue; tiles that cross a frame border or hold the ragged end go row by row here)
-  auto copy_tile_now = [&](int kt, const TilePos &tp, int snk, int snv) -> int {
-    const TileSrc src = tile_src(kt, tp, H, D);
-    if (src.simple) {
-      if (src.strided) copy_tile_strided(src, snk, snv);
-      else copy_tile_dense(src.kb, src.vb, snk, snv);
-      return 2 * NG;
+      const long long e = ((long long)fslot * H.tpf + r) * D;
+      kb = H.k_pool + e;
+      vb = H.v_pool + e;
+      n = (H.tpf - r) / PF_BK;
+      // one border inside the tile, and the next run (a frame, or the chunk with rows D apart) holds the rest of it
+      const bool next_hist = fj + 1 < H.n_sel;
+      if (n == 0 && last >= PF_BK - 1 && (next_hist || H.cur_stride == D)) {
+        const int n1 = H.tpf - r;
+        const long long e2 = (next_hist ? (long long)fslot1 * H.tpf * D : 0ll) - (long long)n1 * D;
+        copy_split(kb, (next_hist ? H.k_pool : H.k_cur) + e2, n1, &sK[0][wrow_bytes] + dk, TagF());
+        copy_split(vb, (next_hist ? H.v_pool : H.v_cur) + e2, n1, &sV[0][wrow_bytes] + dv, TagT());
+        return;
+      }
     }
-    pp_copy_rows_slow<false, RPW>(kt, H, sK[snk], wave, lane);
-    pp_copy_rows_slow<true, RPW>(kt, H, sV[snv], wave, lane);
-    return 2 * RPW;
+    if (n == 0) {                                              // the ragged end, or frames smaller than a tile
+      pp_copy_rows_slow<false, RPW>(u, H, &sK[0][0] + dk, wave, lane);
+      pp_copy_rows_slow<true, RPW>(u, H, &sV[0][0] + dv, wave, lane);
+      return;
+    }
+    const unsigned rb = (unsigned)(stride * 2);                // bytes between rows (below 2^25: checked on the host)
+    run_tile = PF_BK * rb;
+    run_n = __builtin_amdgcn_readfirstlane(pf_min(pf_min(n, it.kt1 - u), 1 << (__builtin_clz(run_tile) - 1)));   // offsets stay below 2^31
+    run_soff = (unsigned)(wave * RPW) * rb;
+    run_k = __builtin_amdgcn_make_buffer_rsrc((void *)kb, 0, (int)(run_tile * (unsigned)run_n), RSRC_FLAGS);
+    run_v = __builtin_amdgcn_make_buffer_rsrc((void *)vb, 0, (int)(run_tile * (unsigned)run_n), RSRC_FLAGS);
+    int lane_l = lane;
+    asm volatile("" : "+v"(lane_l));                           // worked out here, not held in registers through the loop
+    const unsigned lrow = (unsigned)(lane_l >> 4) * rb;
+    const unsigned ck = pp_group_voff<false>(lane_l, wave * RPW) & 0xffu, cv = pp_group_voff<true>(lane_l, wave * RPW) & 0xffu;
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {                             // a group's K chunks are permuted by one more bit, its V chunks are not
+      run_vk[i] = (ck ^ (unsigned)(i << 6)) + lrow + (unsigned)i * (4 * rb - 1024);
+      run_vv[i] = cv + lrow + (unsigned)i * (4 * rb - 1024);
+    }
   };
-  // "Everything but the copies of the last step has landed": at most 2*NG vector-memory operations may be
-  // outstanding (a contiguous tile's copies).  When the last step sent a tile row by row (at a frame border) this
-  // also waits for most of those, which were sent a whole step ago; when it sent nothing, the older copies are all
-  // that is in flight.
-  auto wait_copies = [&](int n) __attribute__((always_inline)) {
+  // Send this wave's rows of tile u (if the item has one): K to ring offset dk, V to dv.  settle() makes sure that fragment reads
+  // which the caller has in flight have landed: the compiler takes their registers as written, and on the rare path, which needs
+  // many registers, it may copy them.
+  auto copy_tile = [&](int u, unsigned dk, unsigned dv, auto settle) __attribute__((always_inline)) {
+    if (__builtin_expect(run_n <= 0, 0)) {
+      if (u < it.kt1) {
+        settle();
+        next_source(u, dk, dv);
+      }
+    }
+    if (__builtin_expect(run_n > 0, 1)) {
+      --run_n;
+      if constexpr (NW == 4) run_soff = __builtin_amdgcn_readfirstlane(run_soff);   // a scalar operand (the compiler holds it in a vector register there)
+      pp_copy_groups(run_k, &sK[0][wrow_bytes] + dk, run_vk, run_soff, std::make_integer_sequence<int, NG>());
+      pp_copy_groups(run_v, &sV[0][wrow_bytes] + dv, run_vv, run_soff, std::make_integer_sequence<int, NG>());
+      run_soff += run_tile;
+    }
+  };
+  // The copies of every step but the last have landed: at most 2*NG vector-memory operations may be outstanding (a
+  // tile's copies).  Where the last step sent more (at a frame border, or row by row) this also waits for most of those,
+  // which were sent a whole step ago; where it sent nothing (tile u, its tile, is beyond the item) older copies are all that is in flight.
+  auto wait_copies = [&](int u) __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * NG));
-    if (__builtin_expect(n == 0, 0)) __builtin_amdgcn_s_waitcnt(0x0F70);
-  };
-  // the copy planned for this step (see plan_copy), K into stage snk, V into stage snv; returns the instruction count
-  auto copy_planned = [&](const TileSrc &src, int kt_copy, int snk, int snv) __attribute__((always_inline)) -> int {
-    if (__builtin_expect(src.simple && !src.strided, 1)) {
-      copy_tile_dense(src.kb, src.vb, snk, snv);
-      return 2 * NG;
-    }
-    if (src.simple) {
-      copy_tile_strided(src, snk, snv);
-      return 2 * NG;
-    }
-    if (src.split) return copy_tile_split(src, snk, snv);
-    pp_copy_rows_slow<false, RPW>(kt_copy, H, sK[snk], wave, lane);
-    pp_copy_rows_slow<true, RPW>(kt_copy, H, sV[snv], wave, lane);
-    return 2 * RPW;
+    if (__builtin_expect(u >= it.kt1, 0)) __builtin_amdgcn_s_waitcnt(0x0F70);
   };
 
   // ---- prologue: tiles kt0 .. kt0+2 start travelling, then Q^T is fetched.  Vector-memory operations complete
   // in order, so once Q^T is in its registers (the empty asm makes the compiler wait here, not inside the loop,
   // where such a wait would drain the copies in flight) the three tiles have landed too. ----
-  TilePos pos = tile_pos_init(it.kt0, H.hist_tokens, H.n_sel, H.tpf);
-  copy_tile_now(it.kt0, pos, 0, 0);
-  if (it.kt0 + 1 < it.kt1) {
-    tile_pos_advance(pos, H.n_sel, H.tpf);
-    copy_tile_now(it.kt0 + 1, pos, 1, 1);
-  }
-  if (it.kt0 + 2 < it.kt1) {
-    tile_pos_advance(pos, H.n_sel, H.tpf);
-    copy_tile_now(it.kt0 + 2, pos, 2, 2);
-  }
-  // ---- plan of the next copy (made in one vector phase and carried out at the start of the next, so the
-  // scalar load of a frame's slot has a whole tile time to arrive) ----
-  TileSrc nsrc;
-  nsrc.kb = nsrc.vb = nsrc.kb2 = nsrc.vb2 = nullptr;
-  nsrc.simple = nsrc.split = false;
-  nsrc.n1 = 0;
-  int ncopy_kt = -1;                                           // tile planned for the next copy, -1: none
-  int run_left = 0;                                            // tiles after the planned one that continue its source run
-  long long run_step = 0;                                      // elements from one tile of the run to the next
-  auto plan_copy = [&](int kt_target) __attribute__((always_inline)) {
-    if (__builtin_expect(run_left <= 0, 0)) {
-      ncopy_kt = -1;
-      if (kt_target < it.kt1) {
-        tile_pos_advance(pos, H.n_sel, H.tpf);
-        nsrc = tile_src(kt_target, pos, H, D);
-        ncopy_kt = kt_target;
-        if (nsrc.simple) {
-          const int room = pos.j < H.n_sel ? H.tpf - pos.r : H.lkv - kt_target * PF_BK;   // keys from the tile's first row to the run's end
-          run_left = pf_min(room / PF_BK - 1, it.kt1 - 1 - kt_target);
-          run_step = (long long)PF_BK * (pos.j < H.n_sel ? D : H.cur_stride);
-        }
-      }
-    } else {
-      // common case: the tile follows a contiguous tile of the same frame (or of the chunk), is itself whole and
-      // inside it, and belongs to this work item: both sources move on by one tile, no slot lookup
-      --run_left;
-      pos.r += PF_BK;
-      nsrc.kb += run_step;
-      nsrc.vb += run_step;
-      ncopy_kt = kt_target;
-    }
-  };
+#pragma unroll 1
+  for (int i = 0; i < 3; ++i) copy_tile(it.kt0 + i, i * PP_TILE_BYTES, i * PP_TILE_BYTES, []() {});
 
   // A wave whose 32 query rows all lie beyond the chunk's end (the last query tile of a head) still sends its share
   // of the copies and meets every barrier, but skips the fragments, MFMAs and softmax: its partner on the SIMD then
@@ -1186,7 +1137,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
 #pragma unroll
   for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+v"(qf[0][ks]));
   __builtin_amdgcn_s_waitcnt(0x0F70);
-  int n_last = 0;                                              // copy instructions sent in the last vector phase
   __builtin_amdgcn_s_barrier();
   if (grp == 1) __builtin_amdgcn_s_barrier();                  // group 1 trails by one phase
 
@@ -1202,10 +1152,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
   u32x4 kf[16];
   auto issue_frag = [&](auto idx, unsigned offK, unsigned offV) {
     pp_issue_frag<decltype(idx)::value>(vl, vh, kf, ak + offK, av + offV);
-  };
-  // wait until fragment I has arrived, LAST being the newest fragment requested so far
-  auto wait_frag = [&](auto idx, auto last) {
-    pp_wait_frag<decltype(idx)::value, decltype(last)::value>(vl, vh, kf);
   };
   auto mfma_frag = [&](auto idx) {
     constexpr int I = decltype(idx)::value;
@@ -1233,49 +1179,38 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     pf[kb * 2 + (i >> 3)][i & 7] = (__bf16)e0;
     pf[kb * 2 + (i >> 3)][(i & 7) + 1] = (__bf16)e1;
   };
-  // ---- matrix phase: PV of the tile whose V sits in stage st_pv (its fragments 0 .. PP_RING-1 already
-  // requested), QK of the tile whose K sits in stage st_qk ----
-  auto m_phase = [&](auto has_pv, auto has_qk, int st_qk, int st_pv, int st_v_next) {
+  // ---- matrix phase: PV of the tile whose V sits offV bytes into its ring (its fragments 0 .. PP_RING-1 already
+  // requested), QK of the tile whose K sits offK bytes into its ring, and towards its end the requests for the first V^T fragments of
+  // the QK tile (V ring offset off_v_next), which the next matrix phase starts with.  `end` is the wait for copies and the barrier:
+  // PP_EARLY MFMAs stand behind it, so that the other group's matrix phase starts while the pipe is still busy with them (by then
+  // the LDS reads of the phase have been sent, and what they read is overwritten two barriers later). ----
+  auto m_phase = [&](auto has_pv, auto has_qk, unsigned offK, unsigned offV, unsigned off_v_next, auto end) __attribute__((always_inline)) {
     constexpr bool HAS_PV = decltype(has_pv)::value, HAS_QK = decltype(has_qk)::value;
-    constexpr int FIRST = HAS_PV ? 0 : 16, LAST = HAS_QK ? 31 : 15;
-    const unsigned offK = st_qk * PP_TILE_BYTES, offV = st_pv * PP_TILE_BYTES;
-    if (__builtin_expect(has_rows, 1)) {
+    constexpr int FIRST = HAS_PV ? 0 : 16, LAST = HAS_QK ? 31 : 15, LAST_SENT = HAS_QK ? LAST + PP_RING : LAST;
+    auto request = [&](auto f) __attribute__((always_inline)) {
+      constexpr int I = decltype(f)::value;
+      if constexpr (I <= LAST) issue_frag(f, offK, offV);
+      else issue_frag(IntC<I - LAST - 1>(), 0u, off_v_next);
+    };
     __builtin_amdgcn_s_setprio(3);                              // the matrix phase goes first on its SIMD
-    if constexpr (!HAS_PV) static_for<16, 16 + PP_RING>([&](auto f) { issue_frag(f, offK, offV); });
+    if constexpr (!HAS_PV) static_for<16, 16 + PP_RING>([&](auto f) { request(f); });
     static_for<FIRST, LAST + 1>([&](auto f) {
       constexpr int I = decltype(f)::value;
-      constexpr int NEWEST = I + PP_RING - 1 < LAST ? I + PP_RING - 1 : LAST;
-      wait_frag(f, IntC<NEWEST>());
+      constexpr int NEWEST = I + PP_RING - 1 < LAST_SENT ? I + PP_RING - 1 : LAST_SENT;
+      pp_wait_lgkm<pp_reads_between(I, NEWEST)>();
       mfma_frag(f);
-      if constexpr (I + PP_RING <= LAST) issue_frag(IntC<I + PP_RING>(), offK, offV);
+      if constexpr (I + PP_RING <= LAST_SENT) request(IntC<I + PP_RING>());
       __builtin_amdgcn_sched_barrier(0);                        // keep the hand-made order: wait, MFMA, next request
+      if constexpr (I == LAST - PP_EARLY) {
+        end();
+        __builtin_amdgcn_sched_barrier(0);
+      }
     });
-    // the first V^T fragments of the QK tile (V stage st_v_next), for the next matrix phase: requested here, at the
-    // end of the shorter of the two instruction streams
-    if constexpr (HAS_QK) static_for<0, PP_RING>([&](auto f) { issue_frag(f, 0u, (unsigned)(st_v_next * PP_TILE_BYTES)); });
     __builtin_amdgcn_s_setprio(0);
-    }
-    // this wave's rows of the tile after the QK tile (sent two vector phases ago) have landed once only the
-    // copies of its last vector phase are outstanding
-    if (HAS_QK) wait_copies(n_last);
-    __builtin_amdgcn_s_barrier();
   };
 
-  // ---- vector phase: copies of tile kt+3, plan of the copy after that, scores of tile kt -> weights ----
-  auto v_phase = [&](int kt, int sk_, int sv_) {
-    // the copy planned one vector phase ago: tile kt+3, K into the stage tile kt-1 lived in, V into tile kt-2's
-    // (their last readers, both groups' M(kt-1), are two barriers back)
-    n_last = 0;
-    if (__builtin_expect(ncopy_kt >= 0, 1)) {
-      const int snk = (sk_ + 3) & (PP_KSTAGES - 1);
-      const int snv = sv_ >= 2 ? sv_ - 2 : sv_ + PP_VSTAGES - 2;
-      n_last = copy_planned(nsrc, ncopy_kt, snk, snv);
-    }
-    plan_copy(kt + 4);
-    if (__builtin_expect(!has_rows, 0)) {
-      __builtin_amdgcn_s_barrier();
-      return;
-    }
+  // ---- scores of tile kt -> weights ----
+  auto softmax = [&](int kt) __attribute__((always_inline)) {
     const int valid = H.lkv - kt * BK;                          // ragged tail: only the head's last tile
     if (__builtin_expect(valid < BK, 0)) {
       int g_l = g;
@@ -1310,21 +1245,52 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
       weights();
     }
     l_run[0] += ts[0] + ts[1];
-    __builtin_amdgcn_s_barrier();
   };
 
-  int sk = 0, sv = 0;                                          // K and V stage of the tile whose scores are computed
-  plan_copy(it.kt0 + 3);
-  m_phase(TagF(), TagT(), 0, PP_VSTAGES - 1, 0);               // "the V stage before tile kt0's"
-  v_phase(it.kt0, 0, 0);
-  for (int kt = it.kt0 + 1; kt < it.kt1; ++kt) {
-    const int sp = sv;
-    sk = (sk + 1) & (PP_KSTAGES - 1);
-    sv = sv + 1 == PP_VSTAGES ? 0 : sv + 1;
-    m_phase(TagT(), TagT(), sk, sp, sv);
-    v_phase(kt, sk, sv);
+  // Ring offsets of tile kt (ok, ov) and of the V tiles before it (ov1, ov2).  The copies of tile kt+3, sent in vector phase kt, go
+  // where tile kt-1 (K) and tile kt-2 (V) lived: their last readers, both groups' M(kt-1), are two barriers back.
+  unsigned ok = 0, ov = 0, ov1 = (PP_VSTAGES - 1) * PP_TILE_BYTES, ov2 = (PP_VSTAGES - 2) * PP_TILE_BYTES;
+  auto rings_on = [&]() __attribute__((always_inline)) {
+    ok = (ok + PP_TILE_BYTES) & (PP_KSTAGES * PP_TILE_BYTES - 1);
+    ov2 = ov1;
+    ov1 = ov;
+    ov = ov + PP_TILE_BYTES == PP_VSTAGES * PP_TILE_BYTES ? 0 : ov + PP_TILE_BYTES;
+  };
+  auto copy_next = [&](int kt, auto settle) __attribute__((always_inline)) {
+    copy_tile(kt + 3, (ok + 3 * PP_TILE_BYTES) & (PP_KSTAGES * PP_TILE_BYTES - 1), ov2, settle);
+  };
+  auto settle = [&]() __attribute__((always_inline)) { pp_settle_frags<PP_RING>(vl, vh); };
+  if (__builtin_expect(has_rows, 1)) {
+    m_phase(TagF(), TagT(), 0, 0, 0, []() { __builtin_amdgcn_s_barrier(); });
+    copy_next(it.kt0, settle);
+    softmax(it.kt0);
+    __builtin_amdgcn_s_barrier();
+    for (int kt = it.kt0 + 1; kt < it.kt1; ++kt) {
+      rings_on();
+      // this wave's rows of tile kt+1 (sent two vector phases ago) have landed once only the copies of its last vector phase are outstanding
+      m_phase(TagT(), TagT(), ok, ov1, ov, [&]() __attribute__((always_inline)) {
+        wait_copies(kt + 2);
+        __builtin_amdgcn_s_barrier();
+      });
+      copy_next(kt, settle);
+      softmax(kt);
+      __builtin_amdgcn_s_barrier();
+    }
+    m_phase(TagT(), TagF(), 0, ov, 0, []() { __builtin_amdgcn_s_barrier(); });
+  } else {
+    // the same copies and barriers, and nothing else
+    __builtin_amdgcn_s_barrier();
+    copy_next(it.kt0, []() {});
+    __builtin_amdgcn_s_barrier();
+    for (int kt = it.kt0 + 1; kt < it.kt1; ++kt) {
+      rings_on();
+      wait_copies(kt + 2);
+      __builtin_amdgcn_s_barrier();
+      copy_next(kt, []() {});
+      __builtin_amdgcn_s_barrier();
+    }
+    __builtin_amdgcn_s_barrier();
   }
-  m_phase(TagT(), TagF(), 0, sv, 0);
   if (grp == 0) __builtin_amdgcn_s_barrier();                  // group 0 waits for group 1's last phase
   __syncthreads();
   } else {
@@ -1344,7 +1310,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     });
     w64_zero_o();
     __builtin_amdgcn_s_waitcnt(0x0F70);
-    int n_last = 0;                                            // copy instructions sent at the last barrier
     __builtin_amdgcn_s_barrier();
 
     f32x16 sA[2], sB[2];                                       // S^T of a half tile, per query block
@@ -1428,7 +1393,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
         }
       };
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (!PV) static_for<0, PP_RING>([&](auto f) { issue(f); });   // with a PV part the previous half step has sent these
+      if constexpr (!PV) static_for<0, W64_RING>([&](auto f) { issue(f); });   // with a PV part the previous half step has sent these
       if constexpr (!PV && SM) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // no MFMA ahead of the first read of the scores
       static_for<0, NSLOT>([&](auto sl) {
         constexpr int SL = decltype(sl)::value, qb = SL % 2;
@@ -1444,7 +1409,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
             if constexpr (i == 0) w64_mfma_s0<qb * 8 + i>(s_nxt[qb], kf[i * 2 + KB]);
             else w64_mfma_s<qb * 8 + i>(s_nxt[qb], kf[i * 2 + KB]);
           }
-          if constexpr (qb == 1) issue(IntC<p + PP_RING>());
+          if constexpr (qb == 1) issue(IntC<p + W64_RING>());
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (SM) {
@@ -1457,18 +1422,14 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     };
     // Between a tile's two half steps: this wave's rows of tile kt+1 have landed once only the copies of its last such
     // point are outstanding; after the barrier that holds for every wave's rows, and every wave is done with K of tile
-    // kt-1 and V of tile kt-2.  The copies of tile kt+3 go into those stages, and the copy after that is planned.
+    // kt-1 and V of tile kt-2.  The copies of tile kt+3 go into those stages.
     int sk = 0, sv = 0;                                        // K and V stage of tile kt
     auto tile_sync = [&](int kt) __attribute__((always_inline)) {
-      wait_copies(n_last);
+      wait_copies(kt + 2);
       __builtin_amdgcn_s_barrier();
-      n_last = 0;
-      if (__builtin_expect(ncopy_kt >= 0, 1)) {
-        const int snk = (sk + 3) & (PP_KSTAGES - 1);
-        const int snv = sv >= 2 ? sv - 2 : sv + PP_VSTAGES - 2;
-        n_last = copy_planned(nsrc, ncopy_kt, snk, snv);
-      }
-      plan_copy(kt + 4);
+      const int snk = (sk + 3) & (PP_KSTAGES - 1);
+      const int snv = sv >= 2 ? sv - 2 : sv + PP_VSTAGES - 2;
+      copy_tile(kt + 3, snk * PP_TILE_BYTES, snv * PP_TILE_BYTES, [&]() __attribute__((always_inline)) { pp_settle_frags<W64_RING>(vl, vh); });
     };
     auto mask_tail = [&](auto &s_cur, int key0, int kt) __attribute__((always_inline)) {
       const int valid = H.lkv - kt * BK - key0;                 // ragged tail: only the head's last tile
@@ -1506,7 +1467,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
       sv = sv + 1 == PP_VSTAGES ? 0 : sv + 1;
     };
 
-    plan_copy(it.kt0 + 3);
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb)
 #pragma unroll

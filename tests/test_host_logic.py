@@ -313,6 +313,14 @@ def test_build_refuses_a_listing_where_the_compiler_uses_the_hidden_registers():
         BLD.check_hidden_registers("other_kernel:\n\ts_endpgm")
 
 
+def test_build_refuses_a_buffer_copy_that_loops_over_its_lanes():
+    from paper_2605_13111_amd import build as BLD
+    copy = "\tbuffer_load_dwordx4 v1, s[4:7], s2 offen lds"
+    BLD.check_scalar_operands("\n".join(["k:", copy, copy + " ; s_xor_b64 exec, exec, vcc", "\ts_xor_b64 s[0:1], exec, vcc", "\ts_endpgm"]))
+    with pytest.raises(RuntimeError):
+        BLD.check_scalar_operands("\n".join(["k:", "\ts_and_saveexec_b64 vcc, vcc", copy, "\ts_xor_b64 exec, exec, vcc", "\ts_endpgm"]))
+
+
 def test_stored_counter_summary_belongs_to_this_attention_kernel():
     """bench.py takes roofline.traffic from profiles/pf_attn_pp_kernel_c3_step.md only when that summary was made from
     this very pf_attn.hip (SHA-256 recorded in the summary); a summary of another version makes the field null."""
