@@ -1,13 +1,15 @@
 // Offline tri-pattern head classification (Sec. 4.1; pre-processing and harmonic folding as in the appendix
 // paragraph on the FFT analysis stage), then a vote per head.
 // All arithmetic is fp64: the decisions (thresholds, peak bin) are taken in the precision a host implementation
-// would use.  Two kernels share the steps:
-//   pf_classify_batch_kernel   sequences of 4 to CLS_BATCH_HIST frames (the paper analyses 69): the spectra of 16
-//                              sequences at a time as a matrix product on the fp64 matrix cores
+// would use.  Three kernels share the steps:
+//   pf_classify_batch_kernel   sequences of 4 to 72 frames (the paper analyses 69): a workgroup's sequences side by side in LDS, the
+//                              spectra of 16 at a time as a matrix product on the fp64 matrix cores
+//   pf_classify_rounds_kernel  73 to 256 frames: the same products, 16 sequences at a time through LDS
 //   pf_classify_kernel         others, and launches of few long ones: one workgroup per sequence, a direct DFT (their tables do not fit beside
 //                              16 sequences in LDS)
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <type_traits>
 #include "pf_internal.h"
 
 constexpr int CLS_THREADS = 256;
@@ -130,61 +132,340 @@ __global__ __launch_bounds__(CLS_THREADS) void pf_classify_kernel(ClassifyParams
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Batched form.  A workgroup walks a contiguous run of sequences, 16 at a time (four per wave): a sequence that the sign
-// rates decide is finished there; the others' windowed differences go into an LDS buffer of `cap` rows, and when the
-// buffer is full (or the run ends) their spectra are computed together.  The differences x of length N are folded,
+// Batched form.  A workgroup takes a contiguous run of sequences, one per compute unit where the launch is large, and keeps them in LDS
+// as they lie in memory; a sequence that the sign rates decide is finished there, the others are listed, and every wave then takes 16
+// listed sequences at a time from the raw values to the result.  The differences x of length N are folded,
 // e[m] = x[m] + x[N-m], o[m] = x[m] - x[N-m], so that re X[k] = sum_m e[m] cos(2 pi k m / N) and
 // im X[k] = -sum_m o[m] sin(2 pi k m / N) run over m = 0 .. N/2 only, and both are products of a [16 x N/2] and a
 // [N/2 x 16] matrix on v_mfma_f64_16x16x4 (A: lane l holds row l % 16, inner index l / 16; B: column l % 16, inner index
-// l / 16; result: register r of lane l is row l / 16 + 4 r, column l % 16).  The twiddles are read from a table of
-// N points by the index k m mod N, which every lane carries along by adding 4 k mod N.
-// What it replaces, one workgroup per sequence (the form above), spent its time on barriers, on an fp64 table of N sines
-// per sequence and on three integer instructions and two LDS gathers per multiply-add: 410 us for 92 160 sequences of 69
-// frames, of which the bytes need 6 us.  This form takes 60 us: reading 14, counting and folding 12, the matrix products
-// and amplitudes 23, the scores 10 (each measured by leaving the later ones out); it is bound by the latency of those
-// short chains at three waves per SIMD.  More, smaller workgroups (1024 of 32 rows: 79 us), larger ones of eight waves
-// (72 us) and fewer (512 of 64 rows: 62 us) lose more to half-full row groups and barriers than they hide.
+// l / 16; result: register r of lane l is row l / 16 + 4 r, column l % 16).  Every lane folds its A operands (a quarter of the inner
+// indices) from the raw values straight into registers; the B operands, the same for all waves, lie in LDS as the lanes read them.
+// The amplitudes of a sequence go where its raw values were.
+// Bound: the chain of one workgroup, and the fetching of its code, most of which runs once: 92 160 sequences of 69 frames take
+// 21 us (with 62 us before: four waves in rounds of 16 sequences between barriers, folded into LDS, twiddles gathered by index), of
+// which their 25 MB need 5 and the votes 4.  On the way: raw values through registers into padded rows 25 us, with every loop
+// unrolled (3200 instructions instead of 2200) 29.  48 sequences take as long as before (12 us, the call), 6400 13.0 us against 13.8,
+// 23 040 of 72 frames 14.8 against 23.7, 92 160 of 24 frames 16.0 against 36.1.
 // ---------------------------------------------------------------------------------------------------
-constexpr int CLS_FEW_HIST = 80, CLS_FEW_SEQ = 768;   // longer sequences than this, but fewer: a workgroup each
-constexpr int CLS_BATCH_HIST = 256;     // longest sequence of the batched form (16 rows and the tables: 72 KB of LDS)
 constexpr int CLS_BATCH_MIN = 4;        // shortest sequence with a spectrum (three differences)
-constexpr int CLS_BATCH_LDS = 53 * 1024;  // three workgroups per compute unit where that leaves at least one round's rows
-constexpr int CLS_WAVES = 4;            // of the batched form
+constexpr int CLS_STEPS = 9;            // matrix steps: sequences of at most 72 frames (with 16, for 128 frames, the folded operands of a
+                                        // wave no longer fit its 128 registers: 23 040 of 100 frames took 30 us, in the form below 28)
+constexpr int CLS_WAVES = 16;           // of the batched form
 constexpr int CLS_BATCH_THREADS = CLS_WAVES * 64;
-constexpr int CLS_ROWS_PER_WAVE = 4;
-constexpr int CLS_MAX_CAP = 64;         // rows of the buffer at most
-constexpr int CLS_BATCH_WGS = 768;      // workgroups of a large launch: three per compute unit, all resident
+constexpr int CLS_LDS = 159 * 1024;     // of the 160 KB of a compute unit
+constexpr int CLS_WGS = 256;            // workgroups of a large launch, one per compute unit
+constexpr int CLS_REST = 4;             // bins beyond a multiple of 16 that are not worth a matrix product of their own
 typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 struct ClassifyBatchParams {
   ClassifyParams c;
-  int n_seq, per_wg, cap;
+  int n_seq, per_wg, cap;               // sequences: all, of a workgroup, of one round
 };
-// LDS layout in doubles: tables cos, sin, window [N each]; e and o rows [cap][ld] each; amplitudes [cap][la]; row sums
-// [cap]; then ints: sequence of each row [cap]; then floats: raw sequences [16][n_hist]
 __host__ __device__ constexpr int cls_inner(int N) { return (N / 2 + 1 + 3) / 4 * 4; }      // inner length, padded to the matrix step
-__host__ __device__ constexpr int cls_ld(int N) { return cls_inner(N) | 1; }                // odd: 16 rows start in different banks
-__host__ __device__ constexpr int cls_la(int N) { return (N / 2 + 1) | 1; }
-__host__ __device__ constexpr size_t cls_lds_bytes(int n_hist, int cap) {
-  return sizeof(double) * (3 * (size_t)n_hist + (size_t)cap * (2 * cls_ld(n_hist - 1) + cls_la(n_hist - 1) + 1)) +
-         sizeof(int) * (size_t)cap + sizeof(float) * CLS_WAVES * CLS_ROWS_PER_WAVE * (size_t)n_hist;
+__host__ __device__ constexpr int cls_groups(int N) { return (N / 2 + 15) / 16; }           // bins 1 .. N/2, 16 at a time
+static_assert(cls_inner(71) == 4 * CLS_STEPS && cls_inner(72) > 4 * CLS_STEPS, "72 frames are 71 differences");
+__host__ __device__ constexpr int cls_table(int n) { return (n + 1) & ~1; }                 // what follows starts on a 16-byte border
+// LDS layout in doubles: B operands [groups][CLS_STEPS][cos | sin][64]; tables cos, sin, window [cls_table each]; then floats: raw sequences
+// [cap][n] and a copy's overhang; then ints: listed sequences [cap]
+constexpr int CLS_COPY = 64 * 4;        // floats of one wave's copy
+__host__ __device__ constexpr size_t cls_lds_bytes(int n, int cap) {
+  return sizeof(double) * ((size_t)cls_groups(n - 1) * CLS_STEPS * 128 + 3 * (size_t)cls_table(n)) + sizeof(float) * ((size_t)cap * n + CLS_COPY) +
+         sizeof(int) * (size_t)cap;
 }
 
-static_assert(cls_lds_bytes(CLS_BATCH_HIST, CLS_WAVES * CLS_ROWS_PER_WAVE) <= 160 * 1024 - 256, "one round of the longest sequence fits");
+// A lane's value of the lane d further on in its group of 16 (d = 8, 4, 2, 1: an exchange of halves for what is summed or compared
+// over all 16)
+template <int D>
+__device__ __forceinline__ int row_turn(int x) { return __builtin_amdgcn_update_dpp(x, x, 0x120 | D, 0xf, 0xf, false); }   // row_ror
+template <int D>
+__device__ __forceinline__ double row_turn(double x) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = (unsigned)row_turn<D>((int)(unsigned)u), hi = (unsigned)row_turn<D>((int)(unsigned)(u >> 32));
+  return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+// Sum over the four lanes 16 apart
+__device__ __forceinline__ int quarter_sum(int x) {
+  auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  x = a[0] + a[1];
+  auto b = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return b[0] + b[1];
+}
+__device__ __forceinline__ double quarter_sum(double x) {
+  auto half = [](double v, auto swap) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    auto lo = swap((unsigned)u), hi = swap((unsigned)(u >> 32));
+    return __builtin_bit_cast(double, (unsigned long long)hi[0] << 32 | (unsigned)lo[0]) +
+           __builtin_bit_cast(double, (unsigned long long)hi[1] << 32 | (unsigned)lo[1]);
+  };
+  x = half(x, [](unsigned v) { return __builtin_amdgcn_permlane32_swap(v, v, false, false); });
+  return half(x, [](unsigned v) { return __builtin_amdgcn_permlane16_swap(v, v, false, false); });
+}
 
 __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(ClassifyBatchParams B) {
+  extern __shared__ __attribute__((aligned(16))) double s_batch_mem[];
+  __shared__ int s_count, s_hi, s_lo;
+  typedef __attribute__((address_space(3))) void *lptr_t;
+  constexpr int S = CLS_STEPS, GROUPS = (4 * S - 1 + 15) / 16;     // bin groups at most (N / 2 <= 4 S - 1)
+  const ClassifyParams &P = B.c;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, lq = lane >> 4;
+  const int n = P.n_hist, N = n - 1, nb = N / 2;
+  const int groups = cls_groups(N), steps = cls_inner(N) / 4;
+  // the last group as a matrix product, unless it has a few bins only
+  const int rest = nb - 16 * (groups - 1), full = rest <= CLS_REST ? groups - 1 : groups;
+  const int nt = cls_table(n);
+  double *s_b = s_batch_mem, *s_cos = s_b + groups * S * 128, *s_sin = s_cos + nt, *s_win = s_sin + nt;
+  float *s_raw = (float *)(s_win + nt);
+  int *s_list = (int *)(s_raw + B.cap * n + CLS_COPY);
+  const int seq0 = blockIdx.x * B.per_wg, seq1 = pf_min(seq0 + B.per_wg, B.n_seq);
+
+  auto finish = [&](int seq, int type, double period) {
+    P.prompt_type[seq] = type;
+    if (P.prompt_period) P.prompt_period[seq] = period;
+  };
+  // a round's raw values, as they lie in memory, straight into LDS: 1 KB per copy where they start on a 16-byte border, else 256 bytes;
+  // the last copy's overhang reads zeros (beyond the descriptor's end) and lands behind the last sequence
+  auto request = [&](int sb, int rows) {
+    const float *from = P.logits + (size_t)sb * n;
+    const int bytes = rows * n * (int)sizeof(float);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)from, 0, bytes, 0x00020000u);
+    if (((uintptr_t)from & 15) == 0) {
+      for (int o = wave * 1024; o < bytes; o += CLS_WAVES * 1024)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)((char *)s_raw + o), 16, lane * 16, o, 0, 0);
+    } else {
+      for (int o = wave * 256; o < bytes; o += CLS_WAVES * 256)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)((char *)s_raw + o), 4, lane * 4, o, 0, 0);
+    }
+  };
+  request(seq0, pf_min(B.cap, seq1 - seq0));                       // travels while the tables are made
+  static_assert(8 * CLS_STEPS <= 512, "a table is made by half the threads");
+  {
+    const int m = tid & 511;
+    const bool win = tid >= 512;
+    if (m < N) {                                                   // one copy of the sine for both tables: this code runs once and is fetched for it
+      double sn, cs;
+      sincospi(2.0 * (double)m / (double)(win ? N - 1 : N), &sn, &cs);
+      if (win) s_win[m] = 0.5 - 0.5 * cs;
+      else s_cos[m] = cs, s_sin[m] = sn;
+    }
+  }
+  // The sign rates decide by whole numbers: at least s_hi positive values is an Anchor sequence, at most s_lo a Veil one
+  // (the same quotients and comparisons as for one sequence, made once for every count)
+  if (wave == CLS_WAVES - 1) {
+    int hi = n + 1, lo = -1;
+    for (int c0 = 0; c0 <= n; c0 += 64) {
+      const double r_pos = (double)(c0 + lane) / (double)n;
+      const bool anchor = c0 + lane <= n && r_pos >= P.alpha, veil = c0 + lane <= n && !anchor && 1.0 - r_pos >= P.alpha;
+      const unsigned long long am = __builtin_amdgcn_ballot_w64(anchor), vm = __builtin_amdgcn_ballot_w64(veil);
+      if (am) hi = pf_min(hi, c0 + __builtin_ctzll(am));
+      if (vm) lo = c0 + 63 - __builtin_clzll(vm);
+    }
+    if (lane == 0) {
+      s_hi = hi;
+      s_lo = lo;
+      s_count = 0;
+    }
+  }
+  __syncthreads();
+  // j = k m mod N by a multiplication: k m < 2^11, and the quotient is exact while k m N < 2^22
+  const int inv = (1 << 22) / N + 1;
+  for (int e = tid; e < groups * S * 64; e += CLS_BATCH_THREADS) { // bin k (columns beyond the last repeat it), inner index m
+    const int l = e & 63, gs = e >> 6, g = gs / S, m = 4 * (gs - g * S) + (l >> 4);
+    const int km = m <= nb ? pf_min(1 + g * 16 + (l & 15), nb) * m : 0, j = km - (int)(((long long)km * inv) >> 22) * N;
+    s_b[gs * 128 + l] = s_cos[j];
+    s_b[gs * 128 + 64 + l] = s_sin[j];
+  }
+
+  for (int sb = seq0; sb < seq1; sb += B.cap) {
+    const int rows = pf_min(B.cap, seq1 - sb);
+    if (sb > seq0) request(sb, rows);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                            // this wave's copies have landed
+    __syncthreads();
+
+    // ---- sign rates: 16 sequences per wave, four lanes each ----
+    const int hi = s_hi, lo = s_lo;
+    for (int r0 = wave * 16; r0 < rows; r0 += CLS_WAVES * 16) {
+      const int row = r0 + l16;
+      const float *a = s_raw + pf_min(row, rows - 1) * n;
+      int lq_c = lq;
+      asm volatile("" : "+v"(lq_c));               // places and tests are worked out here: held through the kernel they would take its registers
+      float v[2 * S];                                              // all reads in flight
+#pragma unroll
+      for (int i = 0; i < 2 * S; ++i) v[i] = a[pf_min(4 * i + lq_c, N)];
+      int pos = 0;
+#pragma unroll
+      for (int i = 0; i < 2 * S; ++i) pos += v[i] > 0.0f && 4 * i + lq_c < n ? 1 : 0;
+      pos = quarter_sum(pos);
+      const bool settled = pos >= hi || pos <= lo, mine = lq == 0 && row < rows;
+      if (mine && settled) finish(sb + row, pos >= hi ? PF_ANCHOR : PF_VEIL, INFINITY);
+      const unsigned long long und = __builtin_amdgcn_ballot_w64(mine && !settled);
+      if (und) {
+        int next = 0;
+        if (lane == 0) next = atomicAdd(&s_count, __builtin_popcountll(und));
+        next = __builtin_amdgcn_readfirstlane(next) + __builtin_popcountll(und & ((1ull << lane) - 1ull));
+        if (mine && !settled) s_list[next] = row;
+      }
+    }
+    __syncthreads();
+    const int listed = s_count;
+
+    // ---- 16 listed sequences per wave and turn: difference, mean removal (the differences sum to last - first), window, folding
+    // into the A operands; spectra; folded scores, their maximum, the lowest bin in the tie band ----
+    for (int b0 = wave * 16; b0 < listed; b0 += CLS_WAVES * 16) {
+      double e[S], o[S], total = 0.0;
+      const int first = s_list[pf_min(b0 + l16, listed - 1)] * n;
+      {
+        const float *a = s_raw + first;
+        int lq_b = lq;
+        asm volatile("" : "+v"(lq_b));             // as above
+        const double dmean = ((double)a[N] - (double)a[0]) / (double)N;
+        // the sum of all values comes from the same reads: m = 0 .. nb, N-m+1 for the pairs, and nb + 1 remain
+        if (lq == 0) total = (double)a[nb + 1];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          const int m = 4 * s + lq_b, q = N - m;                   // m and q coincide at N/2 and have no partner at 0
+          const bool in = m <= nb, pair = in && m != 0 && q != m;
+          const int mi = in ? m : 0, qi = pair ? q : 0;
+          const double am = (double)a[mi], aq = (double)a[qi + 1];
+          const double x = in ? ((double)a[mi + 1] - am - dmean) * s_win[mi] : 0.0;
+          const double y = (aq - (double)a[qi] - dmean) * s_win[qi];
+          e[s] = pair ? x + y : x;
+          o[s] = pair ? x - y : 0.0;
+          total += (in ? am : 0.0) + (pair ? aq : 0.0);
+          if (s % 3 == 2) __builtin_amdgcn_sched_barrier(0);       // three steps' reads in flight
+        }
+      }
+      total = quarter_sum(total);
+      // The raw values of these sequences are in registers now (LDS operations of one wave complete in order), and the amplitudes of
+      // bins 1 .. nb go where they were: nb doubles from the first 8-byte border on
+      double *const s_amp = (double *)s_raw - 1;
+      int at[4];                                                   // of this lane's four results
+#pragma unroll
+      for (int r = 0; r < 4; ++r) at[r] = (s_list[pf_min(b0 + lq + 4 * r, listed - 1)] * n + 1) >> 1;
+#pragma unroll 1
+      for (int g = 0; g < full; ++g) {
+        f64x4 re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+        const double *pb = s_b + g * S * 128 + lane;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          if (s < steps) {                                         // uniform
+            re = __builtin_amdgcn_mfma_f64_16x16x4f64(e[s], pb[s * 128], re, 0, 0, 0);
+            im = __builtin_amdgcn_mfma_f64_16x16x4f64(o[s], pb[s * 128 + 64], im, 0, 0, 0);
+          }
+        const int k = 1 + g * 16 + l16;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (k <= nb && b0 + lq + 4 * r < listed) s_amp[at[r] + k] = sqrt(re[r] * re[r] + im[r] * im[r]);
+      }
+      // a few bins left over, two at a time: a lane adds up its own inner indices of its sequence, the four lanes of a sequence are
+      // added, and two of them keep a bin each
+#pragma unroll 1
+      for (int i = 0; i < rest && full < groups; i += 2) {
+        double re[2] = {0.0, 0.0}, im[2] = {0.0, 0.0};
+        const double *pb = s_b + full * S * 128 + lq * 16 + i;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          if (s < steps) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              re[j] += e[s] * pb[s * 128 + j];
+              im[j] += o[s] * pb[s * 128 + 64 + j];
+            }
+          }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          re[j] = quarter_sum(re[j]);
+          im[j] = quarter_sum(im[j]);
+        }
+        const double x = lq == 0 ? re[0] : re[1], y = lq == 0 ? im[0] : im[1];
+        if (lq < 2 && i + lq < rest && b0 + l16 < listed) s_amp[((first + 1) >> 1) + 1 + full * 16 + i + lq] = sqrt(x * x + y * y);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      int k = 0;                                                   // lane 16 lq + r writes the result of sequence lq + 4 r
+#pragma unroll 1
+      for (int r = 0; r < 4; ++r) {
+        const double *amp = s_amp + ((s_list[pf_min(b0 + lq + 4 * r, listed - 1)] * n + 1) >> 1);
+        double sc[GROUPS], best = 0.0;
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g) {
+          const int kg = 1 + g * 16 + l16;
+          double v[CLS_HARMONICS];                                 // all in flight
+#pragma unroll
+          for (int h = 1; h <= CLS_HARMONICS; ++h) v[h - 1] = amp[pf_min(h * kg, nb)];
+          constexpr double w[CLS_HARMONICS] = {1.0, 0.5, 1.0 / 3.0, 0.25};
+          sc[g] = 0.0;
+#pragma unroll
+          for (int h = 1; h <= CLS_HARMONICS; ++h) sc[g] = h * kg <= nb ? sc[g] + v[h - 1] * w[h - 1] : sc[g];
+          best = fmax(best, sc[g]);
+        }
+        best = fmax(best, row_turn<8>(best));
+        best = fmax(best, row_turn<4>(best));
+        best = fmax(best, row_turn<2>(best));
+        best = fmax(best, row_turn<1>(best));
+        const bool peak = best > 0.0 && isfinite(best);
+        int kmin = CLS_MAX_HIST;                                   // the lane's lowest bin, then the sequence's (none: beyond the last)
+#pragma unroll
+        for (int g = GROUPS - 1; g >= 0; --g)
+          if (peak && 1 + g * 16 + l16 <= nb && sc[g] >= best * (1.0 - CLS_TIE_REL)) kmin = 1 + g * 16 + l16;
+        kmin = pf_min(kmin, row_turn<8>(kmin));
+        kmin = pf_min(kmin, row_turn<4>(kmin));
+        kmin = pf_min(kmin, row_turn<2>(kmin));
+        kmin = pf_min(kmin, row_turn<1>(kmin));
+        if (l16 == r) k = kmin;
+      }
+      // the sum is with lane l16 = sequence: fetched from there
+      const int which = lq + 4 * l16;
+      const double sum = __shfl(total, which & 15, 64);
+      if (l16 < 4 && b0 + which < listed) {
+        const double period = k <= nb ? (double)N / (double)k : (double)INFINITY;
+        finish(sb + s_list[b0 + which], period < P.beta ? PF_WAVE : sum / (double)n > 0.0 ? PF_ANCHOR : PF_VEIL, period);
+      }
+    }
+    __syncthreads();                               // the next round's values go into the same places
+    if (tid == 0) s_count = 0;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Batched form for sequences whose operands do not fit beside each other in LDS or registers (73 to 256 frames).  A workgroup walks
+// a contiguous run of sequences, 16 at a time (four per wave): a sequence that the sign
+// rates decide is finished there; the others' windowed and folded differences go into an LDS buffer of `cap` rows, and when the
+// buffer is full (or the run ends) their spectra are computed together, as above; the twiddles are read from a table of
+// N points by the index k m mod N, which every lane carries along by adding 4 k mod N.
+// ---------------------------------------------------------------------------------------------------
+constexpr int CLS_FEW_HIST = 80, CLS_FEW_SEQ = 768;   // longer sequences than this, but fewer: a workgroup each
+constexpr int CLS_ROUNDS_HIST = 256;    // its longest sequence (16 rows and the tables: 72 KB of LDS)
+constexpr int CLS_ROUNDS_LDS = 53 * 1024;  // three workgroups per compute unit where that leaves at least one round's rows
+constexpr int CLS_ROUNDS_WAVES = 4;            // of the batched form
+constexpr int CLS_ROUNDS_THREADS = CLS_ROUNDS_WAVES * 64;
+constexpr int CLS_ROUNDS_PER_WAVE = 4;
+constexpr int CLS_ROUNDS_MAX_CAP = 64;         // rows of the buffer at most
+constexpr int CLS_ROUNDS_WGS = 768;      // workgroups of a large launch: three per compute unit, all resident
+
+// LDS layout in doubles: tables cos, sin, window [N each]; e and o rows [cap][ld] each; amplitudes [cap][la]; row sums
+// [cap]; then ints: sequence of each row [cap]; then floats: raw sequences [16][n_hist]
+__host__ __device__ constexpr int cls_rounds_ld(int N) { return cls_inner(N) | 1; }                // odd: 16 rows start in different banks
+__host__ __device__ constexpr int cls_rounds_la(int N) { return (N / 2 + 1) | 1; }
+__host__ __device__ constexpr size_t cls_rounds_lds_bytes(int n_hist, int cap) {
+  return sizeof(double) * (3 * (size_t)n_hist + (size_t)cap * (2 * cls_rounds_ld(n_hist - 1) + cls_rounds_la(n_hist - 1) + 1)) +
+         sizeof(int) * (size_t)cap + sizeof(float) * CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE * (size_t)n_hist;
+}
+
+static_assert(cls_rounds_lds_bytes(CLS_ROUNDS_HIST, CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE) <= 160 * 1024 - 256, "one round of the longest sequence fits");
+
+__global__ __launch_bounds__(CLS_ROUNDS_THREADS) void pf_classify_rounds_kernel(ClassifyBatchParams B) {
   extern __shared__ double s_mem[];
   __shared__ int s_count, s_hi, s_lo;
   const ClassifyParams &P = B.c;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, lq = lane >> 4;
   const int n = P.n_hist, N = n - 1, nb = N / 2;
-  const int ld = cls_ld(N), la = cls_la(N), inner = cls_inner(N);
+  const int ld = cls_rounds_ld(N), la = cls_rounds_la(N), inner = cls_inner(N);
   double *s_cos = s_mem, *s_sin = s_cos + n, *s_win = s_sin + n;
   double *s_e = s_win + n, *s_o = s_e + (size_t)B.cap * ld, *s_amp = s_o + (size_t)B.cap * ld;
   double *s_tot = s_amp + (size_t)B.cap * la;
   int *s_seq = (int *)(s_tot + B.cap);
-  float *s_raw = (float *)(s_seq + B.cap) + (size_t)wave * CLS_ROWS_PER_WAVE * n;
-  for (int m = tid; m < N; m += CLS_BATCH_THREADS) {
+  float *s_raw = (float *)(s_seq + B.cap) + (size_t)wave * CLS_ROUNDS_PER_WAVE * n;
+  for (int m = tid; m < N; m += CLS_ROUNDS_THREADS) {
     double sn, cs;
     sincospi(2.0 * (double)m / (double)N, &sn, &cs);
     s_cos[m] = cs;
@@ -199,7 +480,7 @@ __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(Cl
     s_lo = -1;
   }
   __syncthreads();
-  for (int c = tid; c <= n; c += CLS_BATCH_THREADS) {
+  for (int c = tid; c <= n; c += CLS_ROUNDS_THREADS) {
     const double r_pos = (double)c / (double)n;
     if (r_pos >= P.alpha) atomicMin(&s_hi, c);
     else if (1.0 - r_pos >= P.alpha) atomicMax(&s_lo, c);
@@ -213,26 +494,26 @@ __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(Cl
   };
   const int seq0 = blockIdx.x * B.per_wg, seq1 = pf_min(seq0 + B.per_wg, B.n_seq);
   // a wave's four sequences are consecutive in memory and travel as one flat run
-  constexpr int FLAT = (CLS_ROWS_PER_WAVE * CLS_BATCH_HIST + 63) / 64;
-  const int flat = CLS_ROWS_PER_WAVE * n;
+  constexpr int FLAT = (CLS_ROUNDS_PER_WAVE * CLS_ROUNDS_HIST + 63) / 64;
+  const int flat = CLS_ROUNDS_PER_WAVE * n;
   float ahead[FLAT];
   auto request = [&](int sb) {
-    const int first = pf_min(sb + wave * CLS_ROWS_PER_WAVE, B.n_seq - 1);
+    const int first = pf_min(sb + wave * CLS_ROUNDS_PER_WAVE, B.n_seq - 1);
     const float *from = P.logits + (size_t)first * n;
-    const int most = pf_min(B.n_seq - first, CLS_ROWS_PER_WAVE) * n - 1;
+    const int most = pf_min(B.n_seq - first, CLS_ROUNDS_PER_WAVE) * n - 1;
 #pragma unroll
     for (int i = 0; i < FLAT; ++i)
       if (i * 64 < flat) ahead[i] = from[pf_min(i * 64 + lane, most)];
   };
   request(seq0);
-  for (int sb = seq0; sb < seq1; sb += CLS_WAVES * CLS_ROWS_PER_WAVE) {
+  for (int sb = seq0; sb < seq1; sb += CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE) {
     // ---- four sequences per wave: raw values (requested one round ahead), sign rates ----
 #pragma unroll
     for (int i = 0; i < FLAT; ++i)
       if (i * 64 < flat) {                         // uniform
         if (i * 64 + lane < flat) s_raw[i * 64 + lane] = ahead[i];
       }
-    request(sb + CLS_WAVES * CLS_ROWS_PER_WAVE);
+    request(sb + CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE);
     // the wave's own rows of s_raw are read by other lanes below (LDS operations of one wave complete in order)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -250,7 +531,7 @@ __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(Cl
       pos += __shfl_xor(pos, o, 16);
       total += __shfl_xor(total, o, 16);
     }
-    const int seq = sb + wave * CLS_ROWS_PER_WAVE + lq;
+    const int seq = sb + wave * CLS_ROUNDS_PER_WAVE + lq;
     const bool settled = pos >= hi || pos <= lo, und = seq < seq1 && !settled;
     if (l16 == 0 && seq < seq1 && settled) finish(seq, pos >= hi ? PF_ANCHOR : PF_VEIL, INFINITY);
     const unsigned long long und_rows = __builtin_amdgcn_ballot_w64(und && l16 == 0);
@@ -280,8 +561,8 @@ __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(Cl
     }
     __syncthreads();
     const int rows = s_count;
-    const bool last = sb + CLS_WAVES * CLS_ROWS_PER_WAVE >= seq1;
-    if (rows == 0 || (!last && rows + CLS_WAVES * CLS_ROWS_PER_WAVE <= B.cap)) {
+    const bool last = sb + CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE >= seq1;
+    if (rows == 0 || (!last && rows + CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE <= B.cap)) {
       __syncthreads();                             // every wave has read the count before a faster one appends again
       continue;
     }
@@ -289,7 +570,7 @@ __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(Cl
     // ---- spectra: one task = 16 rows x 16 bins (k = 1 ..), both parts.  Rows beyond the last hold old values;
     // their results are not read ----
     const int row_groups = pf_ceil_div(rows, 16), bin_groups = pf_ceil_div(nb, 16);
-    for (int task = wave; task < row_groups * bin_groups; task += CLS_WAVES) {
+    for (int task = wave; task < row_groups * bin_groups; task += CLS_ROUNDS_WAVES) {
       const int rg = task / bin_groups, k = 1 + (task - rg * bin_groups) * 16 + l16;
       const double *pe = s_e + (size_t)(rg * 16 + l16) * ld + lq, *po = s_o + (size_t)(rg * 16 + l16) * ld + lq;
       // k m mod N for this lane's m = lq, and its step from one m to the next (columns beyond the last bin repeat it)
@@ -316,12 +597,12 @@ __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(Cl
     __syncthreads();
 
     // ---- folded scores, their maximum, the lowest bin in the tie band: 16 lanes per row ----
-    for (int row0 = wave * 4; row0 < rows; row0 += CLS_WAVES * 4) {
+    for (int row0 = wave * 4; row0 < rows; row0 += CLS_ROUNDS_WAVES * 4) {
       const int row = row0 + lq;
       const double *amp = s_amp + (size_t)pf_min(row, rows - 1) * la;
-      double sc[CLS_BATCH_HIST / 32], best = 0.0;
+      double sc[CLS_ROUNDS_HIST / 32], best = 0.0;
 #pragma unroll
-      for (int i = 0; i < CLS_BATCH_HIST / 32; ++i) {
+      for (int i = 0; i < CLS_ROUNDS_HIST / 32; ++i) {
         const int k = 1 + i * 16 + l16;
         sc[i] = 0.0;
         if (i * 16 < nb) {                         // uniform: bins beyond the last are not looked at
@@ -337,7 +618,7 @@ __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(Cl
       int kmin = 0;
       if (best > 0.0 && isfinite(best)) {
 #pragma unroll
-        for (int i = CLS_BATCH_HIST / 32 - 1; i >= 0; --i)
+        for (int i = CLS_ROUNDS_HIST / 32 - 1; i >= 0; --i)
           if (i * 16 < nb && 1 + i * 16 + l16 <= nb && sc[i] >= best * (1.0 - CLS_TIE_REL)) kmin = 1 + i * 16 + l16;
       }
       // the lane's lowest bin, then the row's (0 = none)
@@ -366,7 +647,7 @@ __global__ __launch_bounds__(CLS_VOTE_WAVES * 64) void pf_classify_vote_kernel(c
   const int h = blockIdx.x * 64 + lane;
   int votes[3] = {0, 0, 0};
   if (h < n_heads) {
-#pragma unroll 4
+#pragma unroll 16
     for (int p = wave; p < n_prompts; p += CLS_VOTE_WAVES) {
       const int t = prompt_type[(size_t)p * n_heads + h];
 #pragma unroll
@@ -403,19 +684,29 @@ extern "C" int pf_classify_heads(const float *logits, int n_prompts, int n_heads
   // Few long sequences finish earlier in a workgroup each: of 240 frames 48 take 13.8 us against 23.1 us in batches, 400 17.8 against
   // 23.4 (1920 of 200 frames 56.6 against 21.5); of 100 frames 48 take 12.9 against 13.7, of 69 or fewer as long either way.
   const bool few = n_hist > CLS_FEW_HIST && (long long)n_prompts * n_heads < CLS_FEW_SEQ;
-  if (n_hist >= CLS_BATCH_MIN && n_hist <= CLS_BATCH_HIST && !few) {
-    // the longer the buffer, the fuller its groups of 16 rows; 48 rows for the paper's 69 frames
+  if (n_hist < CLS_BATCH_MIN || n_hist > CLS_ROUNDS_HIST || few) {
+    hipLaunchKernelGGL(pf_classify_kernel, dim3(n_prompts * n_heads), dim3(CLS_THREADS), 0, (hipStream_t)stream, P);
+  } else if (cls_inner(n_hist - 1) <= 4 * CLS_STEPS) {
+    // a workgroup per compute unit, as many sequences each, in as few rounds of equal size as LDS allows
     ClassifyBatchParams B;
     B.c = P;
     B.n_seq = n_prompts * n_heads;
-    B.cap = CLS_MAX_CAP;
-    while (B.cap > CLS_WAVES * CLS_ROWS_PER_WAVE && cls_lds_bytes(n_hist, B.cap) > CLS_BATCH_LDS) B.cap -= 16;
-    const int batches = pf_ceil_div(B.n_seq, CLS_WAVES * CLS_ROWS_PER_WAVE);
-    B.per_wg = pf_ceil_div(batches, CLS_BATCH_WGS) * CLS_WAVES * CLS_ROWS_PER_WAVE;
+    B.per_wg = pf_ceil_div(B.n_seq, CLS_WGS);
+    const size_t tables = cls_lds_bytes(n_hist, 0), each = cls_lds_bytes(n_hist, 1) - tables;
+    B.cap = pf_ceil_div(B.per_wg, pf_ceil_div(B.per_wg, (int)((CLS_LDS - tables) / each)));
     hipLaunchKernelGGL(pf_classify_batch_kernel, dim3(pf_ceil_div(B.n_seq, B.per_wg)), dim3(CLS_BATCH_THREADS),
                        cls_lds_bytes(n_hist, B.cap), (hipStream_t)stream, B);
   } else {
-    hipLaunchKernelGGL(pf_classify_kernel, dim3(n_prompts * n_heads), dim3(CLS_THREADS), 0, (hipStream_t)stream, P);
+    // the longer the buffer, the fuller its groups of 16 rows
+    ClassifyBatchParams B;
+    B.c = P;
+    B.n_seq = n_prompts * n_heads;
+    B.cap = CLS_ROUNDS_MAX_CAP;
+    while (B.cap > CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE && cls_rounds_lds_bytes(n_hist, B.cap) > CLS_ROUNDS_LDS) B.cap -= 16;
+    const int batches = pf_ceil_div(B.n_seq, CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE);
+    B.per_wg = pf_ceil_div(batches, CLS_ROUNDS_WGS) * CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE;
+    hipLaunchKernelGGL(pf_classify_rounds_kernel, dim3(pf_ceil_div(B.n_seq, B.per_wg)), dim3(CLS_ROUNDS_THREADS),
+                       cls_rounds_lds_bytes(n_hist, B.cap), (hipStream_t)stream, B);
   }
   PF_HIP_CHECK(hipGetLastError());
   hipLaunchKernelGGL(pf_classify_vote_kernel, dim3(pf_ceil_div(n_heads, 64)), dim3(CLS_VOTE_WAVES * 64), 0, (hipStream_t)stream,

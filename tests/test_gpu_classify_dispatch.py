@@ -1,7 +1,8 @@
-"""GPU: both classification kernels give the same types and periods, bit for bit, on either side of the line between them."""
+"""GPU: the classification kernels give the same types and periods, bit for bit, on either side of the lines between them."""
 import pytest
 import torch
 
+from oracle import classify as OC
 from paper_2605_13111_amd import binding as B
 from paper_2605_13111_amd import synth
 
@@ -16,3 +17,26 @@ def test_few_long_sequences_agree_with_many(hist):
     _, t, p = B.pf_classify_heads(logits[:63].contiguous())      # 756: a workgroup each
     torch.cuda.synchronize()
     assert torch.equal(t, types[:63]) and torch.equal(p.view(torch.int64), periods[:63].view(torch.int64))
+
+
+# shortest and longest of the kernel that keeps sequences in LDS, its neighbour; bins left over beside the groups of 16: 0, 1, 2, 3, 4, 5
+# (N/2 = 16, 17, 18, 35, 20, 21) and a group of its own; even lengths whose rows start in few banks
+@pytest.mark.parametrize("hist", [4, 5, 6, 33, 35, 38, 42, 44, 64, 69, 71, 72, 73])
+@pytest.mark.parametrize("skip", [0, 1])
+def test_short_sequences_in_lds(hist, skip):
+    logits, _ = synth.head_logits(40, 23, hist, 11)
+    flat = torch.empty(logits.numel() + skip, device="cuda:0")   # skip = 1: no 16-byte border at the start
+    flat[skip:] = logits.flatten().to("cuda:0")
+    view = flat[skip:].view(40, 23, hist)
+    head, types, periods = B.pf_classify_heads(view)
+    want_head, want_types, want_periods = OC.classify_heads(logits.numpy())
+    assert (head.cpu().numpy() == want_head).all() and (types.cpu().numpy() == want_types).all()
+    assert (periods.cpu().numpy() == want_periods).all()
+
+
+def test_more_sequences_per_workgroup_than_lds_holds():
+    logits, _ = synth.head_logits(16, 360, 72, 3)
+    logits = logits.to("cuda:0").repeat(21, 1, 1)                # 120 960 sequences: two rounds of each workgroup
+    _, types, periods = B.pf_classify_heads(logits)
+    _, t, p = B.pf_classify_heads(logits[:16].contiguous())
+    assert torch.equal(types, t.repeat(21, 1)) and torch.equal(periods, p.repeat(21, 1))
