@@ -350,24 +350,38 @@ __device__ __forceinline__ void classic_loop(const HeadKV &H, int kt0, int kt1, 
 // ---------------------------------------------------------------------------------------------------
 constexpr int attn_stage_floats(int bq, int d) { return bq * (d + 4) + 2 * bq; }
 
-// 16-byte device-scope store: written through to the memory all dies share (see st_dev1).
-__device__ __forceinline__ void st_dev4(float *p, f32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(p), "v"(v) : "memory");
-}
-
-// A partial result of item `it`: O [BQ][D], m [BQ], l [BQ] of its segment `seg`.
+constexpr int ATT_DEVICE_SCOPE = 16;         // sc1 of a buffer load or store: written through to, read from the memory all dies share (see st_dev1)
+// A partial result of item `it`: O (BQ * D floats as the threads hold them, see attn_park), m [BQ], l [BQ] of its segment `seg`.
 template <int D, int BQ>
 __device__ __forceinline__ float *attn_partial(const AttnParams &P, const PfWorkItem &it, int seg) {
   return P.workspace + (size_t)(it.part0 + seg * P.n_qt) * ((size_t)BQ * (D + 2));
 }
 
-// The workgroup has parked its partial result of a split head's item `it`; the last segment of the (head, query tile) to
-// arrive merges all of them.  sM, sInvL: BQ floats of LDS each, not in use.
-template <int D, int BQ, int NT>
-__device__ __forceinline__ void attn_arrive_and_merge(const AttnParams &P, const PfWorkItem &it, float *sM, float *sInvL,
-                                                      int32_t *sFlagp, int tid) {
-  const float c = P.scale_log2;
-  __bf16 *oh = P.out + (size_t)pf_item_head(it) * P.head_stride;
+// Split heads: every workgroup parks its unnormalised result, NV quads of floats per thread in the order the threads hold them (a
+// store is 1 KB, and what a thread needs of the other segments it finds at its own place), and the last segment of the (head, query
+// tile) to arrive adds all of them up, each thread its own values.
+// Bound: the round trips of one workgroup's loads.  Partials were rows that went through LDS, their maxima were looked up in two
+// passes before the values were asked for, and the die's L2 was invalidated first, which emptied it for the die's other workgroups as
+// well; a workgroup that merged was held up for 15 to 20 us.  5 heads x 666 queries, two layers 49.7 -> 40.3 us, one layer at 18
+// frames 547 -> 524, 57 frames x eight layers 5510 -> 5365, one-frame chunks 1085 -> 1054, head_dim 64 474 -> 460 (without merging
+// at all, results wrong: 39.4, 510, 5265, 1018, 453).
+// quads FIRST .. FIRST + NV - 1 of the thread's share
+template <int D, int BQ, int NT, int FIRST, int NV>
+__device__ __forceinline__ void attn_park(const AttnParams &P, const PfWorkItem &it, const f32x4 (&v)[NV], int tid) {
+  static_assert((FIRST + NV) * NT * 4 <= BQ * D, "a thread's share");
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)attn_partial<D, BQ>(P, it, it.seg), 0, BQ * D * 4, 0x00020000u);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[i]), r, tid * 16, (FIRST + i) * NT * 16, ATT_DEVICE_SCOPE);
+}
+// reference maximum and row sum of query row r
+template <int D, int BQ>
+__device__ __forceinline__ void attn_park_row(const AttnParams &P, const PfWorkItem &it, int r, float m, float l) {
+  float *pm = attn_partial<D, BQ>(P, it, it.seg) + (size_t)BQ * D;
+  st_dev1(pm + r, m);
+  st_dev1(pm + BQ + r, l);
+}
+// The workgroup has parked its result; is it the last of its (head, query tile)?
+__device__ __forceinline__ bool attn_arrive(const AttnParams &P, const PfWorkItem &it, int32_t *sFlagp, int tid) {
   __builtin_amdgcn_s_waitcnt(0);             // this wave's partial stores have completed
 #if PF_STRICT_FENCES
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // the memory model's own publication: release before the arrival
@@ -383,69 +397,60 @@ __device__ __forceinline__ void attn_arrive_and_merge(const AttnParams &P, const
     if (*sFlagp) P.counters[it.group] = 0;     // ready for the next launch on this index
   }
   __syncthreads();
-  if (!*sFlagp) return;
-
-  // ---- merge.  The other segments' stores went through to memory before their arrival was counted; what
-  // this die's L2 may still hold of these addresses is older (the workspace is reused by every launch), so
-  // the L2 copies are dropped first (acquire at device scope: an invalidate, no write-back) and the partials
-  // are then read with ordinary wide loads.
-  // Phase A: per query row, the maximum M over the segments' reference maxima and the total denominator
-  // L = sum_s 2^((m_s-M)c) l_s.  Phase B: out = sum_s 2^((m_s-M)c) O_s / L. ----
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  const bool last = *sFlagp != 0;
+#if PF_STRICT_FENCES
+  if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+#endif
+  return last;
+}
+// Sum of all segments' partials: v = sum_s 2^((m_s-M)c) O_s and l = sum_s 2^((m_s-M)c) l_s of query row `row`, with M the largest of
+// its reference maxima m_s; added in the order of the segments, whoever arrived last.  v: quads FIRST .. FIRST + NV - 1 of the
+// thread's share, which all belong to that row.  The other segments' stores went through to memory before their arrival was counted;
+// what this die's L2 may still hold of these addresses is older (the workspace is reused by every launch), so they are read at
+// device scope (past the L2), 16 bytes at a time and two segments' worth in flight (with the first two asked for before the maxima are
+// known, the kernel's registers no longer suffice).
+template <int D, int BQ, int NT, int FIRST, int NV>
+__device__ __forceinline__ void attn_merge(const AttnParams &P, const PfWorkItem &it, f32x4 (&v)[NV], int row, float &l, int tid) {
+  const float c = P.scale_log2;
   const float *base = attn_partial<D, BQ>(P, it, 0);
   const size_t seg_stride = (size_t)P.n_qt * ((size_t)BQ * (D + 2));
+  constexpr int SLOT_BYTES = BQ * (D + 2) * 4, M_OFF = BQ * D * 4, L_OFF = BQ * (D + 1) * 4;
   const int nseg = it.nseg;
-  for (int r = tid; r < BQ; r += NT) {
-    const float *pm = base + (size_t)BQ * D + r;
-    float mmax = -3.0e38f;
-#pragma unroll 8
-    for (int sgi = 0; sgi < nseg; ++sgi) mmax = fmaxf(mmax, pm[sgi * seg_stride]);
-    float lsum = 0.0f;
-#pragma unroll 8
-    for (int sgi = 0; sgi < nseg; ++sgi) lsum += fast_exp2((pm[sgi * seg_stride] - mmax) * c) * pm[sgi * seg_stride + BQ];
-    sM[r] = mmax;
-    sInvL[r] = 1.0f / lsum;
+  auto at = [&](int sgi) { return __builtin_amdgcn_make_buffer_rsrc((void *)(base + sgi * seg_stride), 0, SLOT_BYTES, 0x00020000u); };
+  float mmax = -3.0e38f;
+  for (int s0 = 0; s0 < nseg; s0 += 8) {                       // eight in flight (the last one again once they run out)
+    float m[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      m[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(at(pf_min(s0 + k, nseg - 1)), row * 4, M_OFF, ATT_DEVICE_SCOPE));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) mmax = fmaxf(mmax, m[k]);
   }
-  __syncthreads();
-  // 8-channel output groups per thread in flight
-  constexpr int EG = BQ * (D / 8) >= 4 * NT ? 4 : 1, NE = BQ * (D / 8);
-  static_assert(NE % (NT * EG) == 0 || NE < NT, "merge tiling");
-  for (int e0 = tid; e0 < NE; e0 += NT * EG) {
-    int r[EG], d0[EG];
-    float mrow[EG];
-    float4 acc[EG][2];
+  l = 0.0f;
 #pragma unroll
-    for (int k = 0; k < EG; ++k) {
-      const int e = e0 + k * NT;
-      r[k] = e / (D / 8);
-      d0[k] = (e % (D / 8)) * 8;
-      mrow[k] = sM[r[k]];
-      acc[k][0] = acc[k][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int i = 0; i < NV; ++i) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < nseg; s0 += 2) {
+    float m[2], ls[2];
+    f32x4 x[2][NV];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const __amdgpu_buffer_rsrc_t r = at(pf_min(s0 + k, nseg - 1));
+      m[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, row * 4, M_OFF, ATT_DEVICE_SCOPE));
+      ls[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, row * 4, L_OFF, ATT_DEVICE_SCOPE));
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        x[k][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, tid * 16, (FIRST + i) * NT * 16, ATT_DEVICE_SCOPE));
     }
-#pragma unroll 2
-    for (int sgi = 0; sgi < nseg; ++sgi) {
-      const float *ps = base + sgi * seg_stride;
 #pragma unroll
-      for (int k = 0; k < EG; ++k) {
-        const float w = fast_exp2((ps[(size_t)BQ * D + r[k]] - mrow[k]) * c);
-        const float4 va = *(const float4 *)(ps + (size_t)r[k] * D + d0[k]);
-        const float4 vb = *(const float4 *)(ps + (size_t)r[k] * D + d0[k] + 4);
-        acc[k][0].x += w * va.x; acc[k][0].y += w * va.y; acc[k][0].z += w * va.z; acc[k][0].w += w * va.w;
-        acc[k][1].x += w * vb.x; acc[k][1].y += w * vb.y; acc[k][1].z += w * vb.z; acc[k][1].w += w * vb.w;
+    for (int k = 0; k < 2; ++k)
+      if (s0 + k < nseg) {                                     // uniform
+        const float w = fast_exp2((m[k] - mmax) * c);
+        l += w * ls[k];
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[i][e] += w * x[k][i][e];
       }
-    }
-#pragma unroll
-    for (int k = 0; k < EG; ++k) {
-      const int row = it.q0 + r[k];
-      if (row >= P.q_tokens) continue;
-      const float inv = sInvL[r[k]];
-      bf16x8 w;
-      w[0] = (__bf16)(acc[k][0].x * inv); w[1] = (__bf16)(acc[k][0].y * inv);
-      w[2] = (__bf16)(acc[k][0].z * inv); w[3] = (__bf16)(acc[k][0].w * inv);
-      w[4] = (__bf16)(acc[k][1].x * inv); w[5] = (__bf16)(acc[k][1].y * inv);
-      w[6] = (__bf16)(acc[k][1].z * inv); w[7] = (__bf16)(acc[k][1].w * inv);
-      *(bf16x8 *)(oh + (size_t)row * P.tok_stride + d0[k]) = w;
-    }
   }
 }
 
@@ -455,56 +460,55 @@ __device__ __forceinline__ void attn_epilogue(const AttnParams &P, const PfWorkI
                                               int tid) {
   constexpr int BQ = NWAVES * 32 * NQB;
   constexpr int NT = NWAVES * 64;
-  constexpr int NDB = D / 32;
+  constexpr int NQ = D / 8;                        // quads of a query block
   constexpr int LD = D + 4;                        // row stride of the staged tile: 16-byte writes of 16 rows hit all banks
   const int lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, g = lane >> 5;
   const int h = pf_item_head(it);
   float *sO = sStage;                              // [BQ][LD]
-  float *sM = sStage + BQ * LD, *sL = sM + BQ;     // [BQ] each
+  float *sL = sStage + BQ * LD;                    // [BQ]
 
-  // ---- accumulators -> LDS rows ----
+  // quad 4 db + i4 of query block qb: channels 32 db + 8 i4 + 4 g .. + 3 of the lane's row
+  auto quads = [&](int qb, f32x4 (&v)[NQ]) __attribute__((always_inline)) {
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    const int lrow_q = (wave * NQB + qb) * 32 + l32;
-    const float lsum = partner_sum(l_run[qb]);
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4)
-        *(float4 *)(sO + lrow_q * LD + db * 32 + 8 * i4 + 4 * g) =
-            make_float4(o[qb][db][i4 * 4], o[qb][db][i4 * 4 + 1], o[qb][db][i4 * 4 + 2], o[qb][db][i4 * 4 + 3]);
-    if (g == 0) { sM[lrow_q] = m_run[qb]; sL[lrow_q] = lsum; }
+    for (int i = 0; i < NQ; ++i) v[i] = f32x4{o[qb][i / 4][i % 4 * 4], o[qb][i / 4][i % 4 * 4 + 1], o[qb][i / 4][i % 4 * 4 + 2], o[qb][i / 4][i % 4 * 4 + 3]};
+  };
+  if (it.nseg > 1) {
+    static_for<0, NQB>([&](auto b) __attribute__((always_inline)) {
+      constexpr int qb = decltype(b)::value;
+      f32x4 v[NQ];
+      quads(qb, v);
+      attn_park<D, BQ, NT, qb * NQ>(P, it, v, tid);
+      const float lsum = partner_sum(l_run[qb]);
+      if (g == 0) attn_park_row<D, BQ>(P, it, (wave * NQB + qb) * 32 + l32, m_run[qb], lsum);
+    });
+    if (!attn_arrive(P, it, sFlagp, tid)) return;
   }
+  // ---- values -> LDS rows -> normalised output ----
+  static_for<0, NQB>([&](auto b) __attribute__((always_inline)) {
+    constexpr int qb = decltype(b)::value;
+    const int row = (wave * NQB + qb) * 32 + l32;
+    f32x4 v[NQ];
+    float lsum = partner_sum(l_run[qb]);
+    quads(qb, v);
+    if (it.nseg > 1) attn_merge<D, BQ, NT, qb * NQ>(P, it, v, row, lsum, tid);
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) *(f32x4 *)(sO + row * LD + i / 4 * 32 + 8 * (i % 4) + 4 * g) = v[i];
+    if (g == 0) sL[row] = lsum;
+  });
   __syncthreads();
-
   __bf16 *oh = P.out + (size_t)h * P.head_stride;
-  if (it.nseg == 1) {
-    for (int e = tid; e < BQ * (D / 8); e += NT) {
-      const int r = e / (D / 8), d0 = (e % (D / 8)) * 8;
-      const int row = it.q0 + r;
-      if (row >= P.q_tokens) continue;
-      const float inv = 1.0f / sL[r];
-      const float4 a = *(const float4 *)(sO + r * LD + d0), b = *(const float4 *)(sO + r * LD + d0 + 4);
-      bf16x8 w;
-      w[0] = (__bf16)(a.x * inv); w[1] = (__bf16)(a.y * inv); w[2] = (__bf16)(a.z * inv); w[3] = (__bf16)(a.w * inv);
-      w[4] = (__bf16)(b.x * inv); w[5] = (__bf16)(b.y * inv); w[6] = (__bf16)(b.z * inv); w[7] = (__bf16)(b.w * inv);
-      *(bf16x8 *)(oh + (size_t)row * P.tok_stride + d0) = w;
-    }
-    return;
+  for (int e = tid; e < BQ * (D / 8); e += NT) {
+    const int r = e / (D / 8), d0 = (e % (D / 8)) * 8;
+    const int q = it.q0 + r;
+    if (q >= P.q_tokens) continue;
+    const float inv = 1.0f / sL[r];
+    const float4 a = *(const float4 *)(sO + r * LD + d0), b = *(const float4 *)(sO + r * LD + d0 + 4);
+    bf16x8 w;
+    w[0] = (__bf16)(a.x * inv); w[1] = (__bf16)(a.y * inv); w[2] = (__bf16)(a.z * inv); w[3] = (__bf16)(a.w * inv);
+    w[4] = (__bf16)(b.x * inv); w[5] = (__bf16)(b.y * inv); w[6] = (__bf16)(b.z * inv); w[7] = (__bf16)(b.w * inv);
+    *(bf16x8 *)(oh + (size_t)q * P.tok_stride + d0) = w;
   }
-
-  // ---- split head: park the unnormalised partial (O, m, l), the last segment to arrive merges ----
-  {
-    float *po = attn_partial<D, BQ>(P, it, it.seg);
-    float *pm = po + (size_t)BQ * D;                // m[BQ] then l[BQ]
-    for (int e = tid; e < BQ * (D / 4); e += NT) {
-      const int r = e / (D / 4), d0 = (e % (D / 4)) * 4;
-      st_dev4(po + (size_t)r * D + d0, *(const f32x4 *)(sO + r * LD + d0));
-    }
-    for (int e = tid; e < 2 * BQ; e += NT) st_dev1(pm + e, sM[e]);      // sM and sL are adjacent
-  }
-  attn_arrive_and_merge<D, BQ, NT>(P, it, sM, sL, sFlagp, tid);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -1312,10 +1316,12 @@ __global__ __launch_bounds__(NW * 64, NW == 8 ? 2 : 1) void pf_attn_pp_kernel(At
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __builtin_amdgcn_s_barrier();
 
-    f32x16 sA[2], sB[2];                                       // S^T of a half tile, per query block
-    bf16x8 pA[2][2], pB[2][2];                                 // P^T of a half tile: [query block][16-key chunk]
-    u32x2 vl[16], vh[16];
-    u32x4 kf[16];
+    f32x16 sA[2] = {}, sB[2] = {};                             // S^T of a half tile, per query block
+    bf16x8 pA[2][2] = {}, pB[2][2];                                 // P^T of a half tile: [query block][16-key chunk]
+    // Nothing of an earlier item is left in the fragments' registers: undefined, the compiler would keep their old contents
+    // from item to item, through the epilogue, in accumulation registers
+    u32x2 vl[16] = {}, vh[16] = {};
+    u32x4 kf[16] = {};
     float alpha[2] = {1.0f, 1.0f};
     bool pending = false;                                      // the accumulators still have to be multiplied by alpha
     // running state per query block: reference maximum m_run, m_run + lazy margin, m_run * scale, and the row sum in two

@@ -293,25 +293,24 @@ __device__ __forceinline__ void thin_item(const AttnParams &P, const PfWorkItem 
 #pragma unroll
     for (int i = 0; i < VPT; ++i) acc[i] += f * sO[(w * 32 + r) * C::LD + d0 + i];
   }
-  if (it.nseg == 1) {
-    const float inv = 1.0f / lsum;
-    typedef __attribute__((ext_vector_type(VPT))) __bf16 out_t;
-    out_t w;
+  if (it.nseg > 1) {
+    constexpr int BQ = 32, NT = THIN_WAVES * 64, NV = VPT / 4;
+    f32x4 v[NV];
 #pragma unroll
-    for (int i = 0; i < VPT; ++i) w[i] = (__bf16)(acc[i] * inv);
-    if (it.q0 + r < P.q_tokens) *(out_t *)(P.out + (size_t)pf_item_head(it) * P.head_stride + (size_t)(it.q0 + r) * P.tok_stride + d0) = w;
-  } else {
-    constexpr int BQ = 32;
-    float *po = attn_partial<D, BQ>(P, it, it.seg);
+    for (int i = 0; i < VPT; ++i) v[i / 4][i % 4] = acc[i];
+    attn_park<D, BQ, NT, 0>(P, it, v, tid);
+    if (d0 == 0) attn_park_row<D, BQ>(P, it, r, mmax, lsum);
+    if (!attn_arrive(P, it, sFlagp, tid)) return;
+    attn_merge<D, BQ, NT, 0>(P, it, v, r, lsum, tid);
 #pragma unroll
-    for (int i = 0; i < VPT; i += 4) st_dev4(po + (size_t)r * D + d0 + i, f32x4{acc[i], acc[i + 1], acc[i + 2], acc[i + 3]});
-    if (d0 == 0) {
-      st_dev1(po + BQ * D + r, mmax);
-      st_dev1(po + BQ * (D + 1) + r, lsum);
-    }
-    __syncthreads();                                               // the staged results have been read
-    attn_arrive_and_merge<D, BQ, THIN_WAVES * 64>(P, it, sM, sL, sFlagp, tid);
+    for (int i = 0; i < VPT; ++i) acc[i] = v[i / 4][i % 4];
   }
+  const float inv = 1.0f / lsum;
+  typedef __attribute__((ext_vector_type(VPT))) __bf16 out_t;
+  out_t w;
+#pragma unroll
+  for (int i = 0; i < VPT; ++i) w[i] = (__bf16)(acc[i] * inv);
+  if (it.q0 + r < P.q_tokens) *(out_t *)(P.out + (size_t)pf_item_head(it) * P.head_stride + (size_t)(it.q0 + r) * P.tok_stride + d0) = w;
 }
 
 #endif  // PF_ATTN_THIN_H
