@@ -1560,8 +1560,10 @@ static int launch_attn(const AttnParams &P, int head_dim, int variant, int n_blo
                        dim3(4 * 64), 0, stream, P);
   else if (head_dim == 128 && variant == 0)
     hipLaunchKernelGGL((pf_attn_kernel<128>), dim3(n_blocks), dim3(ATT_THREADS), 0, stream, P);
+  else if (head_dim == 64 && variant == 0 && P.tpf >= PF_BK)
+    hipLaunchKernelGGL(pf_attn_d64_kernel<true>, dim3(n_blocks), dim3(D64_WAVES * 64), 0, stream, P);
   else if (head_dim == 64 && variant == 0)
-    hipLaunchKernelGGL(pf_attn_d64_kernel, dim3(n_blocks), dim3(D64_WAVES * 64), 0, stream, P);
+    hipLaunchKernelGGL(pf_attn_d64_kernel<false>, dim3(n_blocks), dim3(D64_WAVES * 64), 0, stream, P);
   else
     return PF_ERR_UNSUPPORTED;                      // kernel 1 exists for head_dim 128 only
   return hipGetLastError() == hipSuccess ? PF_OK : PF_ERR_HIP;

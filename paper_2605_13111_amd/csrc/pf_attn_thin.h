@@ -35,57 +35,95 @@ struct Thin {
   static __device__ constexpr int swz_v(int r) { return D == 128 ? (r & 3) << 2 : ((r >> 1) & 1) << 2; }
 };
 
-// The keys of one wave: where the step's rows sit.  A "run" is a stretch of keys whose rows are a fixed stride apart: the
-// rest of a history frame, or the chunk.
+// The keys of one wave: where the step's rows sit.  A "run" is a stretch of keys whose rows are a fixed stride apart: a history
+// frame, or the chunk.
 struct ThinRun {
   const __bf16 *k, *v;        // row of key t0
   int t0, end;                // keys [t0, end) of the head's sequence
   long long stride;           // elements between rows
+  int j;                      // which frame; n_sel: the chunk
 };
 template <int D>
-__device__ __forceinline__ void thin_locate(ThinRun &R, int t, const HeadKV &H) {
-  R.t0 = t;
-  if (t >= H.hist_tokens) {
-    const long long e = (long long)(t - H.hist_tokens) * H.cur_stride;
-    R.k = H.k_cur + e;
-    R.v = H.v_cur + e;
+__device__ __forceinline__ ThinRun thin_run(int j, int slot, const HeadKV &H) {   // slot: of frame j
+  ThinRun R;
+  R.j = j;
+  if (j >= H.n_sel) {
+    R.t0 = H.hist_tokens;
     R.end = H.lkv;
+    R.k = H.k_cur;
+    R.v = H.v_cur;
     R.stride = H.cur_stride;
   } else {
-    const int j = t / H.tpf;
-    const long long e = ((long long)H.slots[j] * H.tpf + (t - j * H.tpf)) * D;
+    const long long e = (long long)slot * H.tpf * D;
+    R.t0 = j * H.tpf;
+    R.end = R.t0 + H.tpf;
     R.k = H.k_pool + e;
     R.v = H.v_pool + e;
-    R.end = (j + 1) * H.tpf;
     R.stride = D;
+  }
+  return R;
+}
+// The run that key t lies in, and the slot of the frame after it, which is read a run ahead where frames are long, so that it is there
+// when a step crosses the border; shorter ones may be stepped over, and there it is looked up where it is wanted.
+constexpr int THIN_AHEAD = PF_BK;
+struct ThinRuns {
+  ThinRun at;
+  int next_slot;
+};
+template <int D>
+__device__ __forceinline__ int thin_next_slot(int j, const HeadKV &H) {
+  return j + 1 < H.n_sel ? H.slots[j + 1] : 0;
+}
+template <int D, bool LONG = true>                               // LONG: frames may be long
+__device__ __forceinline__ void thin_locate(ThinRuns &R, int t, const HeadKV &H) {
+  const int j = t >= H.hist_tokens ? H.n_sel : __builtin_amdgcn_readfirstlane(t / H.tpf);
+  const int slot = j < H.n_sel ? H.slots[j] : 0;
+  if (LONG && H.tpf >= THIN_AHEAD) R.next_slot = thin_next_slot<D>(j, H);
+  R.at = thin_run<D>(j, slot, H);
+}
+template <int D>
+__device__ __forceinline__ void thin_follow(ThinRuns &R, int t, const HeadKV &H) {
+  if (__builtin_expect(t < R.at.end || R.at.j >= H.n_sel, 1)) return;
+  if (H.tpf >= THIN_AHEAD) {                                     // no frame is stepped over
+    const int slot = R.next_slot;
+    R.next_slot = thin_next_slot<D>(R.at.j + 1, H);
+    R.at = thin_run<D>(R.at.j + 1, slot, H);
+  } else {
+    thin_locate<D>(R, t, H);
   }
 }
 
-// Send the copies of one tensor's rows t .. t+ROWS-1 into `dst` (a place whose row number in its tile
-// is a multiple of 16, the period of the chunk permutations; ROWS / Thin<D>::COPY_ROWS instructions whichever way).
-template <int D, bool IS_V, int ROWS = THIN_KEYS>
-__device__ __forceinline__ void thin_copy(const ThinRun &R, int t, const HeadKV &H, char *dst, int lane) {
+// Send the copies of one tensor's rows t .. t+ROWS-1, the first of them in R.at (or beyond the sequence), into `dst` (a place whose row
+// number in its tile is a multiple of 16, the period of the chunk permutations; ROWS / Thin<D>::COPY_ROWS instructions whichever way).
+// thin_copy_border is for rows that do not all lie in R.at: a step that crosses a border takes its rows from R.at and the run after it by a
+// select per lane.  Where every lane looked its row up for itself (a division, a slot from memory, the address), the waves with such
+// steps held their workgroup up by 5 us: 5 heads x 666 queries at 333 tokens per frame, two layers 40.8 -> 36.6 us, 20 heads x 400
+// queries at 200 102 -> 83, 12 heads x 48 at 48 32 -> 23; head_dim 64, 5 heads x 4680 queries without history 84 -> 78.
+template <int D, bool IS_V, int ROWS = THIN_KEYS, bool LONG = true>
+__device__ __forceinline__ void thin_copy_border(ThinRuns &Rs, int t, const HeadKV &H, char *dst, int lane) {
   typedef Thin<D> C;
   constexpr int NC = ROWS / C::COPY_ROWS;
   typedef const __attribute__((address_space(1))) void *gptr_t;
   typedef __attribute__((address_space(3))) void *lptr_t;
-  const int rr = lane / C::CHUNKS, p = lane % C::CHUNKS;
-  if (__builtin_expect(t + ROWS <= R.end, 1)) {                  // whole step inside the run: scalar base, per-lane offset
-    const long long e = (long long)(t - R.t0) * R.stride;
-    const unsigned row_b = (unsigned)(R.stride * 2);
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)((IS_V ? R.v : R.k) + e), 0, (int)(ROWS * row_b), 0x00020000u);
-    const unsigned low = (unsigned)((p ^ (IS_V ? C::swz_v(rr) : C::swz_k(rr))) << 4);
-    static_for<0, NC>([&](auto gi) {
-      constexpr int G = decltype(gi)::value;
-      constexpr unsigned flip = (unsigned)((IS_V ? C::swz_v(G * C::COPY_ROWS) : C::swz_k(G * C::COPY_ROWS)) << 4);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)(dst + G * 1024), 16, (low ^ flip) + (unsigned)rr * row_b, G * C::COPY_ROWS * row_b, 0, 0);
-    });
-    return;
-  }
-  // frame border inside the step, or the sequence's ragged end (rows past it repeat the last key): every lane finds its row.
-  // Rare: its per-lane values are worked out here, not held in registers through the loop
+  const ThinRun &R = Rs.at;
+  // Rare: per-lane values are worked out here, not held in registers through the loop
   int lane_l = lane;
   asm volatile("" : "+v"(lane_l));
+  if (__builtin_expect(H.tpf >= ROWS || R.j >= H.n_sel, 1)) {    // one border at most; rows past the sequence's end repeat the last key
+    const ThinRun N = thin_run<D>(R.j + 1, LONG && H.tpf >= THIN_AHEAD ? Rs.next_slot : thin_next_slot<D>(R.j, H), H);
+#pragma unroll 2
+    for (int G = 0; G < NC; ++G) {
+      const int row = G * C::COPY_ROWS + lane_l / C::CHUNKS;
+      const int tt = pf_min(t + row, H.lkv - 1);
+      const bool over = tt >= R.end;
+      const char *b = (const char *)(over ? (IS_V ? N.v : N.k) : (IS_V ? R.v : R.k));
+      const long long off = (long long)(tt - (over ? N.t0 : R.t0)) * (over ? (int)N.stride : (int)R.stride) * 2;
+      const int c = (lane_l % C::CHUNKS) ^ (IS_V ? C::swz_v(row) : C::swz_k(row));
+      __builtin_amdgcn_global_load_lds((gptr_t)(b + off + c * 16), (lptr_t)(dst + G * 1024), 16, 0, 0);
+    }
+    return;
+  }
+  // frames shorter than a step: every lane finds its row
   for (int G = 0; G < NC; ++G) {
     const int row = G * C::COPY_ROWS + lane_l / C::CHUNKS;
     const int tt = pf_min(t + row, H.lkv - 1);
@@ -97,6 +135,28 @@ __device__ __forceinline__ void thin_copy(const ThinRun &R, int t, const HeadKV 
     const __bf16 *b = (in_chunk ? (IS_V ? H.v_cur : H.k_cur) : (IS_V ? H.v_pool : H.k_pool)) + e;
     const int c = (lane_l % C::CHUNKS) ^ (IS_V ? C::swz_v(row) : C::swz_k(row));
     __builtin_amdgcn_global_load_lds((gptr_t)((const char *)b + c * 16), (lptr_t)(dst + G * 1024), 16, 0, 0);
+  }
+}
+
+template <int D, bool IS_V, int ROWS = THIN_KEYS, bool LONG = true>
+__device__ __forceinline__ void thin_copy(ThinRuns &Rs, int t, const HeadKV &H, char *dst, int lane) {
+  typedef Thin<D> C;
+  constexpr int NC = ROWS / C::COPY_ROWS;
+  typedef __attribute__((address_space(3))) void *lptr_t;
+  const ThinRun &R = Rs.at;
+  const int rr = lane / C::CHUNKS, p = lane % C::CHUNKS;
+  if (__builtin_expect(t + ROWS <= R.end, 1)) {                  // whole step inside the run: scalar base, per-lane offset
+    const long long e = (long long)(t - R.t0) * R.stride;
+    const unsigned row_b = (unsigned)(R.stride * 2);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)((IS_V ? R.v : R.k) + e), 0, (int)(ROWS * row_b), 0x00020000u);
+    const unsigned low = (unsigned)((p ^ (IS_V ? C::swz_v(rr) : C::swz_k(rr))) << 4);
+    static_for<0, NC>([&](auto gi) {
+      constexpr int G = decltype(gi)::value;
+      constexpr unsigned flip = (unsigned)((IS_V ? C::swz_v(G * C::COPY_ROWS) : C::swz_k(G * C::COPY_ROWS)) << 4);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lptr_t)(dst + G * 1024), 16, (low ^ flip) + (unsigned)rr * row_b, G * C::COPY_ROWS * row_b, 0, 0);
+    });
+  } else {
+    thin_copy_border<D, IS_V, ROWS, LONG>(Rs, t, H, dst, lane);
   }
 }
 
@@ -132,7 +192,7 @@ __device__ __forceinline__ void thin_keys(const AttnParams &P, const PfWorkItem 
   const int l32 = lane & 31, g = lane >> 5;
   const float c = P.scale_log2;
   char *memK = mem, *memV = mem + C::TENSOR_BYTES;
-  ThinRun R;
+  ThinRuns R;
   thin_locate<D>(R, ta, H);
   thin_copy<D, false>(R, ta, H, memK, lane);
   thin_copy<D, true>(R, ta, H, memV, lane);
@@ -177,7 +237,7 @@ __device__ __forceinline__ void thin_keys(const AttnParams &P, const PfWorkItem 
     });
     __builtin_amdgcn_sched_barrier(0);
     if (more) {                                                  // K's place is free: its fragments are in registers
-      if (t + THIN_KEYS >= R.end) thin_locate<D>(R, t + THIN_KEYS, H);
+      thin_follow<D>(R, t + THIN_KEYS, H);
       thin_copy<D, false>(R, t + THIN_KEYS, H, memK, lane);
     }
     const int valid = H.lkv - t;                                 // ragged end of the head's sequence
