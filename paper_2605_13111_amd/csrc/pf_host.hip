@@ -111,7 +111,12 @@ struct PlanCosts {
   double block, split, merge;                       // per block; per parked partial; per partial read back by the merging block
 };
 static const PlanCosts kCostsDirect = {8.0, 2.0, 2.0};
-static const PlanCosts kCostsQueue = {4.0, 2.0, 3.0};
+static const PlanCosts kCostsQueue = {4.0, 1.0, 2.0};
+// Charged 2 and 3, as before partial results were parked in the order the threads hold them and read back without emptying an L2, heads
+// were cut too coarsely (12 heads x 1560 queries x up to 514 tiles, six layers: 245 blocks a layer, 1031 us; now up to 343, 993).
+// 1 and 1 or 2 and 1 cut too finely (8 heads x 1560 queries, 45 frames: 419 -> 431 us; with 1 and 2 419).  The former
+// charges still say which launches are cut at all.
+static const PlanCosts kCostsQueueCut = {4.0, 2.0, 3.0};
 static const PlanCosts kCostsD64 = {2.0, 0.7, 0.7};  // a tile takes four times as long where four workgroups share a compute unit
 // A thin block (32 query rows, pf_attn_thin.h): its share of a full block's time per key tile, its fixed cost, and what parking a
 // partial result adds to it.  A full block's time shared by its eight groups of 32 rows would be 0.125, but a thin block streams all
@@ -123,9 +128,9 @@ static const PlanCosts kCostsD64 = {2.0, 0.7, 0.7};  // a tile takes four times 
 // block (7 heads x 1380 queries x up to 54 tiles: 65 us as 704 thin blocks in halves, 55 us as full ones).
 static const double kThinTile = 0.30, kThinBlock = 5.5, kThinPark = 4.0;
 // ... must finish this much earlier than full ones by the replay, which is good to about a tenth; and what kCostsQueue.merge, fitted to
-// launches of two to four segments a head, charges too much for one with many: 20 segments are replayed at 122 tiles and take 86
-// (2 heads x 1192 queries x 1118 tiles), 10 at 81 and take 61, 5 at 66 and take 61.
-static const double kThinGain = 0.9, kMergeOver = 2.0;
+// launches of two to four segments a head, charges too much for one with many: at 3 per partial, 20 segments were replayed at 122
+// tiles and took 86 (2 heads x 1192 queries x 1118 tiles), 10 at 81 and took 61, 5 at 66 and took 61.
+static const double kThinGain = 0.9, kMergeOver = 1.0;
 constexpr int PF_PLAN_ROUNDS = 3;
 constexpr int PF_PLAN_MAX_NSEG = 16;                // segment counts tried per head in step 2
 constexpr double PF_PLAN_MIN_GAIN = 0.01;           // step 2 must beat step 1 by this much to be used
@@ -134,7 +139,7 @@ constexpr size_t PF_PLAN_CACHE = 16384;            // remembered plans (about 30
 // Blocks of a launch: n_qt query tiles per (head, segment).
 struct LaunchShape {
   int n_qt, slots_per_die, min_seg;
-  bool thin, queue, d64;
+  bool thin, queue, d64, cut;                        // cut: replayed only to see which launches are cut
 };
 static LaunchShape launch_shape(int variant, int head_dim, int q_tokens, bool queue) {
   LaunchShape S;
@@ -144,16 +149,17 @@ static LaunchShape launch_shape(int variant, int head_dim, int q_tokens, bool qu
   S.thin = variant == PF_THIN_VARIANT;
   S.queue = queue;
   S.d64 = head_dim == 64;
+  S.cut = false;
   S.min_seg = PF_AUTO_MIN_SEG;
   return S;
 }
 
 // Finish time of the launch in which head h has key tiles n_kvt[h] cut into segments of at most seg[h] tiles; of one that takes at
-// least `bound`, maybe only that much of it is known (the dies of the form without a queue are replayed one after another, and
-// most cuts lose on the first: a head_dim 64 plan takes 0.30 ms on average, whole replays 0.71).
+// least `bound`, maybe only that much of it is known (a plan takes 1.0 ms on average at head_dim 128 and 0.23 at 64, with whole replays
+// 1.8 and 0.71).
 static double model_finish(const std::vector<int> &n_kvt, const std::vector<int> &seg, const LaunchShape &S, double bound) {
   typedef std::priority_queue<double, std::vector<double>, std::greater<double> > MinHeap;
-  const PlanCosts &C = S.d64 ? kCostsD64 : S.queue ? kCostsQueue : kCostsDirect;
+  const PlanCosts &C = S.d64 ? kCostsD64 : !S.queue ? kCostsDirect : S.cut ? kCostsQueueCut : kCostsQueue;
   const int H = (int)n_kvt.size();
   // heads by descending segment length (ties: head id), as the index kernel ranks them
   std::vector<int> order(H), nsegs(H), len(H);
@@ -177,6 +183,16 @@ static double model_finish(const std::vector<int> &n_kvt, const std::vector<int>
       teams[xcd].push_back(S.thin ? kThinTile * tiles + kThinBlock + (nseg > 1 ? kThinPark : 0.0) : tiles + C.block + park);
     }
   }
+  // No schedule ends before its work spread evenly would (over a die where dies keep to their lists, over the chip otherwise), and none
+  // gets shorter again: most cuts are seen to lose without a whole replay.
+  double even = 0.0;
+  for (int x = 0; x < PF_NUM_XCD; ++x) {
+    double die = 0.0;
+    for (double t : teams[x]) die += t * S.n_qt;
+    even = S.queue ? even + die / PF_NUM_XCD : die > even ? die : even;
+  }
+  even /= S.slots_per_die;
+  if (even * (1.0 - 1e-9) >= bound) return even;
   double finish = 0.0;
   if (!S.queue) {
     for (int x = 0; x < PF_NUM_XCD; ++x) {
@@ -187,8 +203,8 @@ static double model_finish(const std::vector<int> &n_kvt, const std::vector<int>
         cu.pop();
         cu.push(e);
         finish = e > finish ? e : finish;
+        if (finish >= bound) return finish;
       }
-      if (finish >= bound) break;
     }
     return finish;
   }
@@ -206,6 +222,7 @@ static double model_finish(const std::vector<int> &n_kvt, const std::vector<int>
         const double e = w.first + teams[x][next[x] / S.n_qt];
         ++next[x];
         finish = e > finish ? e : finish;
+        if (finish >= bound) return finish;
         workers.push(Worker(e, w.second));
         break;
       }
@@ -341,26 +358,35 @@ int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
   const std::vector<int> n_kvt(key.begin(), key.begin() + H);
   Remembered R;
   R.variant = variant;
-  const double finish = plan_segments(n_kvt, S, uniform_only, plan);
+  double finish = plan_segments(n_kvt, S, uniform_only, plan);
   // A launch whose heads fit one segment each needs no workspace, and callers may rely on that: the forms below are not
   // allowed to bring partial results into it.
   bool splits = plan_splits(n_kvt, *plan);
-  if (splits && S.d64) {
-    // Callers may also rely on which launches do without scratch memory, or with the library's own array.  At head_dim 64 that is
-    // decided by a replay with the rates of two workgroups per compute unit: what it leaves whole stays whole, and what it fits into
-    // the array stays in it, although four workgroups per compute unit would often finish earlier in more, shorter segments
-    // (40 heads x 4680 queries x up to 1463 key tiles: 1480 blocks without partial results, or 16280 with 550 MB of them).
-    LaunchShape pair = S;
-    pair.slots_per_die = 64;
-    pair.d64 = false;
+  if (splits && (S.d64 || queue)) {
+    // Callers may also rely on which launches do without scratch memory, or with the library's own array.  That is decided by a
+    // replay with kCostsQueueCut, at head_dim 64 with the rates of two workgroups per compute unit: what it leaves whole stays whole,
+    // and what it fits into the array stays in it, although more, shorter segments would often finish earlier (head_dim 64, 40
+    // heads x 4680 queries x up to 1463 key tiles: 1480 blocks without partial results, or 16280 with 550 MB of them).
+    LaunchShape before = S;
+    before.cut = true;
+    before.d64 = false;
+    if (S.d64) before.slots_per_die = 64;
+    const size_t slot = pf_partial_bytes(pf_variant_bq(variant), pool->head_dim);
+    const bool over = plan_partials(n_kvt, *plan, S.n_qt) * slot > PF_STATIC_SCRATCH_BYTES;
     PfSegPlan base;
     memset(&base, 0, sizeof(base));
-    plan_segments(n_kvt, pair, uniform_only, &base);
-    const size_t slot = pf_partial_bytes(pf_variant_bq(variant), pool->head_dim);
+    double base_finish = plan_segments(n_kvt, before, true, &base);
+    // step 2 only betters step 1: it leaves a launch cut that step 1 cuts, unless whole heads finish earlier
+    const bool cut_anyway = plan_splits(n_kvt, base) && model_finish(n_kvt, n_kvt, before, INFINITY) >= base_finish;
+    if (!uniform_only && (over || !cut_anyway)) {
+      memset(&base, 0, sizeof(base));
+      base_finish = plan_segments(n_kvt, before, false, &base);
+    }
     splits = plan_splits(n_kvt, base);
-    if (!splits || (plan_partials(n_kvt, base, S.n_qt) * slot <= PF_STATIC_SCRATCH_BYTES &&
-                    plan_partials(n_kvt, *plan, S.n_qt) * slot > PF_STATIC_SCRATCH_BYTES))
+    if (!splits || (over && plan_partials(n_kvt, base, S.n_qt) * slot <= PF_STATIC_SCRATCH_BYTES)) {
       *plan = base;
+      if (!S.d64) finish = base_finish;
+    }
   }
   if (splits && S.d64) {
     LaunchShape fine = S;

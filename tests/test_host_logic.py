@@ -144,6 +144,19 @@ def test_static_scratch_entry_point_rejects_plans_that_do_not_fit():
                                          null) == B.PF_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("heads,policy,T,chunk,tpf,limit", [
+    (4, "veil", 60, 1, 1560, 0), (24, "all", 33, 1, 200, 0), (64, "veil", 27, 3, 500, 0), (2, "wave", 19, 3, 700, 0),
+    (40, "all", 85, 3, 1000, 0), (64, "all", 30, 3, 1560, 0), (80, "all", 54, 2, 500, 160 << 20),
+])
+def test_cheaper_merges_leave_whole_launches_whole_and_array_launches_in_the_array(heads, policy, T, chunk, tpf, limit):
+    """Launches that did without a workspace, or fitted the library's array, although cutting them (finer) would end sooner."""
+    p = {"veil": synth.veil(1, 3), "all": synth.anchor_all(T), "wave": synth.wave(2, T)}[policy]
+    c = _fake_pool([p._replace(slots=max(1, B.slots_needed(p, T)))] * heads, tpf=tpf, D=128)
+    B.pf_set_tuning(attn_variant=-2, seg_tiles=0)
+    _, _, partials = B.pf_plan_segments(c, T, chunk * tpf)
+    assert partials * 256 * (128 + 2) * 4 <= limit
+
+
 def test_chunk_layout_validation_without_a_device():
     """Strided entry points: stride checks happen on the host, before any device access."""
     lib = B.lib()
