@@ -3,6 +3,7 @@ shorter than the rows (several borders inside them), shorter than a tile (frames
 to a chunk of strided rows."""
 import pytest
 
+from paper_2605_13111_amd import binding as B
 from paper_2605_13111_amd import synth
 import gpu_common as G
 
@@ -15,3 +16,17 @@ pytestmark = pytest.mark.gpu
 def test_rows_across_frame_borders(D, tpf, layout):
     pols = [synth.anchor_all(9), synth.anchor_topk(5, 5), synth.wave(2, 9), synth.veil(1, 3)]
     G.run_case(pols, tpf, D, [3, 3, 3], 2 * tpf + 5, seed=500 + tpf, layout=layout, check_every_append=False, label="borders")
+
+
+@pytest.mark.parametrize("layout", ["packed", "model"])
+@pytest.mark.parametrize("variant", [1, 2])
+@pytest.mark.parametrize("tpf,frames,Lq", [(1, 1, 1), (2, 130, 3), (5, 40, 21), (9, 30, 300), (17, 12, 34), (63, 5, 64), (64, 3, 65), (100, 4, 259)])
+def test_full_items_whose_rows_are_found_one_by_one(tpf, frames, Lq, variant, layout):
+    """Full items at frames smaller than a tile and at ragged ends, where every lane finds its own row of the tile: one row in all, frames
+    that divide a wave's rows and its tiles and frames that do not, and the border to a chunk of strided rows inside such a tile."""
+    B.pf_set_tuning(attn_variant=variant)
+    try:
+        pols = [synth.anchor_all(frames), synth.wave(2, frames), synth.veil(1, 3)]
+        G.run_case(pols, tpf, 128, [frames], Lq, seed=900 + tpf, layout=layout, label="rows", variant=variant)
+    finally:
+        B.pf_set_tuning(attn_variant=-2)
