@@ -641,23 +641,32 @@ __global__ __launch_bounds__(CLS_ROUNDS_THREADS) void pf_classify_rounds_kernel(
 // Majority vote over the prompts; equal counts go to the smaller type code.  64 heads per workgroup, one per lane, the
 // prompts dealt to its 16 waves (one thread per head walking all prompts alone took 71 us for 256 prompts).  Bound: the loads' latency;
 // each wave has eight in flight, also where fewer are left (an unrolled loop's remainder goes one by one: 84 prompts x 34 heads of 133
-// frames 19.5 us in all, so 18.8; sixteen in flight 19.6, four 19.0).
+// frames 19.5 us in all, so 18.8; sixteen in flight 19.6, four 19.0), and no more than it has prompts (with eight whatever there is, the
+// vote of 4 prompts took 1.9 us for 1.7, of 17 also 1.9 for 1.6).
 constexpr int CLS_VOTE_WAVES = 16, CLS_VOTE_AHEAD = 8;
 __global__ __launch_bounds__(CLS_VOTE_WAVES * 64) void pf_classify_vote_kernel(const int32_t *prompt_type, int32_t *head_type, int n_prompts, int n_heads) {
   __shared__ int s_votes[CLS_VOTE_WAVES][3][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = blockIdx.x * 64 + lane;
   int votes[3] = {0, 0, 0};
   if (h < n_heads) {
+    unsigned at = (unsigned)wave * n_heads + h;                    // below 2^30 wherever there is a prompt (checked on the host)
 #pragma unroll 1
-    for (int p0 = wave; p0 < n_prompts; p0 += CLS_VOTE_WAVES * CLS_VOTE_AHEAD) {
+    for (int left = n_prompts - wave; left > 0; left -= CLS_VOTE_WAVES * CLS_VOTE_AHEAD) {
       int t[CLS_VOTE_AHEAD];                                       // all in flight, also where fewer are left
 #pragma unroll
-      for (int i = 0; i < CLS_VOTE_AHEAD; ++i) t[i] = prompt_type[(size_t)pf_min(p0 + i * CLS_VOTE_WAVES, n_prompts - 1) * n_heads + h];
+      for (int i = 0; i < CLS_VOTE_AHEAD; ++i) {
+        if (left > i * CLS_VOTE_WAVES) {                           // uniform
+          t[i] = prompt_type[at];
+          at += CLS_VOTE_WAVES * n_heads;
+        }
+      }
 #pragma unroll
       for (int i = 0; i < CLS_VOTE_AHEAD; ++i)
+        if (left > i * CLS_VOTE_WAVES) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) votes[c] += t[i] == c && p0 + i * CLS_VOTE_WAVES < n_prompts ? 1 : 0;
+          for (int c = 0; c < 3; ++c) votes[c] += t[i] == c ? 1 : 0;
+        }
     }
   }
 #pragma unroll

@@ -40,3 +40,13 @@ def test_more_sequences_per_workgroup_than_lds_holds():
     _, types, periods = B.pf_classify_heads(logits)
     _, t, p = B.pf_classify_heads(logits[:16].contiguous())
     assert torch.equal(types, t.repeat(21, 1)) and torch.equal(periods, p.repeat(21, 1))
+
+
+@pytest.mark.parametrize("prompts", [1, 2, 15, 16, 17, 32, 33, 112, 113, 127, 128, 129, 144, 145, 257])
+@pytest.mark.parametrize("heads", [3, 64, 65])
+def test_votes_of_any_number_of_prompts(prompts, heads):
+    """On either side of what one wave counts (every 16th prompt), of its eight loads in flight and of their next turn."""
+    logits, _ = synth.head_logits(prompts, heads, 12, 40 + prompts)
+    head, types, _ = B.pf_classify_heads(logits.to("cuda:0"))
+    want, want_types, _ = OC.classify_heads(logits.numpy())
+    assert (types.cpu().numpy() == want_types).all() and (head.cpu().numpy() == want).all()
