@@ -50,14 +50,21 @@ def check_hidden_registers(listing):
 
 
 def check_scalar_operands(listing):
-    """A buffer copy whose descriptor or scalar offset the compiler holds in vector registers becomes a loop over the
-    lanes' values.  Every such operand of the attention kernels is the same in all lanes, so a loop is time lost, and one
-    that reloads spilled descriptor words inside (seen where two copies under complementary masks had been merged into
-    one with a selected descriptor) reads its second turn's base from the wrong registers.  Raises if the listing has one."""
-    lines = [ln.split(";")[0].strip() for ln in listing.split("\n")]
-    for a, b in zip(lines, lines[1:]):
-        if a.startswith("buffer_load") and b.startswith("s_xor_b64 exec, exec"):
-            raise RuntimeError("a buffer copy loops over its lanes' operands: " + a)
+    """A buffer copy or store whose descriptor or scalar offset the compiler holds in vector registers becomes a loop over
+    the lanes' values.  Every such operand of the attention kernels is the same in all lanes, so a loop is time lost, and
+    one that reloads spilled descriptor words inside (seen where two copies under complementary masks had been merged into
+    one with a selected descriptor) reads its second turn's base from the wrong registers.  The loop takes the lanes that
+    share a value (s_and_saveexec), does the access for them, takes them out (s_xor of the execution mask) and goes round
+    while any are left.  Raises if the listing has one, whatever stands between these."""
+    access = None                                  # buffer access since the execution mask was last saved
+    for ln in listing.split("\n"):
+        st = ln.split(";")[0].strip()
+        if "_saveexec_b64" in st:
+            access = None
+        elif st.startswith(("buffer_load", "buffer_store")):
+            access = access or st
+        elif st.startswith("s_xor_b64 exec, exec") and access:
+            raise RuntimeError("a buffer access loops over its lanes' operands: " + access)
 
 
 def build(verbose=False, extra=()):

@@ -334,6 +334,37 @@ def test_build_refuses_a_buffer_copy_that_loops_over_its_lanes():
         BLD.check_scalar_operands("\n".join(["k:", "\ts_and_saveexec_b64 vcc, vcc", copy, "\ts_xor_b64 exec, exec, vcc", "\ts_endpgm"]))
 
 
+def _lane_loop(access, behind=(), before=()):
+    """A listing with a loop over the lanes' values of an access's operands, in the form the compiler writes it."""
+    return "\n".join(["k:                                ; @k", "\ts_mov_b64 s[0:1], exec", ".LBB0_1:      ; =>This Inner Loop Header: Depth=1",
+                      "\tv_readfirstlane_b32 s8, v2", "\tv_cmp_eq_u32_e32 vcc, s8, v2", "\ts_and_saveexec_b64 vcc, vcc", *before, access, *behind,
+                      "\ts_xor_b64 exec, exec, vcc", "\ts_cbranch_execnz .LBB0_1", "\ts_mov_b64 exec, s[0:1]", "\ts_endpgm"])
+
+
+IMPLICIT = "                                        ; implicit-def: $vgpr2"
+
+
+@pytest.mark.parametrize("access", ["\tbuffer_load_dwordx4 v0, s[4:7], s8 offen lds", "\tbuffer_load_dwordx4 v[4:7], v8, s[4:7], 0 offen sc1",
+                                    "\tbuffer_store_dwordx4 v[2:5], v0, s[4:7], 0 offen sc1"])
+@pytest.mark.parametrize("behind", [[], [IMPLICIT], [IMPLICIT, "", IMPLICIT], ["\tv_mov_b32_e32 v9, v8", "\ts_nop 0"]])
+def test_build_refuses_a_buffer_access_that_loops_over_its_lanes(access, behind):
+    from paper_2605_13111_amd import build as BLD
+    with pytest.raises(RuntimeError):
+        BLD.check_scalar_operands(_lane_loop(access, behind))
+    with pytest.raises(RuntimeError):
+        BLD.check_scalar_operands(_lane_loop(access, behind, before=["\tbuffer_load_dword v9, v1, s[4:7], 0 offen"]))
+
+
+def test_build_takes_buffer_accesses_under_a_mask():
+    from paper_2605_13111_amd import build as BLD
+    copy = "\tbuffer_load_dwordx4 v1, s[4:7], s2 offen lds"
+    BLD.check_scalar_operands(_lane_loop("\tv_add_u32_e32 v0, v1, v2"))           # a loop over lanes without such an access
+    # a branch with an access on either side, in a loop
+    BLD.check_scalar_operands("\n".join([".LBB0_2:", "\ts_and_saveexec_b64 s[2:3], vcc", "\ts_xor_b64 s[2:3], exec, s[2:3]", "\ts_cbranch_execz .LBB0_3", copy,
+                                         ".LBB0_3:", "\ts_or_saveexec_b64 s[2:3], s[2:3]", "\ts_xor_b64 exec, exec, s[2:3]", "\ts_cbranch_execz .LBB0_4", copy,
+                                         ".LBB0_4:", "\ts_or_b64 exec, exec, s[2:3]", "\ts_andn2_b64 exec, exec, s[4:5]", "\ts_cbranch_execnz .LBB0_2", "\ts_endpgm"]))
+
+
 def test_stored_counter_summary_belongs_to_this_attention_kernel():
     """bench.py takes roofline.traffic from profiles/pf_attn_pp_kernel_c3_step.md only when that summary was made from
     this very pf_attn.hip (SHA-256 recorded in the summary); a summary of another version makes the field null."""
