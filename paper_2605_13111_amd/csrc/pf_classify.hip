@@ -156,6 +156,7 @@ constexpr int CLS_LDS = 159 * 1024;     // of the 160 KB of a compute unit
 constexpr int CLS_WGS = 256;            // workgroups of a large launch, one per compute unit
 constexpr int CLS_REST = 4;             // bins beyond a multiple of 16 that are not worth a matrix product of their own
 typedef __attribute__((ext_vector_type(4))) double f64x4;
+typedef double __attribute__((may_alias)) amp_t;   // an amplitude in the place of raw values: its accesses are ordered with those of the floats
 
 struct ClassifyBatchParams {
   ClassifyParams c;
@@ -337,7 +338,7 @@ __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(Cl
       total = quarter_sum(total);
       // The raw values of these sequences are in registers now (LDS operations of one wave complete in order), and the amplitudes of
       // bins 1 .. nb go where they were: nb doubles from the first 8-byte border on
-      double *const s_amp = (double *)s_raw - 1;
+      amp_t *const s_amp = (amp_t *)s_raw - 1;
       int at[4];                                                   // of this lane's four results
 #pragma unroll
       for (int r = 0; r < 4; ++r) at[r] = (s_list[pf_min(b0 + lq + 4 * r, listed - 1)] * n + 1) >> 1;
@@ -384,7 +385,7 @@ __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(Cl
       int k = 0;                                                   // lane 16 lq + r writes the result of sequence lq + 4 r
 #pragma unroll 1
       for (int r = 0; r < 4; ++r) {
-        const double *amp = s_amp + ((s_list[pf_min(b0 + lq + 4 * r, listed - 1)] * n + 1) >> 1);
+        const amp_t *amp = s_amp + ((s_list[pf_min(b0 + lq + 4 * r, listed - 1)] * n + 1) >> 1);
         double sc[GROUPS], best = 0.0;
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) {
@@ -658,7 +659,7 @@ __global__ __launch_bounds__(CLS_VOTE_WAVES * 64) void pf_classify_vote_kernel(c
       for (int i = 0; i < CLS_VOTE_AHEAD; ++i) {
         if (left > i * CLS_VOTE_WAVES) {                           // uniform
           t[i] = prompt_type[at];
-          at += CLS_VOTE_WAVES * n_heads;
+          at += (unsigned)CLS_VOTE_WAVES * n_heads;
         }
       }
 #pragma unroll

@@ -1,4 +1,5 @@
 """GPU: the classification kernels give the same types and periods, bit for bit, on either side of the lines between them."""
+import numpy as np
 import pytest
 import torch
 
@@ -50,3 +51,38 @@ def test_votes_of_any_number_of_prompts(prompts, heads):
     head, types, _ = B.pf_classify_heads(logits.to("cuda:0"))
     want, want_types, _ = OC.classify_heads(logits.numpy())
     assert (types.cpu().numpy() == want_types).all() and (head.cpu().numpy() == want).all()
+
+
+def _hand_made(n):
+    t = np.arange(n)
+    n_pos = -(-8 * n // 10)                                      # the fewest positive values that settle a sequence
+    share = lambda k: np.where((t * 7) % n < k, 1.0, -1.0) if n % 7 else np.where((t * 5) % n < k, 1.0, -1.0)   # k of n positive, spread out
+    rows = [share(n_pos), share(n_pos - 1), share(n - n_pos), share(n - n_pos + 1), np.ones(n), np.zeros(n),
+            t - 0.5 * (n - 1), 0.5 * (n - 1) - t, t - 0.5 * (n - 1) + 0.25,        # every difference the same: no spectrum; the mean decides
+            np.where(t % 2 == 0, 1.0, -1.0), np.sin(2 * np.pi * t / 6.0), np.sin(2 * np.pi * t / 20.0) - 0.05,
+            np.sin(2 * np.pi * t / 12.0) + 0.7 * np.sin(2 * np.pi * t / 6.0 + 1.1), np.sin(2 * np.pi * t / 10.0) + np.sin(2 * np.pi * t / 5.0)]
+    if n % 4 == 3:
+        # two jumps half the transform apart, equally far from its ends: all odd bins alike, so the lowest of those with a third harmonic
+        up = (n - 3) // 4
+        rows.append(np.where((t > up) & (t <= n - 2 - up), 0.5, -0.5))
+    wave = np.sin(2 * np.pi * t / 6.0)
+    for bad in (np.nan, np.inf, -np.inf):                        # at an end, in the middle
+        for at in (0, n // 2, n - 1):
+            rows.append(np.where(t == at, bad, wave))
+    return np.stack(rows).astype(np.float32)
+
+
+# the kernel that keeps sequences in LDS at 24 to 72 frames, its neighbours
+@pytest.mark.parametrize("n", [6, 15, 23, 24, 25, 27, 39, 40, 65, 69, 70, 71, 72, 73, 75, 79, 80, 83, 100])
+@pytest.mark.parametrize("first", [0, 5])
+def test_hand_made_sequences(n, first):
+    """Sign rates on and beside their thresholds, flat and empty spectra, tied peaks, infinities and NaN, which must not reach the sequences
+    that are transformed with theirs.  Two prompts: the second one's rows in another order."""
+    rows = np.roll(_hand_made(n), first, axis=0)
+    logits = np.stack([rows, rows[::-1]])
+    with np.errstate(invalid="ignore"):
+        want_head, want_types, want_periods = OC.classify_heads(logits)
+    head, types, periods = B.pf_classify_heads(torch.from_numpy(logits.copy()).to("cuda:0"))
+    assert (types.cpu().numpy() == want_types).all(), np.argwhere(types.cpu().numpy() != want_types)
+    assert (periods.cpu().numpy() == want_periods).all(), np.argwhere(periods.cpu().numpy() != want_periods)
+    assert (head.cpu().numpy() == want_head).all()
