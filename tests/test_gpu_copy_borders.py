@@ -2,6 +2,7 @@
 borders in every way: frames shorter than the rows (several borders inside them), shorter than a tile (frames that a wave steps over),
 barely longer, and the border to a chunk of strided rows."""
 import pytest
+import torch
 
 from paper_2605_13111_amd import binding as B
 from paper_2605_13111_amd import synth
@@ -36,5 +37,38 @@ def test_full_items_whose_rows_are_found_one_by_one(tpf, frames, Lq, variant, la
     try:
         pols = [synth.anchor_all(frames), synth.wave(2, frames), synth.veil(1, 3)]
         G.run_case(pols, tpf, 128, [frames], Lq, seed=900 + tpf, layout=layout, label="rows", variant=variant)
+    finally:
+        B.pf_set_tuning(attn_variant=-2)
+
+
+# bytes between token rows of the chunk: a run of tiles is cut where its 32-bit offsets would pass 2^31, here after two tiles, after one (a
+# power of two, and the widest rows there may be); 2^20: not at all
+@pytest.mark.parametrize("D,variant", [(64, -2), (128, -2), (128, 0), (128, 1), (128, 2)], ids=["d64", "thin", "w4x32", "pp8x32", "w4x64"])
+@pytest.mark.parametrize("stride,Lq", [(1 << 20, 397), (1 << 22, 397), (1 << 23, 203), ((1 << 24) - 8, 139)])
+def test_chunk_rows_far_apart(stride, Lq, D, variant):
+    """The same chunk with its token rows as far apart as the layout may ask for: the packed call's bits."""
+    B.pf_set_tuning(attn_variant=variant)
+    try:
+        H, tpf, frames, dev = 3, 150, 3, "cuda:0"
+        pool = B.Pool([synth.anchor_all(frames), synth.wave(2, frames), synth.veil(1, 1)], tpf, D)
+        B.pf_pool_reset(pool)
+        B.pf_cache_append(pool, *(synth.randn_bf16((H, frames, tpf, D), 70 + i, device=dev) for i in (0, 1)))
+        index = B.Index(pool, Lq)
+        B.pf_build_index(pool, index, Lq)
+        assert index.c.variant == (variant if variant >= 0 else 3 if D == 128 else 0)
+        ws = torch.empty(B.pf_attn_workspace_bytes(pool, Lq), dtype=torch.uint8, device=dev)
+        packed = [synth.randn_bf16((H, Lq, D), 80 + i, device=dev) for i in range(3)]
+        want = torch.full_like(packed[0], float("nan"))
+        B.pf_ragged_attn_fwd(pool, index, *packed, want, ws)
+        # q, k, v and the output share the wide rows
+        rows = torch.empty(Lq * stride, dtype=torch.bfloat16, device=dev)
+        views = [torch.as_strided(rows, (H, Lq, D), (D, stride, 1), i * H * D) for i in range(4)]
+        for t, view in zip(packed + [torch.full_like(want, float("nan"))], views):
+            view.copy_(t)
+        B.pf_ragged_attn_fwd_strided(pool, index, *views, ws)
+        torch.cuda.synchronize()
+        assert torch.isfinite(want.float()).all()
+        assert torch.equal(views[3].contiguous().view(torch.int16), want.view(torch.int16))
+        assert all(torch.equal(view.contiguous().view(torch.int16), t.view(torch.int16)) for t, view in zip(packed, views))
     finally:
         B.pf_set_tuning(attn_variant=-2)

@@ -20,3 +20,15 @@ def test_partial_results_of_many_segments(D, variant, segments):
         G.run_case(pols, 255, D, [frames], 300, seed=60 + segments, seg_tiles=16, label="merge-300", rows=[0, 31, 127, 128, 255, 256, 299])
     finally:
         B.pf_set_tuning(attn_variant=-2)
+
+
+@pytest.mark.parametrize("segments,frames", [(2, 14), (3, 24), (8, 68), (9, 78), (17, 152)])
+def test_partial_results_of_many_thin_segments(segments, frames):
+    """Thin items have a merge of their own shape (32 rows, two quads a thread).  41 and 70 rows: two and three groups of query rows, nine and
+    six of them in the last one."""
+    B.pf_set_tuning(attn_variant=-2)
+    pols = [synth.anchor_all(frames)] * 2
+    for Lq, gain in ((41, 4.0), (70, 1.0)):
+        c = B.Pool(pols, 333, 128).c
+        assert B.pf_plan_segments(c, frames, Lq)[2] == 2 * -(-Lq // 32) * segments
+        G.run_case(pols, 333, 128, [frames], Lq, seed=80 + segments, q_gain=gain, label="thin-merge", rows=[0, 1, 31, 32, Lq - 1], variant=3)
