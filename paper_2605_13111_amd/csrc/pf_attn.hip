@@ -112,10 +112,12 @@ __device__ __forceinline__ float partner_sum(float x) {
 
 // Partial results cross workgroups that may run on different dies, each with its own L2.  They are written
 // with device-scope stores, which go through to the memory side that all dies share; no L2 write-back fence is
-// needed, only the wait for the stores' completion before the arrival counter is bumped (the merging workgroup
-// drops what its own caches hold before it reads).  Building with -DPF_STRICT_FENCES=1 adds the release fence the
-// memory model asks for in front of every arrival (here and in the pool append): the known-correct form, measured
-// against this one.
+// needed, only the wait for the stores' completion before the arrival counter is bumped.  The merging workgroup's caches
+// are NOT invalidated and may hold older contents of these addresses (the workspace is used again by every launch): partials
+// must be read with device-scope loads, which pass them by (attn_merge), never with ordinary ones.  Building with
+// -DPF_STRICT_FENCES=1 adds the release fence and the acquire that the memory model asks for around every arrival (here and in
+// the pool append): the known-correct form, under which the same tests pass and eight layers at 57 frames take 6100 us instead of
+// 5070, one-frame chunks 1213 instead of 948.
 __device__ __forceinline__ void st_dev1(float *p, float a) {
   __hip_atomic_store(p, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -348,7 +350,7 @@ __device__ __forceinline__ void classic_loop(const HeadKV &H, int kt0, int kt1, 
 // access of the epilogue is a full row segment: 16 bytes per lane, consecutive lanes consecutive addresses.
 // sStage: attn_stage_floats(BQ, D) floats of LDS that no wave reads any more (all passed the loop's last barrier).
 // ---------------------------------------------------------------------------------------------------
-constexpr int attn_stage_floats(int bq, int d) { return bq * (d + 4) + 2 * bq; }
+constexpr int attn_stage_floats(int bq, int d) { return bq * (d + 4) + bq; }
 
 constexpr int ATT_DEVICE_SCOPE = 16;         // sc1 of a buffer load or store: written through to, read from the memory all dies share (see st_dev1)
 // A partial result of item `it`: O (BQ * D floats as the threads hold them, see attn_park), m [BQ], l [BQ] of its segment `seg`.
@@ -362,9 +364,9 @@ __device__ __forceinline__ float *attn_partial(const AttnParams &P, const PfWork
 // tile) to arrive adds all of them up, each thread its own values.
 // Bound: the round trips of one workgroup's loads.  Partials were rows that went through LDS, their maxima were looked up in two
 // passes before the values were asked for, and the die's L2 was invalidated first, which emptied it for the die's other workgroups as
-// well; a workgroup that merged was held up for 15 to 20 us.  5 heads x 666 queries, two layers 49.7 -> 40.3 us, one layer at 18
-// frames 547 -> 524, 57 frames x eight layers 5510 -> 5365, one-frame chunks 1085 -> 1054, head_dim 64 474 -> 460 (without merging
-// at all, results wrong: 39.4, 510, 5265, 1018, 453).
+// well; a workgroup that merged was held up for 15 to 20 us.  5 heads x 666 queries, two layers 49.5 -> 40.3 us, one layer at 18
+// frames 544 -> 513, 57 frames x eight layers 5304 -> 5197, one-frame chunks 1059 -> 1018, head_dim 64 457 -> 441 (on a slower board
+// 40.3, 524, 5365, 1054 and 460, and without merging at all, results wrong, 39.4, 510, 5265, 1018 and 453).
 // quads FIRST .. FIRST + NV - 1 of the thread's share
 template <int D, int BQ, int NT, int FIRST, int NV>
 __device__ __forceinline__ void attn_park(const AttnParams &P, const PfWorkItem &it, const f32x4 (&v)[NV], int tid) {
@@ -616,7 +618,7 @@ __global__ __launch_bounds__(ATT_THREADS, 2) void pf_attn_kernel(AttnParams P) {
 // and four taken branches beside 112 vector ones), -> 2536 by the next tile's first fragments requested in the slots of the last
 // MFMAs instead of behind them, -> 2411 by five fragments ahead instead of four and the barrier in front of the last MFMA (two
 // MFMAs behind it: 2410, three at lower priority 2855, four 3135; six fragments ahead 2510; no raised priority 2625; copies
-// after the softmax 2525).  First chunk 288 -> 269 us, 57 frames x eight layers 5530 -> 5390, 40 skewed heads 2249 -> 2174.
+// after the softmax 2525).  First chunk 274 -> 259 us, 57 frames x eight layers 5479 -> 5303, 40 skewed heads 2248 -> 2151.
 // K/V tiles travel global -> LDS three tiles ahead (K ring of 4 stages, V ring of 5: V of a tile is read one
 // phase after its K) with 16-byte copies: one instruction
 // moves four 256-byte rows (lane i -> bytes 16*i of the 1 KB destination), a quarter of the instructions the

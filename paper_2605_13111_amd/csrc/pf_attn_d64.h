@@ -5,8 +5,9 @@
 // cycles of fma, exp2, add and rounding), so what counts is that the four waves of a SIMD keep its vector ALU busy while
 // others wait for LDS, copies or their own MFMAs: at most 128 registers per wave, two tile stages (32 KB) per workgroup, tiles
 // copied global -> LDS directly (no staging registers), fragments read a few ahead of their MFMA.
-// Measured: 16 heads x 4680 queries x up to 512 key tiles 598 -> 465 us (444 now, with copies that follow runs and a cheaper merge) (706 -> 908 TFLOP/s; 64 heads: 980) against tiles
-// staged through registers at two workgroups per compute unit.  Not better: three workgroups (479 us), eight waves per
+// Measured: 16 heads x 4680 queries x up to 512 key tiles 598 -> 465 us (706 -> 908 TFLOP/s; 64 heads: 980) against tiles
+// staged through registers at two workgroups per compute unit; since then 457 -> 441 by a cheaper merge and -> 432 by copies that
+// follow runs.  Not better: three workgroups (479 us), eight waves per
 // workgroup (481), the next tile's scores computed between this tile's weights (523: needs 168 registers).  Without its
 // copies the kernel would take 11 % less, without the PV half 25 % less.
 #ifndef PF_ATTN_D64_H

@@ -113,7 +113,8 @@ struct PlanCosts {
 static const PlanCosts kCostsDirect = {8.0, 2.0, 2.0};
 static const PlanCosts kCostsQueue = {4.0, 1.0, 2.0};
 // Charged 2 and 3, as before partial results were parked in the order the threads hold them and read back without emptying an L2, heads
-// were cut too coarsely (12 heads x 1560 queries x up to 514 tiles, six layers: 245 blocks a layer, 1031 us; now up to 343, 993).
+// were cut too coarsely (12 heads x 1560 queries x up to 514 tiles, six layers: 245 blocks a layer, 1018 us; now up to 343, 958; 91
+// random launches that are cut otherwise take 0.990 of their time on average, 0.67 to 1.05).
 // 1 and 1 or 2 and 1 cut too finely (8 heads x 1560 queries, 45 frames: 419 -> 431 us; with 1 and 2 419).  The former
 // charges still say which launches are cut at all.
 static const PlanCosts kCostsQueueCut = {4.0, 2.0, 3.0};
@@ -125,7 +126,11 @@ static const PlanCosts kCostsD64 = {2.0, 0.7, 0.7};  // a tile takes four times 
 // blocks leave most of the chip idle (5 heads x 666 queries x up to 58 tiles: 25 us against 57).  The fixed cost is the one of a
 // launch whose blocks are mostly taken over by other dies (12 heads x 1560 queries x 25 tiles: 55 us as thin blocks, 45 us as full
 // ones).  Parking was charged 0.25 to 1 at first: launches of split thin blocks took 5 to 20 tiles longer than replayed, 4 per
-// block (7 heads x 1380 queries x up to 54 tiles: 65 us as 704 thin blocks in halves, 55 us as full ones).
+// block (7 heads x 1380 queries x up to 54 tiles: 65 us as 704 thin blocks in halves, 55 us as full ones).  All of this was fitted when
+// merges and border steps cost both forms more than now.  Looked at since over 220 random launches whose replays lie within 0.6 to 1
+// of each other: the choice takes 0.705 of the full form's time on average and more than 1.02 of it 7 times (up to 1.16: 35 heads x
+// 204 queries x 5 tiles, frames of 31 tokens, 18.4 us against 15.8; 27 x 82 x 662, 150 against 130), and in 16 of the 31 that it
+// leaves to the full form thin items would take at least 5 % less.
 static const double kThinTile = 0.30, kThinBlock = 5.5, kThinPark = 4.0;
 // ... must finish this much earlier than full ones by the replay, which is good to about a tenth; and what kCostsQueue.merge, fitted to
 // launches of two to four segments a head, charges too much for one with many: at 3 per partial, 20 segments were replayed at 122

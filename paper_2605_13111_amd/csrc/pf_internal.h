@@ -161,7 +161,7 @@ static inline PfWorkLayout pf_work_layout(int n_heads, int n_qt, long long max_b
   return L;
 }
 
-// bytes of one partial-result slot: O [bq][D] fp32, then m [bq], l [bq]
+// bytes of one partial-result slot: O fp32 (bq * D values in the order in which the workgroup's threads hold them), then m [bq], l [bq]
 PF_HD size_t pf_partial_bytes(int bq, int head_dim) { return (size_t)bq * (head_dim + 2) * sizeof(float); }
 constexpr size_t PF_STATIC_SCRATCH_BYTES = 160ull << 20;   // the library's own array for them (pf_ragged_attn_fwd_static)
 
