@@ -1567,7 +1567,7 @@ static int launch_attn(const AttnParams &P, int head_dim, int variant, int n_blo
                        dim3(4 * 64), 0, stream, P);
   else if (head_dim == 128 && variant == 0)
     hipLaunchKernelGGL((pf_attn_kernel<128>), dim3(n_blocks), dim3(ATT_THREADS), 0, stream, P);
-  else if (head_dim == 64 && variant == 0 && P.tpf >= PF_BK)
+  else if (head_dim == 64 && variant == 0 && d64_follows_runs(P.tpf, P.q_tokens))
     hipLaunchKernelGGL(pf_attn_d64_kernel<true>, dim3(n_blocks), dim3(D64_WAVES * 64), 0, stream, P);
   else if (head_dim == 64 && variant == 0)
     hipLaunchKernelGGL(pf_attn_d64_kernel<false>, dim3(n_blocks), dim3(D64_WAVES * 64), 0, stream, P);

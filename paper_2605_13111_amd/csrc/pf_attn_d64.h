@@ -33,8 +33,14 @@ __device__ __forceinline__ void d64_copy_rows(__amdgpu_buffer_rsrc_t k, __amdgpu
   __builtin_amdgcn_raw_ptr_buffer_load_lds(v, (lptr_t)(to + D64_TENSOR_BYTES), 16, v0, s1, 1024, 0);
 }
 
-// RUNS: copies follow runs of tiles.  Frames shorter than a tile have none, and there what a run costs to set up comes with every tile:
-// 4 heads x 48 queries at 16 tokens per frame 6.6 us without, 7.2 with runs.
+// RUNS: copies follow runs of tiles.  What a run costs to set up has to be spread over some tiles: 22 heads x 80 queries, 19 frames of
+// 80 tokens take 24.1 us without and 27.1 with runs, 40 heads x 256, 20 frames of 128, 38.9 and 40.5; at 200 tokens per frame both forms
+// take as long (22 x 200 x 19 frames 22.9 and 23.2, 12 x 600 x 40 frames 39.5 and 38.6), and from there on runs gain (12 x 768 x 40 frames of
+// 256 47.2 and 46.3; 24 heads x 1200 queries without history 20.7 and 19.8).  A chunk of six tiles is a run of its own: with one, runs
+// gain from frames of two tiles on (24 heads x 384 queries without history 8.93 and 8.69, behind 57 frames of 128 tokens the same).
+__device__ __host__ constexpr bool d64_follows_runs(int tpf, int q_tokens) {
+  return tpf >= 4 * PF_BK || (tpf >= 2 * PF_BK && q_tokens >= 6 * PF_BK);
+}
 template <bool RUNS>
 __global__ __launch_bounds__(D64_WAVES * 64, 4) void pf_attn_d64_kernel(AttnParams P) {
   typedef Thin<64> C;
@@ -65,7 +71,7 @@ __global__ __launch_bounds__(D64_WAVES * 64, 4) void pf_attn_d64_kernel(AttnPara
     if constexpr (!RUNS) {
       if (u >= n_tiles) return;
       const int t = tw + u * PF_BK;
-      if (t >= R.at.end && R.at.j < H.n_sel) thin_locate<64, false>(R, t, H);
+      if (t >= R.at.end) thin_locate<64, false>(R, pf_min(t, H.lkv - 1), H);
       thin_copy<64, false, D64_ROWS, false>(R, t, H, mine + stage, lane);
       thin_copy<64, true, D64_ROWS, false>(R, t, H, mine + stage + D64_TENSOR_BYTES, lane);
       return;
@@ -73,7 +79,7 @@ __global__ __launch_bounds__(D64_WAVES * 64, 4) void pf_attn_d64_kernel(AttnPara
     if (__builtin_expect(run_n <= 0, 0)) {
       if (u < n_tiles) {
         const int t = tw + u * PF_BK;
-        thin_follow<64>(R, t, H);
+        thin_follow<64, D64_ROWS>(R, t, H);
         const int room = R.at.end - t - D64_ROWS;
         const unsigned rb = (unsigned)(R.at.stride * 2);
         run_tile = PF_BK * rb;

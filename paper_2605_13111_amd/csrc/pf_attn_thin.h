@@ -83,14 +83,14 @@ __device__ __forceinline__ void thin_locate(ThinRuns &R, int t, const HeadKV &H)
   if (LONG && H.tpf >= THIN_AHEAD) R.next_slot = thin_next_slot<D>(j, H);
   R.at = thin_run<D>(j, slot, H);
 }
-template <int D>
+template <int D, int ROWS = THIN_KEYS>                           // ROWS: of a step
 __device__ __forceinline__ void thin_follow(ThinRuns &R, int t, const HeadKV &H) {
   if (__builtin_expect(t < R.at.end || R.at.j >= H.n_sel, 1)) return;
   if (H.tpf >= THIN_AHEAD) {                                     // no frame is stepped over
     const int slot = R.next_slot;
     R.next_slot = thin_next_slot<D>(R.at.j + 1, H);
     R.at = thin_run<D>(R.at.j + 1, slot, H);
-  } else if (H.tpf >= THIN_KEYS || t >= H.hist_tokens) {         // shorter frames' rows are looked up one by one: R.at stays behind
+  } else if (H.tpf >= ROWS || t >= H.hist_tokens) {              // shorter frames' rows are looked up one by one: R.at stays behind
     thin_locate<D>(R, t, H);
   }
 }
