@@ -3,9 +3,7 @@
 #include <stdlib.h>
 #include <string.h>
 #include <algorithm>
-#include <functional>
 #include <mutex>
-#include <queue>
 #include <unordered_map>
 #include <vector>
 #include "pf_internal.h"
@@ -159,33 +157,68 @@ static LaunchShape launch_shape(int variant, int head_dim, int q_tokens, bool qu
   return S;
 }
 
+// A worker of the replay as one number, by which the heap gives the one who is free first (equal times: the lower die): times are not
+// negative, so their bits are ordered as they are.  A worker who takes a block is given back with a later time: the hole at the top sinks
+// along the earlier children and he rises from the bottom, where most stay.  Taken out and put in again as two steps, and with memory of
+// its own for every replay, a plan took 2.8 ms on average over 400 random launches at head_dim 128 (up to 39), now 0.7 (up to 10).
+typedef unsigned __int128 Worker;
+static Worker worker(double free_at, int home) {
+  unsigned long long bits;
+  memcpy(&bits, &free_at, sizeof(bits));
+  return (Worker)bits << 8 | (unsigned)home;
+}
+static double free_at(Worker w) {
+  const unsigned long long bits = (unsigned long long)(w >> 8);
+  double t;
+  memcpy(&t, &bits, sizeof(t));
+  return t;
+}
+static void replace_top(std::vector<Worker> &heap, Worker w) {
+  Worker *const a = heap.data();
+  const size_t n = heap.size();
+  size_t at = 0, c = 1;
+  for (; c + 1 < n; c = 2 * at + 1) {
+    c += a[c + 1] < a[c];
+    a[at] = a[c];
+    at = c;
+  }
+  if (c < n) {
+    a[at] = a[c];
+    at = c;
+  }
+  for (; at > 0 && w < a[(at - 1) / 2]; at = (at - 1) / 2) a[at] = a[(at - 1) / 2];
+  a[at] = w;
+}
+struct ReplayMemory {                                // kept over the replays of one plan
+  std::vector<int> order, nsegs, len;
+  std::vector<double> teams[PF_NUM_XCD];             // per die: the cost of each team (n_qt equal blocks), in launch order
+  std::vector<Worker> workers;
+};
+
 // Finish time of the launch in which head h has key tiles n_kvt[h] cut into segments of at most seg[h] tiles; of one that takes at
-// least `bound`, maybe only that much of it is known (a plan takes 1.0 ms on average at head_dim 128 and 0.23 at 64, with whole replays
-// 1.8 and 0.71).
-static double model_finish(const std::vector<int> &n_kvt, const std::vector<int> &seg, const LaunchShape &S, double bound) {
-  typedef std::priority_queue<double, std::vector<double>, std::greater<double> > MinHeap;
+// least `bound`, maybe only that much of it is known.
+static double model_finish(const std::vector<int> &n_kvt, const std::vector<int> &seg, const LaunchShape &S, double bound, ReplayMemory &M) {
   const PlanCosts &C = S.d64 ? kCostsD64 : !S.queue ? kCostsDirect : S.cut ? kCostsQueueCut : kCostsQueue;
   const int H = (int)n_kvt.size();
   // heads by descending segment length (ties: head id), as the index kernel ranks them
-  std::vector<int> order(H), nsegs(H), len(H);
+  M.order.resize(H), M.nsegs.resize(H), M.len.resize(H);
   for (int h = 0; h < H; ++h) {
-    order[h] = h;
-    nsegs[h] = pf_max(1, pf_ceil_div(n_kvt[h], seg[h]));
-    len[h] = pf_ceil_div(n_kvt[h], nsegs[h]);
+    M.order[h] = h;
+    M.nsegs[h] = pf_max(1, pf_ceil_div(n_kvt[h], seg[h]));
+    M.len[h] = pf_ceil_div(n_kvt[h], M.nsegs[h]);
   }
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return len[a] > len[b]; });
-  // per die: the cost of each team (n_qt equal blocks), in launch order
-  std::vector<std::vector<double> > teams(PF_NUM_XCD);
+  std::sort(M.order.begin(), M.order.end(), [&](int a, int b) { return M.len[a] != M.len[b] ? M.len[a] > M.len[b] : a < b; });
+  for (int x = 0; x < PF_NUM_XCD; ++x) M.teams[x].clear();
   int k = 0;                                         // team rank, as in the index kernel
   for (int o = 0; o < H; ++o) {
-    const int nk = n_kvt[order[o]], nseg = nsegs[order[o]];
+    const int nk = n_kvt[M.order[o]], nseg = M.nsegs[M.order[o]];
     for (int sgi = 0; sgi < nseg; ++sgi, ++k) {
       const int row = k / PF_NUM_XCD, col = k % PF_NUM_XCD;
       const int xcd = (row & 1) ? PF_NUM_XCD - 1 - col : col;
       const int tiles = pf_seg_begin(nk, nseg, sgi + 1) - pf_seg_begin(nk, nseg, sgi);
       // the merge falls to whichever segment arrives last; the replay charges it to the last one launched
       const double park = (nseg > 1 ? C.split : 0.0) + (nseg > 1 && sgi == nseg - 1 ? C.merge * nseg : 0.0);
-      teams[xcd].push_back(S.thin ? kThinTile * tiles + kThinBlock + (nseg > 1 ? kThinPark : 0.0) : tiles + C.block + park);
+      M.teams[xcd].push_back(S.thin ? kThinTile * tiles + kThinBlock + (nseg > 1 ? kThinPark : 0.0) : tiles + C.block + park);
     }
   }
   // No schedule ends before its work spread evenly would (over a die where dies keep to their lists, over the chip otherwise), and none
@@ -193,7 +226,7 @@ static double model_finish(const std::vector<int> &n_kvt, const std::vector<int>
   double even = 0.0;
   for (int x = 0; x < PF_NUM_XCD; ++x) {
     double die = 0.0;
-    for (double t : teams[x]) die += t * S.n_qt;
+    for (double t : M.teams[x]) die += t * S.n_qt;
     even = S.queue ? even + die / PF_NUM_XCD : die > even ? die : even;
   }
   even /= S.slots_per_die;
@@ -201,37 +234,32 @@ static double model_finish(const std::vector<int> &n_kvt, const std::vector<int>
   double finish = 0.0;
   if (!S.queue) {
     for (int x = 0; x < PF_NUM_XCD; ++x) {
-      MinHeap cu;
-      for (int c = 0; c < S.slots_per_die; ++c) cu.push(0.0);
-      for (size_t i = 0; i < teams[x].size() * (size_t)S.n_qt; ++i) {
-        const double e = cu.top() + teams[x][i / S.n_qt];
-        cu.pop();
-        cu.push(e);
-        finish = e > finish ? e : finish;
-        if (finish >= bound) return finish;
-      }
+      M.workers.assign(S.slots_per_die, worker(0.0, 0));
+      for (double t : M.teams[x])
+        for (int i = 0; i < S.n_qt; ++i) {
+          const double e = free_at(M.workers[0]) + t;
+          replace_top(M.workers, worker(e, 0));
+          finish = e > finish ? e : finish;
+          if (finish >= bound) return finish;
+        }
     }
     return finish;
   }
   // work queue: the worker that frees up first takes the next block of its die's list, else of the next die's
-  typedef std::pair<double, int> Worker;             // (time it is free, home die)
-  std::priority_queue<Worker, std::vector<Worker>, std::greater<Worker> > workers;
-  for (int w = 0; w < PF_NUM_XCD * S.slots_per_die; ++w) workers.push(Worker(0.0, w % PF_NUM_XCD));
-  size_t next[PF_NUM_XCD] = {};
-  while (!workers.empty()) {
-    const Worker w = workers.top();
-    workers.pop();
-    for (int hop = 0; hop < PF_NUM_XCD; ++hop) {
-      const int x = (w.second + hop) % PF_NUM_XCD;
-      if (next[x] < teams[x].size() * (size_t)S.n_qt) {
-        const double e = w.first + teams[x][next[x] / S.n_qt];
-        ++next[x];
-        finish = e > finish ? e : finish;
-        if (finish >= bound) return finish;
-        workers.push(Worker(e, w.second));
-        break;
-      }
-    }
+  M.workers.resize(PF_NUM_XCD * S.slots_per_die);
+  for (size_t w = 0; w < M.workers.size(); ++w) M.workers[w] = worker(0.0, (int)w / S.slots_per_die);   // in order, so a heap
+  size_t next[PF_NUM_XCD] = {}, left = 0;            // the team that a die hands out, and blocks of it that are gone
+  int gone[PF_NUM_XCD] = {};
+  for (int x = 0; x < PF_NUM_XCD; ++x) left += M.teams[x].size() * (size_t)S.n_qt;
+  for (; left > 0; --left) {
+    const int home = (int)(M.workers[0] & 255);
+    int x = home;
+    while (next[x] == M.teams[x].size()) x = (x + 1) % PF_NUM_XCD;
+    const double e = free_at(M.workers[0]) + M.teams[x][next[x]];
+    if (++gone[x] == S.n_qt) gone[x] = 0, ++next[x];
+    replace_top(M.workers, worker(e, home));
+    finish = e > finish ? e : finish;
+    if (finish >= bound) return finish;
   }
   return finish;
 }
@@ -254,7 +282,7 @@ struct Remembered {
 std::unordered_map<std::vector<int>, Remembered, KeyHash> g_plan_cache;
 
 // Segment lengths for one kernel; returns the replayed finish time.
-double plan_segments(const std::vector<int> &n_kvt, const LaunchShape &S, bool uniform_only, PfSegPlan *plan) {
+double plan_segments(const std::vector<int> &n_kvt, const LaunchShape &S, bool uniform_only, PfSegPlan *plan, ReplayMemory &M) {
   const int H = (int)n_kvt.size();
   // Many candidate lengths cut the heads into the same segment counts: the replay runs once per distinct cut.
   std::unordered_map<std::vector<int>, double, KeyHash> seen;
@@ -264,7 +292,7 @@ double plan_segments(const std::vector<int> &n_kvt, const LaunchShape &S, bool u
     for (int h = 0; h < H; ++h) cut[h] = pf_max(1, pf_ceil_div(n_kvt[h], seg[h]));
     auto f = seen.find(cut);
     if (f != seen.end()) return f->second;
-    const double t = model_finish(n_kvt, seg, S, bound);
+    const double t = model_finish(n_kvt, seg, S, bound, M);
     seen.emplace(cut, t);
     return t;
   };
@@ -363,7 +391,8 @@ int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
   const std::vector<int> n_kvt(key.begin(), key.begin() + H);
   Remembered R;
   R.variant = variant;
-  double finish = plan_segments(n_kvt, S, uniform_only, plan);
+  ReplayMemory M;
+  double finish = plan_segments(n_kvt, S, uniform_only, plan, M);
   // A launch whose heads fit one segment each needs no workspace, and callers may rely on that: the forms below are not
   // allowed to bring partial results into it.
   bool splits = plan_splits(n_kvt, *plan);
@@ -380,12 +409,12 @@ int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
     const bool over = plan_partials(n_kvt, *plan, S.n_qt) * slot > PF_STATIC_SCRATCH_BYTES;
     PfSegPlan base;
     memset(&base, 0, sizeof(base));
-    double base_finish = plan_segments(n_kvt, before, true, &base);
+    double base_finish = plan_segments(n_kvt, before, true, &base, M);
     // step 2 only betters step 1: it leaves a launch cut that step 1 cuts, unless whole heads finish earlier
-    const bool cut_anyway = plan_splits(n_kvt, base) && model_finish(n_kvt, n_kvt, before, INFINITY) >= base_finish;
+    const bool cut_anyway = plan_splits(n_kvt, base) && model_finish(n_kvt, n_kvt, before, INFINITY, M) >= base_finish;
     if (!uniform_only && (over || !cut_anyway)) {
       memset(&base, 0, sizeof(base));
-      base_finish = plan_segments(n_kvt, before, false, &base);
+      base_finish = plan_segments(n_kvt, before, false, &base, M);
     }
     splits = plan_splits(n_kvt, base);
     if (!splits || (over && plan_partials(n_kvt, base, S.n_qt) * slot <= PF_STATIC_SCRATCH_BYTES)) {
@@ -404,7 +433,7 @@ int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
     }
     PfSegPlan fp;
     memset(&fp, 0, sizeof(fp));
-    if (fine.min_seg < S.min_seg && plan_segments(n_kvt, fine, uniform_only, &fp) < finish) *plan = fp;
+    if (fine.min_seg < S.min_seg && plan_segments(n_kvt, fine, uniform_only, &fp, M) < finish) *plan = fp;
   }
   // Small launches: with 32 query rows per block there are eight times the blocks, at 2.4 times the time per row; which side wins is
   // left to the replay.  Looked at only where it could: its work spread evenly over the chip would finish earlier.
@@ -417,7 +446,7 @@ int pf_auto_plan(const pf_pool *pool, int T, int q_tokens, PfSegPlan *plan) {
     if (even < full && total * thin.n_qt <= PF_THIN_MAX_BLOCKS) {
       PfSegPlan tp;
       memset(&tp, 0, sizeof(tp));
-      if (plan_segments(n_kvt, thin, true, &tp) < kThinGain * full && (splits || !plan_splits(n_kvt, tp))) {
+      if (plan_segments(n_kvt, thin, true, &tp, M) < kThinGain * full && (splits || !plan_splits(n_kvt, tp))) {
         *plan = tp;
         R.variant = PF_THIN_VARIANT;
       }
