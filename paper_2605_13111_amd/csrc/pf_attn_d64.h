@@ -36,10 +36,11 @@ __device__ __forceinline__ void d64_copy_rows(__amdgpu_buffer_rsrc_t k, __amdgpu
 // RUNS: copies follow runs of tiles.  What a run costs to set up has to be spread over some tiles: 22 heads x 80 queries, 19 frames of
 // 80 tokens take 24.1 us without and 27.1 with runs, 40 heads x 256, 20 frames of 128, 38.9 and 40.5; at 200 tokens per frame both forms
 // take as long (22 x 200 x 19 frames 22.9 and 23.2, 12 x 600 x 40 frames 39.5 and 38.6), and from there on runs gain (12 x 768 x 40 frames of
-// 256 47.2 and 46.3; 24 heads x 1200 queries without history 20.7 and 19.8).  A chunk of six tiles is a run of its own: with one, runs
-// gain from frames of two tiles on (24 heads x 384 queries without history 8.93 and 8.69, behind 57 frames of 128 tokens the same).
+// 256 47.2 and 46.3; 24 heads x 1200 queries without history 20.7 and 19.8).  A long chunk is a run of its own: from eight tiles
+// on, runs gain at frames of two tiles already (24 heads x 600 queries without history 12.7 and 12.3, behind 40 frames of 200 tokens 39.5 and
+// 38.6); one of six loses with history in front of it (40 heads x 390, a frame of 195 tokens 13.0 and 13.5).
 __device__ __host__ constexpr bool d64_follows_runs(int tpf, int q_tokens) {
-  return tpf >= 4 * PF_BK || (tpf >= 2 * PF_BK && q_tokens >= 6 * PF_BK);
+  return tpf >= 4 * PF_BK || (tpf >= 2 * PF_BK && q_tokens >= 8 * PF_BK);
 }
 template <bool RUNS>
 __global__ __launch_bounds__(D64_WAVES * 64, 4) void pf_attn_d64_kernel(AttnParams P) {

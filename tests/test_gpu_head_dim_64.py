@@ -29,7 +29,7 @@ def test_attention_head_dim_64(tpf, chunks, Lq, layout, seg_tiles):
 @pytest.mark.gpu
 @pytest.mark.parametrize("layout", ["packed", "model"])
 @pytest.mark.parametrize("tpf,frames,Lq", [
-    (127, 5, 384), (128, 5, 383), (128, 5, 384), (130, 4, 390), (255, 3, 255), (255, 3, 510), (256, 3, 256), (257, 3, 70), (300, 4, 17)])
+    (127, 5, 512), (128, 5, 511), (128, 5, 512), (130, 4, 520), (255, 3, 255), (255, 3, 510), (256, 3, 256), (257, 3, 70), (300, 4, 17)])
 def test_attention_head_dim_64_on_both_sides_of_runs(tpf, frames, Lq, layout):
     """Frames and chunks on either side of the line from which copies follow runs of tiles: frames that are whole tiles and frames that leave
     some rows over, chunks of less than a wave's rows and of several tiles."""
