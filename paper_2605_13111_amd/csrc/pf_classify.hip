@@ -4,9 +4,10 @@
 // would use.  Three kernels share the steps:
 //   pf_classify_batch_kernel   sequences of 4 to 72 frames (the paper analyses 69): a workgroup's sequences side by side in LDS, the
 //                              spectra of 16 at a time as a matrix product on the fp64 matrix cores
-//   pf_classify_rounds_kernel  73 to 256 frames: the same products, 16 sequences at a time through LDS
-//   pf_classify_kernel         others, and launches of few long ones: one workgroup per sequence, a direct DFT (their tables do not fit beside
-//                              16 sequences in LDS)
+//   pf_classify_rounds_kernel  73 to 256 frames, and some shorter ones in launches of medium size: the same products, 16 sequences at a time
+//                              through LDS
+//   pf_classify_kernel         launches of few sequences, and the longest (their tables do not fit beside 16 sequences in LDS): one workgroup
+//                              per sequence, a direct DFT
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <type_traits>
@@ -144,8 +145,8 @@ __global__ __launch_bounds__(CLS_THREADS) void pf_classify_kernel(ClassifyParams
 // Bound: the chain of one workgroup, and the fetching of its code, most of which runs once: 92 160 sequences of 69 frames take
 // 21 us (with 62 us before: four waves in rounds of 16 sequences between barriers, folded into LDS, twiddles gathered by index), of
 // which their 25 MB need 5 and the votes 4.  On the way: raw values through registers into padded rows 25 us, with every loop
-// unrolled (3200 instructions instead of 2200) 29.  48 sequences take as long as before (12 us, the call), 6400 13.0 us against 13.8,
-// 23 040 of 72 frames 14.8 against 23.7, 92 160 of 24 frames 16.0 against 36.1.
+// unrolled (3200 instructions instead of 2200) 29.  6400 take 13.0 us against 13.8, 23 040 of 72 frames 14.8 against 23.7, 92 160 of
+// 24 frames 16.0 against 36.1; few sequences, and some lengths in launches of medium size, are left to the forms below.
 // ---------------------------------------------------------------------------------------------------
 constexpr int CLS_BATCH_MIN = 4;        // shortest sequence with a spectrum (three differences)
 constexpr int CLS_STEPS = 9;            // matrix steps: sequences of at most 72 frames (with 16, for 128 frames, the folded operands of a
@@ -428,13 +429,16 @@ __global__ __launch_bounds__(CLS_BATCH_THREADS) void pf_classify_batch_kernel(Cl
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Batched form for sequences whose operands do not fit beside each other in LDS or registers (73 to 256 frames).  A workgroup walks
+// Batched form for sequences whose operands do not fit beside each other in LDS or registers (73 to 256 frames), and for those where it
+// is the shorter one (see the dispatch).  A workgroup walks
 // a contiguous run of sequences, 16 at a time (four per wave): a sequence that the sign
 // rates decide is finished there; the others' windowed and folded differences go into an LDS buffer of `cap` rows, and when the
 // buffer is full (or the run ends) their spectra are computed together, as above; the twiddles are read from a table of
 // N points by the index k m mod N, which every lane carries along by adding 4 k mod N.
 // ---------------------------------------------------------------------------------------------------
-constexpr int CLS_FEW_HIST = 80, CLS_FEW_SEQ = 768;   // longer sequences than this, but fewer: a workgroup each
+constexpr int CLS_FEW_SEQ = 768;        // fewer: a workgroup each
+// Shorter and longer sequences than these, but fewer, go by rounds though they would fit the batched form
+constexpr int CLS_BATCH_FROM = 11, CLS_BATCH_TO = 70, CLS_BATCH_SEQ = 4608;
 constexpr int CLS_ROUNDS_HIST = 256;    // its longest sequence (16 rows and the tables: 72 KB of LDS)
 constexpr int CLS_ROUNDS_LDS = 53 * 1024;  // three workgroups per compute unit where that leaves at least one round's rows
 constexpr int CLS_ROUNDS_WAVES = 4;            // of the batched form
@@ -704,16 +708,21 @@ extern "C" int pf_classify_heads(const float *logits, int n_prompts, int n_heads
   P.n_hist = n_hist;
   P.alpha = alpha;
   P.beta = beta;
-  // Few long sequences finish earlier in a workgroup each: of 240 frames 48 take 13.8 us against 23.1 us in batches, 400 17.8 against
-  // 23.4 (1920 of 200 frames 56.6 against 21.5); of 100 frames 48 take 12.9 against 13.7, of 69 or fewer as long either way.
-  const bool few = n_hist > CLS_FEW_HIST && (long long)n_prompts * n_heads < CLS_FEW_SEQ;
+  // Few sequences finish earlier in a workgroup each: of 240 frames 48 take 13.8 us against 23.1 us in batches, 400 17.8 against
+  // 23.4 (1920 of 200 frames 56.6 against 21.5); of 69 frames 48 take 8.5 (11.4 in batches, 11.5 by rounds; kernels alone), 756 10.1 (11.8, 12.0), 1276
+  // 12.3 (12.1, 12.2), 2000 16.8 (12.0, 12.1); of 13 frames 756 8.2 (9.4, 9.5), 1276 10.0 (9.7, 9.7).
+  // The batched form's tables and its few left-over bins have to pay: 2000 of 8 frames 9.6 against 9.4 by rounds, 4000 9.9 against 9.6, 6400 10.2
+  // against 10.6; of 72 2000 12.7 against 12.3, 4000 13.1 against 12.6, 6400 13.2 against 14.4; between 11 and 70 frames it is
+  // the shorter one throughout (1000 of 12 frames 9.5 both, of 69 11.8 against 12.0).
+  const int n_seq = n_prompts * n_heads;
+  const bool few = n_seq < CLS_FEW_SEQ, batch = n_seq >= CLS_BATCH_SEQ || (n_hist >= CLS_BATCH_FROM && n_hist <= CLS_BATCH_TO);
   if (n_hist < CLS_BATCH_MIN || n_hist > CLS_ROUNDS_HIST || few) {
-    hipLaunchKernelGGL(pf_classify_kernel, dim3(n_prompts * n_heads), dim3(CLS_THREADS), 0, (hipStream_t)stream, P);
-  } else if (cls_inner(n_hist - 1) <= 4 * CLS_STEPS) {
+    hipLaunchKernelGGL(pf_classify_kernel, dim3(n_seq), dim3(CLS_THREADS), 0, (hipStream_t)stream, P);
+  } else if (batch && cls_inner(n_hist - 1) <= 4 * CLS_STEPS) {
     // a workgroup per compute unit, as many sequences each, in as few rounds of equal size as LDS allows
     ClassifyBatchParams B;
     B.c = P;
-    B.n_seq = n_prompts * n_heads;
+    B.n_seq = n_seq;
     B.per_wg = pf_ceil_div(B.n_seq, CLS_WGS);
     const size_t tables = cls_lds_bytes(n_hist, 0), each = cls_lds_bytes(n_hist, 1) - tables;
     B.cap = pf_ceil_div(B.per_wg, pf_ceil_div(B.per_wg, (int)((CLS_LDS - tables) / each)));
@@ -723,7 +732,7 @@ extern "C" int pf_classify_heads(const float *logits, int n_prompts, int n_heads
     // the longer the buffer, the fuller its groups of 16 rows
     ClassifyBatchParams B;
     B.c = P;
-    B.n_seq = n_prompts * n_heads;
+    B.n_seq = n_seq;
     B.cap = CLS_ROUNDS_MAX_CAP;
     while (B.cap > CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE && cls_rounds_lds_bytes(n_hist, B.cap) > CLS_ROUNDS_LDS) B.cap -= 16;
     const int batches = pf_ceil_div(B.n_seq, CLS_ROUNDS_WAVES * CLS_ROUNDS_PER_WAVE);

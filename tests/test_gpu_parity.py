@@ -502,9 +502,8 @@ def test_pool_that_disagrees_with_the_host_plan_is_reported_and_attention_writes
                                                       (2, 3, 257), (41, 330, 12), (64, 12, 129), (64, 12, 256), (128, 360, 69)])
 def test_head_classification_batched_form_at_its_edges(n_prompts, n_heads, n_hist):
     """The batched form (16 spectra at a time on the matrix cores): shortest and longest sequence, both parities of the
-    transform length, row and bin counts that are no multiple of 16; 128 x 360 sequences of 69 frames, of which a workgroup takes
-    64 and its row buffer holds 48, so that the buffer is emptied in the middle and filled again.  Fewer than 768 sequences of
-    more than 80 frames, and 257 frames, take the other form.  Types, periods (exact quotients) and votes equal the oracle's."""
+    transform length, row and bin counts that are no multiple of 16; 128 x 360 sequences of 69 frames, 180 to a workgroup.  Fewer than 768
+    sequences, and 257 frames, take the form without batches.  Types, periods (exact quotients) and votes equal the oracle's."""
     from oracle import classify as OC
     lg, _ = synth.head_logits(n_prompts, n_heads, n_hist, seed=900 + n_hist)
     if n_hist == 12 or n_prompts == 128:
